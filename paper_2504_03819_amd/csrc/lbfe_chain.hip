@@ -80,6 +80,62 @@ template <int W> __device__ inline double smooth2(const double *g, int c) {
     return A1 * r0 + A0 * r1 + A1 * r2;
 }
 
+// In-plane parts of grad mu at index c of an LDS plane with row stride W:
+// Dx Wy g, Wx Dy g, Wx Wy g.
+template <int W> __device__ inline void plane_grad(const double *g, int c, double &Av, double &Bv, double &Cv) {
+    const double l0 = g[c - W - 1], l1 = g[c - W], l2 = g[c - W + 1];
+    const double m0 = g[c - 1], m1 = g[c], m2 = g[c + 1];
+    const double h0 = g[c + W - 1], h1 = g[c + W], h2 = g[c + W + 1];
+    Av = A1 * (l2 - l0) + A0 * (m2 - m0) + A1 * (h2 - h0);
+    Bv = A1 * (h0 - l0) + A0 * (h1 - l1) + A1 * (h2 - l2);
+    Cv = A1 * (A1 * l0 + A0 * l1 + A1 * l2) + A0 * (A1 * m0 + A0 * m1 + A1 * m2) +
+         A1 * (A1 * h0 + A0 * h1 + A1 * h2);
+}
+
+// F and phi at a fluid node from the in-plane parts of grad mu in the planes
+// below, at and above it, its density, mu and momentum.
+template <class real>
+__device__ inline void force_phi(double Aa, double Ab, double Ac, double Ba, double Bb, double Bc, double Ca, double Cc,
+                                 double rd, double mu, const real (&j)[3], real &Fx, real &Fy, real &Fz,
+                                 real (&phi)[3]) {
+    const double gx = 0.5 * (A1 * Aa + A0 * Ab + A1 * Ac);
+    const double gy = 0.5 * (A1 * Ba + A0 * Bb + A1 * Bc);
+    const double gz = 0.5 * (Cc - Ca);
+    const double c1 = 1.0 / 3.0 - rd;
+    Fx = (real)(c1 * gx);
+    Fy = (real)(c1 * gy);
+    Fz = (real)(c1 * gz);
+    const real ir = (real)1 / (real)rd;
+    const real ux = (j[0] + (real)0.5 * Fx) * ir;
+    const real uy = (j[1] + (real)0.5 * Fy) * ir;
+    const real uz = (j[2] + (real)0.5 * Fz) * ir;
+    // p_m - rho/3 with p_m = (1 + mu)/3
+    const real c2 = (real)((1.0 + mu - rd) * (1.0 / 3.0));
+    phi[0] = c2 * ux;
+    phi[1] = c2 * uy;
+    phi[2] = c2 * uz;
+}
+
+// In-plane parts of d_x phi_x, d_y phi_y, d_z phi_z at index c.
+template <int W, class real>
+__device__ inline void plane_div(const real *gx, const real *gy, const real *gz, int c, real &X, real &Y, real &Z) {
+    const real w1r = (real)A1, w0r = (real)A0;
+    X = w1r * (gx[c - W + 1] - gx[c - W - 1]) + w0r * (gx[c + 1] - gx[c - 1]) + w1r * (gx[c + W + 1] - gx[c + W - 1]);
+    Y = w1r * (gy[c + W - 1] - gy[c - W - 1]) + w0r * (gy[c + W] - gy[c - W]) + w1r * (gy[c + W + 1] - gy[c - W + 1]);
+    Z = w1r * (w1r * gz[c - W - 1] + w0r * gz[c - W] + w1r * gz[c - W + 1]) +
+        w0r * (w1r * gz[c - 1] + w0r * gz[c] + w1r * gz[c + 1]) +
+        w1r * (w1r * gz[c + W - 1] + w0r * gz[c + W] + w1r * gz[c + W + 1]);
+}
+// Q from the in-plane parts in the planes below, at and above the node.
+template <class real>
+__device__ inline void q_of(real Xa, real Xb, real Xc, real Ya, real Yb, real Yc, real Za, real Zc, real &qx, real &qy,
+                            real &qz) {
+    const real h = (real)(-1.5), w1r = (real)A1, w0r = (real)A0;
+    qx = h * (w1r * Xa + w0r * Xb + w1r * Xc);
+    qy = h * (w1r * Ya + w0r * Yb + w1r * Yc);
+    qz = h * (Zc - Za);
+}
+
 template <int P, bool WALLS>
 __global__ __launch_bounds__(CB) void k_chain(KP kp, const double *__restrict__ rho, const double *__restrict__ mu0,
                                               const void *jq, double *__restrict__ mu, void *Fq, void *Qq, int cz) {
@@ -220,15 +276,7 @@ __global__ __launch_bounds__(CB) void k_chain(KP kp, const double *__restrict__ 
     // in-plane parts of grad mu from mu plane p at the owned phi point m
     auto abc = [&](int p, int m, double &Av, double &Bv, double &Cv) {
         const int r = tid + m * CB;
-        const int c = (r / WP + 2) * WM + (r % WP + 2);
-        const double *g = sm[p & 1];
-        const double l0 = g[c - WM - 1], l1 = g[c - WM], l2 = g[c - WM + 1];
-        const double m0 = g[c - 1], m1 = g[c], m2 = g[c + 1];
-        const double h0 = g[c + WM - 1], h1 = g[c + WM], h2 = g[c + WM + 1];
-        Av = A1 * (l2 - l0) + A0 * (m2 - m0) + A1 * (h2 - h0);
-        Bv = A1 * (h0 - l0) + A0 * (h1 - l1) + A1 * (h2 - l2);
-        Cv = A1 * (A1 * l0 + A0 * l1 + A1 * l2) + A0 * (A1 * m0 + A0 * m1 + A1 * m2) +
-             A1 * (A1 * h0 + A0 * h1 + A1 * h2);
+        plane_grad<WM>(sm[p & 1], (r / WP + 2) * WM + (r % WP + 2), Av, Bv, Cv);
     };
 
     // wrapped indices of planes k, k+1, k+2, k+3, k+4
@@ -385,6 +433,214 @@ __global__ __launch_bounds__(CB) void k_chain(KP kp, const double *__restrict__ 
     }
 }
 
+// ---------------------------------------------------------------------------
+// The same chain for small grids: a workgroup owns a TX x TY x CZ block,
+// loads the block's whole rho region (halo HR in the plane, 3 in z) at once
+// and then runs the three stencils one after the other.  In each, a thread
+// marches the columns it owns through all planes of the region in registers
+// (the sums of k_chain, in the same order, so the same bits), so the block
+// passes three barriers in all instead of three per plane, and its loads wait
+// for memory once.  The region is recomputed by the neighbouring blocks
+// (mu on 3.5 times the owned nodes at 16 x 8 x 4), which only pays while the
+// march is set by latency: at 32^3 in FP64 the march takes 25.6 us (seven
+// iterations of 3.7 us, half of its 64-wide tile empty), this kernel 6 us.
+// ---------------------------------------------------------------------------
+template <class real, bool WALLS, int TX, int TY, int CZ, int NT>
+__global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restrict__ rho,
+                                                    const double *__restrict__ mu0, const void *jq,
+                                                    double *__restrict__ mu, void *Fq, void *Qq) {
+    // mu one node wider next to walls: Eq. (36) averages it over x +- 1, y +- 1
+    constexpr int HM = WALLS ? 3 : 2, HR = HM + 1;
+    constexpr int WR = TX + 2 * HR, NR = WR * (TY + 2 * HR), ZR = CZ + 6;  // rho region
+    constexpr int WM = TX + 2 * HM, NM = WM * (TY + 2 * HM), ZM = CZ + 4;  // mu region
+    constexpr int WP = TX + 2, NP = WP * (TY + 2), ZP = CZ + 2;            // phi region
+    constexpr int MR = (NR + NT - 1) / NT, MM = (NM + NT - 1) / NT, MP = (NP + NT - 1) / NT;
+    static_assert(TX * TY <= NT, "one owned column per thread");
+    __shared__ double sr[ZR][NR];
+    __shared__ double sm[ZM][NM];
+    __shared__ real sp[ZP][3][NP];
+
+    const int ntx = (kp.nx + TX - 1) / TX;
+    const unsigned ntiles = gridDim.x, nb = gridDim.x * gridDim.y;
+    const unsigned hw = blockIdx.y * gridDim.x + blockIdx.x;
+    const unsigned q = nb >> 3, rem = nb & 7u, xcd = hw & 7u;
+    const unsigned lid = xcd * q + (xcd < rem ? xcd : rem) + (hw >> 3);
+    const int tile = (int)(lid % ntiles), chunk = (int)(lid / ntiles);
+    const int x0 = (tile % ntx) * TX, y0 = (tile / ntx) * TY;
+    const int zs = kp.z0 + chunk * CZ, ze = min(zs + CZ, kp.z1);
+    const int tid = threadIdx.x;
+    const size_t N = kp.N;
+    const real *j = (const real *)jq;
+    real *F = (real *)Fq;
+    real *Q = (real *)Qq;
+    auto fluid = [&](int p) { return WALLS ? (p >= 1 && p <= kp.nz - 2) : true; };
+    // wrapped index of a region coordinate; points past the grid's halo stand
+    // for its last halo point (nothing reads them)
+    auto wrap1 = [&](int v, int n) {
+        v = min(v, n + HR - 1);
+        if (n < HR) return wrap(v, n);
+        return v < 0 ? v + n : (v >= n ? v - n : v);
+    };
+    auto node = [&](int x, int y) { return (unsigned)wrap1(y, kp.ny) * kp.nx + (unsigned)wrap1(x, kp.nx); };
+    // first node of planes zs - 3 .. zs + CZ + 2 (outside a walled box they
+    // wrap to planes whose values are not used)
+    size_t pb[ZR];
+    {
+        int g = wrap(zs - 3, kp.nz);
+#pragma unroll
+        for (int z = 0; z < ZR; ++z) {
+            pb[z] = (size_t)g * kp.plane;
+            g = g + 1 == kp.nz ? 0 : g + 1;
+        }
+    }
+
+    // every load of the block, before the first barrier
+    double m0[MM][ZM];
+    real pj[MP][ZP][3];
+    unsigned orr[MR], om[MM], op[MP];
+#pragma unroll
+    for (int m = 0; m < MR; ++m) {
+        const int r = min(tid + m * NT, NR - 1);
+        orr[m] = node(x0 + r % WR - HR, y0 + r / WR - HR);
+    }
+#pragma unroll
+    for (int m = 0; m < MM; ++m) {
+        const int r = min(tid + m * NT, NM - 1);
+        om[m] = node(x0 + r % WM - HM, y0 + r / WM - HM);
+    }
+#pragma unroll
+    for (int m = 0; m < MP; ++m) {
+        const int r = min(tid + m * NT, NP - 1);
+        op[m] = node(x0 + r % WP - 1, y0 + r / WP - 1);
+    }
+    {
+        double pr[MR][ZR];
+#pragma unroll
+        for (int z = 0; z < ZR; ++z)
+#pragma unroll
+            for (int m = 0; m < MR; ++m) pr[m][z] = rho[pb[z] + orr[m]];
+#pragma unroll
+        for (int z = 0; z < ZM; ++z)
+#pragma unroll
+            for (int m = 0; m < MM; ++m) m0[m][z] = mu0[pb[z + 1] + om[m]];
+#pragma unroll
+        for (int z = 0; z < ZP; ++z)
+#pragma unroll
+            for (int m = 0; m < MP; ++m)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) pj[m][z][c] = j[c * N + pb[z + 2] + op[m]];
+#pragma unroll
+        for (int z = 0; z < ZR; ++z)
+#pragma unroll
+            for (int m = 0; m < MR; ++m)
+                if (tid + m * NT < NR) sr[z][tid + m * NT] = pr[m][z];
+    }
+    __syncthreads();
+
+    // mu of planes zs - 2 .. zs + CZ + 1 (fluid ones)
+#pragma unroll
+    for (int m = 0; m < MM; ++m) {
+        const int r = tid + m * NT;
+        if (r >= NM) continue;
+        const int a = r % WM, b = r / WM, c = (b + 1) * WR + a + 1;
+        const bool own = a >= HM && b >= HM && a < TX + HM && b < TY + HM && x0 + a - HM < kp.nx && y0 + b - HM < kp.ny;
+        double P0 = smooth2<WR>(sr[0], c), P1 = smooth2<WR>(sr[1], c);
+#pragma unroll
+        for (int z = 0; z < ZM; ++z) {
+            const int p = zs - 2 + z;
+            const double P2 = smooth2<WR>(sr[z + 2], c);
+            const double r0 = sr[z + 1][c];
+            const double s27 = A1 * P0 + A0 * P1 + A1 * P2;
+            const double v = m0[m][z] - kp.kappa * 6.0 * (s27 - r0);
+            if (fluid(p)) {
+                sm[z][r] = v;
+                if (own && p >= zs && p < ze) mu[pb[z + 1] + om[m]] = v;
+            }
+            P0 = P1;
+            P1 = P2;
+        }
+    }
+    __syncthreads();
+    if constexpr (WALLS) {  // the solid planes inside the region, Eq. (36)
+        const bool lo = zs <= 2, hi = ze + 1 >= kp.nz - 1;
+        auto wall_mu = [&](int ps, int pf, bool write_out) {
+            const int zw = ps - (zs - 2), zf = pf - (zs - 2);
+#pragma unroll
+            for (int m = 0; m < MM; ++m) {
+                const int r = tid + m * NT, a = r % WM, b = r / WM;
+                if (r >= NM || a < 1 || a > WM - 2 || b < 1 || b > TY + 2 * HM - 2) continue;
+                const double v = smooth2<WM>(sm[zf], r);
+                sm[zw][r] = v;
+                if (write_out && a >= HM && b >= HM && a < TX + HM && b < TY + HM && x0 + a - HM < kp.nx &&
+                    y0 + b - HM < kp.ny)
+                    mu[(size_t)ps * kp.plane + om[m]] = v;
+            }
+        };
+        if (lo) wall_mu(0, 1, zs == 1);
+        if (hi) wall_mu(kp.nz - 1, kp.nz - 2, ze == kp.nz - 1);
+        if (lo || hi) __syncthreads();
+    }
+
+    // F and phi of planes zs - 1 .. zs + CZ
+#pragma unroll
+    for (int m = 0; m < MP; ++m) {
+        const int r = tid + m * NT;
+        if (r >= NP) continue;
+        const int a = r % WP, b = r / WP;
+        const int c = (b + HM - 1) * WM + a + HM - 1, cr = (b + HR - 1) * WR + a + HR - 1;
+        const bool own = a >= 1 && b >= 1 && a <= TX && b <= TY && x0 + a - 1 < kp.nx && y0 + b - 1 < kp.ny;
+        double Aa, Ba, Ca, Ab, Bb, Cb, Ac, Bc, Cc;
+        plane_grad<WM>(sm[0], c, Aa, Ba, Ca);
+        plane_grad<WM>(sm[1], c, Ab, Bb, Cb);
+#pragma unroll
+        for (int z = 0; z < ZP; ++z) {
+            const int p = zs - 1 + z;
+            plane_grad<WM>(sm[z + 2], c, Ac, Bc, Cc);
+            if (fluid(p)) {
+                real Fx, Fy, Fz, ph[3];
+                force_phi(Aa, Ab, Ac, Ba, Bb, Bc, Ca, Cc, sr[z + 2][cr], sm[z + 1][c], pj[m][z], Fx, Fy, Fz, ph);
+                for (int k = 0; k < 3; ++k) sp[z][k][r] = ph[k];
+                if (own && p >= zs && p < ze) {
+                    const size_t n = pb[z + 2] + op[m];
+                    F[n] = Fx;
+                    F[N + n] = Fy;
+                    F[2 * N + n] = Fz;
+                }
+            } else {
+                for (int k = 0; k < 3; ++k) sp[z][k][r] = (real)0;
+            }
+            Aa = Ab, Ba = Bb, Ca = Cb;
+            Ab = Ac, Bb = Bc, Cb = Cc;
+        }
+    }
+    __syncthreads();
+
+    // Q of the owned columns
+    const int a = tid % TX, b = tid / TX;
+    if (tid < TX * TY && x0 + a < kp.nx && y0 + b < kp.ny) {
+        const int c = (b + 1) * WP + a + 1;
+        const size_t n0 = (size_t)(y0 + b) * kp.nx + (x0 + a);
+        real Xa, Ya, Za, Xb, Yb, Zb, Xc, Yc, Zc;
+        plane_div<WP>(sp[0][0], sp[0][1], sp[0][2], c, Xa, Ya, Za);
+        plane_div<WP>(sp[1][0], sp[1][1], sp[1][2], c, Xb, Yb, Zb);
+#pragma unroll
+        for (int z = 0; z < CZ; ++z) {
+            plane_div<WP>(sp[z + 2][0], sp[z + 2][1], sp[z + 2][2], c, Xc, Yc, Zc);
+            const int p = zs + z;
+            if (p < ze) {
+                const size_t n = pb[z + 3] + n0;
+                real qx, qy, qz;
+                q_of(Xa, Xb, Xc, Ya, Yb, Yc, Za, Zc, qx, qy, qz);
+                Q[n] = qx;
+                Q[N + n] = qy;
+                Q[2 * N + n] = qz;
+            }
+            Xa = Xb, Ya = Yb, Za = Zb;
+            Xb = Xc, Yb = Yc, Zb = Zc;
+        }
+    }
+}
+
 }  // namespace
 
 // Planes per workgroup.  One workgroup fits a CU (LDS), and every march
@@ -405,15 +661,55 @@ static int chain_chunk(const KP &kp, unsigned tiles) {
     return cz;
 }
 
+// Tile of k_chain_block.
+// The block kernel takes grids below 2^20 fluid nodes, where the march waits
+// for its barriers and its fill planes (us per step, march against block, two-
+// pass path: FP64 16^3 34.8 / 16.2, 32^3 38.7 / 18.8, 64^3 61 / 48, 101x67x53
+// 92 / 77, 96^3 152 / 140; FP32 32^3 30 / 16.4, 64^3 42 / 32, 96^3 95 / 86);
+// beyond, the blocks' recomputed region costs more (128^3 FP64 301 / 329, FP32
+// 165 / 184).  A chunk length that the caller forces and the block kernel does
+// not have (it has 1, 2 and 4) goes to the march.
+constexpr unsigned kBlockNodes = 1u << 20;
+constexpr int BX = 16, BY = 8;  // 32x8, 32x4 and 16x4 blocks: 0-12 % slower per step
+static bool chain_block_grid(const KP &kp) { return kp.nfluid < kBlockNodes; }
+
 int chain_chunk_for(const KP &kp) {
+    if (kp.chain_cz > 0) return kp.chain_cz;
+    if (chain_block_grid(kp)) {
+        // the fewest planes that leave one workgroup per CU, else 4 (32^3: 1,
+        // 2, 4 planes take 18.8, 19.6, 21.2 us per FP64 step; 64^3: 54, 51, 48)
+        const size_t tiles = (size_t)((kp.nx + BX - 1) / BX) * ((kp.ny + BY - 1) / BY);
+        const size_t nzf = kp.z1 - kp.z0;
+        return tiles * nzf <= kCUs ? 1 : (tiles * ((nzf + 1) / 2) <= kCUs ? 2 : 4);
+    }
     const unsigned ntx = (kp.nx + TX - 1) / TX, nty = (kp.ny + TY - 1) / TY;
-    return kp.chain_cz > 0 ? kp.chain_cz : chain_chunk(kp, ntx * nty);
+    return chain_chunk(kp, ntx * nty);
+}
+
+template <class real, bool WALLS, int CZ> static void go_block(hipStream_t s, const KP &kp, const Bufs &b) {
+    constexpr int NT = WALLS ? 320 : 256;  // one mu column per thread (308, 240)
+    const dim3 g((kp.nx + BX - 1) / BX * ((kp.ny + BY - 1) / BY), (kp.z1 - kp.z0 + CZ - 1) / CZ);
+    k_chain_block<real, WALLS, BX, BY, CZ, NT><<<g, NT, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q);
+}
+template <class real, bool WALLS> static void go_block(hipStream_t s, const KP &kp, const Bufs &b, int cz) {
+    switch (cz) {
+        case 1: go_block<real, WALLS, 1>(s, kp, b); break;
+        case 2: go_block<real, WALLS, 2>(s, kp, b); break;
+        default: go_block<real, WALLS, 4>(s, kp, b); break;
+    }
 }
 
 hipError_t launch_chain(hipStream_t s, int prec, const KP &kp, const Bufs &b) {
     const unsigned ntx = (kp.nx + TX - 1) / TX, nty = (kp.ny + TY - 1) / TY;
     const int cz = chain_chunk_for(kp);
     const int nzf = kp.z1 - kp.z0;
+    if (chain_block_grid(kp) && (cz == 1 || cz == 2 || cz == 4)) {
+        if (prec == LBFE_FP64)
+            kp.walls ? go_block<double, true>(s, kp, b, cz) : go_block<double, false>(s, kp, b, cz);
+        else
+            kp.walls ? go_block<float, true>(s, kp, b, cz) : go_block<float, false>(s, kp, b, cz);
+        return hipGetLastError();
+    }
     const dim3 grid(ntx * nty, (nzf + cz - 1) / cz);
     auto go = [&](auto pc) {
         constexpr int P = decltype(pc)::value;
