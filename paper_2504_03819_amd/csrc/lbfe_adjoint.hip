@@ -497,6 +497,73 @@ __global__ __launch_bounds__(kBlock) void k_adj_wall_move(KP kp, Bufs b, const v
     A[A_PMB * kp.N + n] += wpb;
 }
 
+// ---- the transposed stencils, factored ---------------------------------------
+// The isotropic D3Q27 stencils factor into D1Q3 pieces (weights 1/6, 2/3, 1/6
+// along each axis), so each one is an in-plane part read from one LDS plane
+// and a z part over a register ring that a thread keeps for its column:
+//   sum_i w_i g(x + c_i) = Wz (Wx Wy g),   3 sum_i w_i c_ix g(x + c_i) =
+//   1/2 Wz (Dx Wy g),  ... y: 1/2 Wz (Wx Dy g),  ... z: 1/2 Dz (Wx Wy g).
+constexpr double A1 = 1.0 / 6.0, A0 = 2.0 / 3.0;
+
+// Wx Wy g at index c of an LDS plane with row stride W
+template <int W> __device__ inline double smooth2(const double *g, int c) {
+    const double r0 = A1 * g[c - W - 1] + A0 * g[c - W] + A1 * g[c - W + 1];
+    const double r1 = A1 * g[c - 1] + A0 * g[c] + A1 * g[c + 1];
+    const double r2 = A1 * g[c + W - 1] + A0 * g[c + W] + A1 * g[c + W + 1];
+    return A1 * r0 + A0 * r1 + A1 * r2;
+}
+// Dx Wy g and Wx Dy g
+template <int W> __device__ inline double dx_wy(const double *g, int c) {
+    return A1 * (g[c - W + 1] - g[c - W - 1]) + A0 * (g[c + 1] - g[c - 1]) + A1 * (g[c + W + 1] - g[c + W - 1]);
+}
+template <int W> __device__ inline double wx_dy(const double *g, int c) {
+    return A1 * (g[c + W - 1] - g[c - W - 1]) + A0 * (g[c + W] - g[c - W]) + A1 * (g[c + W + 1] - g[c - W + 1]);
+}
+__device__ inline double wz(double a, double b, double c) { return A1 * a + A0 * b + A1 * c; }
+// the three in-plane parts of one plane, and the ring of the last two
+struct Part3 {
+    double x, y, z;
+};
+struct Ring3 {
+    Part3 a{0, 0, 0}, b{0, 0, 0};  // two planes back, one plane back
+    __device__ void push(const Part3 &n) {
+        a = b;
+        b = n;
+    }
+};
+
+// Tile and chunk of this workgroup: each XCD takes a contiguous range of
+// (chunk, tile) pairs, the tiles of one chunk consecutively, so that
+// neighbouring tiles find each other's halo lines in that XCD's L2.
+__device__ inline void xcd_tile(int &tile, int &chunk) {
+    const unsigned nt = gridDim.x, nb = gridDim.x * gridDim.y, hw = blockIdx.y * gridDim.x + blockIdx.x;
+    const unsigned q = nb >> 3, rem = nb & 7u, x = hw & 7u;
+    const unsigned lid = x * q + (x < rem ? x : rem) + (hw >> 3);
+    tile = (int)(lid % nt);
+    chunk = (int)(lid / nt);
+}
+
+// Branch-free access to one plane of a field (masked lanes carry kNone: they
+// read 0 and store nothing), as in the forward chain.
+constexpr unsigned kNone = 0x80000000u;
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+__device__ inline __amdgpu_buffer_rsrc_t plane_of(const void *p, size_t first, unsigned plane, unsigned esize) {
+    return __builtin_amdgcn_make_buffer_rsrc((char *)const_cast<void *>(p) + first * esize, 0, (int)(plane * esize),
+                                             0x00020000);
+}
+__device__ inline void pld(double &v, __amdgpu_buffer_rsrc_t r, unsigned o) {
+    v = __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, o == kNone ? kNone : o * 8u, 0, 0));
+}
+__device__ inline void pld(float &v, __amdgpu_buffer_rsrc_t r, unsigned o) {
+    v = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, o == kNone ? kNone : o * 4u, 0, 0));
+}
+__device__ inline void pst(double v, __amdgpu_buffer_rsrc_t r, unsigned o) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, o == kNone ? kNone : o * 8u, 0, 0);
+}
+__device__ inline void pst(float v, __amdgpu_buffer_rsrc_t r, unsigned o) {
+    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, o == kNone ? kNone : o * 4u, 0, 0);
+}
+
 // The transposed Q and gradient stencils in one z-march:
 //   phi part, at fluid nodes: phi_bar_a = transpose of Q_a = -9 sum_i w_i
 //     c_ia phi_a(x + c_i) = 9 sum_i w_i c_ia Q_bar_a(x + c_i), then back
@@ -504,196 +571,173 @@ __global__ __launch_bounds__(kBlock) void k_adj_wall_move(KP kp, Bufs b, const v
 //     j_bar, rho_bar (local part), G_bar and the local part of mu_bar;
 //   mu part, at every node: mu_bar(y) = local part (fluid) - 3 sum_i w_i
 //     c_i . G_bar(y + c_i) (G_bar is zero at solid nodes), into A_MUBT.
-// A workgroup owns a 32 x 16 tile of mu_bar planes [zs, ze).  Iteration k
-// evaluates the phi part at plane k+1 on the tile and its one-node ring (Q_bar
-// and mu staged with a two-node halo in a three-plane LDS ring), which leaves
-// G_bar of those 34 x 18 nodes in a three-plane LDS ring, then sums mu_bar of
-// plane k on the tile.  G_bar never goes to HBM; the owned node's j_bar and
-// rho_bar do, the ring nodes only give G_bar.
-constexpr int PWX = ZTX + 4, PNR = PWX * (ZTY + 4);  // Q_bar and mu region: tile + 2-node halo
-constexpr int GWX = ZTX + 2, GNR = GWX * (ZTY + 2);  // G_bar region: tile + 1-node ring
-constexpr int PCB = ZCB + 128;                       // threads: the tile's nodes, then the ring's
-constexpr int PPT = (PNR + PCB - 1) / PCB;           // Q_bar / mu region points per thread
-static_assert(GNR <= PCB, "one G_bar node per thread");
-
-__device__ inline int zslot3(int p) { return ((p % 3) + 3) % 3; }
-
-template <int P, bool MASK> __global__ __launch_bounds__(PCB) void k_adj_phimu(KP kp, Bufs b, int cz) {
+// A workgroup owns a PTX x PTY tile of mu_bar planes [zs, ze); the phi part
+// runs on the tile and its one-node ring, one node per thread.  Iteration t
+// stages Q_bar and mu of plane t (two-node halo), takes the in-plane parts of
+// plane t-1 and the phi part of plane t-2, whose G_bar goes to LDS, then the
+// in-plane parts of G_bar(t-3) and mu_bar(t-4).  Each stage reads what the
+// iteration before wrote (two slots per LDS plane), so one barrier per plane
+// suffices.  G_bar never goes to HBM; the owned node's j_bar and rho_bar do,
+// the ring nodes only give G_bar.  Bound by its loads (128 B per node without
+// the halos) and their latency: at 192x192x96 in FP32 133 us, 3.4 TB/s on
+// those bytes, where reading every 27-point sum from LDS took 192 us; at
+// 48x40x32 in FP64 18 against 62 us.
+template <int P, bool MASK, int PTX, int PTY, int PNT>
+__global__ __launch_bounds__(PNT, 4) void k_adj_phimu(KP kp, Bufs b, int cz) {
     using real = real_t<P>;
-    __shared__ double sq[3][4][PNR];  // Q_bar x, y, z and mu of planes p (slot p mod 3)
-    __shared__ double sg[3][3][GNR];  // G_bar of planes p (slot p mod 3)
-    int x0, y0, zs, ze;
-    ztile(kp, cz, 0, kp.nz, x0, y0, zs, ze);
+    constexpr int PWX = PTX + 4, PNR = PWX * (PTY + 4);  // Q_bar and mu region: tile + 2-node halo
+    constexpr int GWX = PTX + 2, GNR = GWX * (PTY + 2);  // G_bar region: tile + 1-node ring
+    constexpr int PPT = (PNR + PNT - 1) / PNT;           // Q_bar / mu region points per thread
+    static_assert(GNR <= PNT && PTX * PTY <= PNT, "one G_bar node, one owned column per thread");
+    __shared__ double sq[2][4][PNR];  // Q_bar x, y, z and mu of plane p (slot p & 1)
+    __shared__ double sg[2][3][GNR];  // G_bar of plane p (slot p & 1)
+    __shared__ double sl[3][GNR];     // local part of mu_bar of plane p (slot p mod 3)
+    const int ntx = (kp.nx + PTX - 1) / PTX;
+    int tile, chunk;
+    xcd_tile(tile, chunk);
+    const int x0 = tile % ntx * PTX, y0 = tile / ntx * PTY;
+    const int zs = chunk * cz, ze = min(zs + cz, kp.nz);
     const size_t N = kp.N;
     const unsigned plane = kp.plane;
     double *A = (double *)b.abuf;
     const real *j = (const real *)b.j, *F = (const real *)b.F;
-    const real *qb[3] = {aplane<real>(A, A_QB, 0, N), aplane<real>(A, A_QB, 1, N), aplane<real>(A, A_QB, 2, N)};
     const int tid = threadIdx.x;
-    const int ta = tid % ZTX, tb = tid / ZTX;  // the tile node of threads below ZCB
-    const bool own = tid < ZCB && x0 + ta < kp.nx && y0 + tb < kp.ny;
+    constexpr unsigned S = sizeof(real);
 
     // Q_bar / mu region points of this thread, in-plane node index
     unsigned qoff[PPT];
-    bool qhas[PPT];
 #pragma unroll
     for (int m = 0; m < PPT; ++m) {
-        const int r = tid + m * PCB;
-        qhas[m] = r < PNR;
-        const int rr = qhas[m] ? r : 0;
-        qoff[m] = (unsigned)zwrap(y0 + rr / PWX - 2, kp.ny) * kp.nx + zwrap(x0 + rr % PWX - 2, kp.nx);
+        const int r = tid + m * PNT;
+        qoff[m] = r < PNR ? (unsigned)zwrap(y0 + r / PWX - 2, kp.ny) * kp.nx + zwrap(x0 + r % PWX - 2, kp.nx) : kNone;
     }
-    double qpre[4][PPT];
-    auto load = [&](int p) {
-        const size_t base = (size_t)zwrap(p, kp.nz) * plane;
+    // phi node (ga, gb) of the G_bar region, owned when inside the tile and grid
+    const int ga = tid % GWX, gb = tid / GWX;
+    const bool hasg = tid < GNR;
+    const unsigned noff =
+        hasg ? (unsigned)zwrap(y0 + gb - 1, kp.ny) * kp.nx + zwrap(x0 + ga - 1, kp.nx) : kNone;
+    const bool owng = hasg && ga >= 1 && ga <= PTX && gb >= 1 && gb <= PTY && x0 + ga - 1 < kp.nx && y0 + gb - 1 < kp.ny;
+    const int cq = hasg ? (gb + 1) * PWX + ga + 1 : PWX + 1;  // the node in the Q_bar / mu region
+    // owned column (ta, tb) of the mu part
+    const int ta = tid % PTX, tb = tid / PTX;
+    const bool own = tid < PTX * PTY && x0 + ta < kp.nx && y0 + tb < kp.ny;
+    const unsigned ooff = own ? (unsigned)(y0 + tb) * kp.nx + (x0 + ta) : kNone;
+    const int cg = tid < PTX * PTY ? (tb + 1) * GWX + ta + 1 : GWX + 1;
+
+    auto next = [&](int g) { return g + 1 == kp.nz ? 0 : g + 1; };
+    // loads run one iteration ahead of their use
+    real qpre[3][PPT];
+    double mpre[PPT];
+    auto load_q = [&](int g, bool ok) {  // ok false: a plane the chunk does not need
+        const size_t f = (size_t)g * plane;
 #pragma unroll
-        for (int m = 0; m < PPT; ++m)
-            if (qhas[m]) {
+        for (int m = 0; m < PPT; ++m) {
+            const unsigned o = ok ? qoff[m] : kNone;
 #pragma unroll
-                for (int c = 0; c < 3; ++c) qpre[c][m] = (double)qb[c][base + qoff[m]];
-                qpre[3][m] = b.mu[base + qoff[m]];
-            }
+            for (int c = 0; c < 3; ++c) pld(qpre[c][m], plane_of(aplane<real>(A, A_QB, c, N), f, plane, S), o);
+            pld(mpre[m], plane_of(b.mu, f, plane, 8), o);
+        }
     };
-    auto commit = [&](int p) {
-        const int sl = zslot3(p);
+    double rpre, ppre, bpre;
+    real jpre[3], fpre[3], upre[3], gpre[3];
+    unsigned wpre = 0;
+    auto load_node = [&](int g, bool ok) {
+        const size_t f = (size_t)g * plane;
+        const unsigned o = ok ? noff : kNone, oo = ok && owng ? noff : kNone;
+        pld(rpre, plane_of(b.rho, f, plane, 8), o);
+        pld(ppre, plane_of(A + A_PMB * N, f, plane, 8), oo);
+        pld(bpre, plane_of(A + A_RHOB * N, f, plane, 8), oo);
 #pragma unroll
-        for (int m = 0; m < PPT; ++m)
-            if (qhas[m]) {
-#pragma unroll
-                for (int f = 0; f < 4; ++f) sq[sl][f][tid + m * PCB] = qpre[f][m];
-            }
+        for (int c = 0; c < 3; ++c) {
+            pld(jpre[c], plane_of(j + c * N, f, plane, S), o);
+            pld(fpre[c], plane_of(F + c * N, f, plane, S), o);
+            pld(upre[c], plane_of(aplane<real>(A, A_UB, c, N), f, plane, S), o);
+            pld(gpre[c], plane_of(aplane<real>(A, A_FB, c, N), f, plane, S), o);
+        }
+        if constexpr (MASK) wpre = hasg ? b.nbr[f + noff] : kSelfBit;
     };
 
-    // the phi part at plane p for G-region node (ga, gb): G_bar into LDS;
-    // for an owned node of a plane of this chunk also j_bar and rho_bar to
-    // HBM (the fill planes at both ends belong to the neighbouring chunks),
-    // and the local part of mu_bar returned
-    auto phi_node = [&](int p, int ga, int gb, bool owned) -> double {
-        const int zz = zwrap(p, kp.nz);
-        const int sm = zslot3(p - 1), s0 = zslot3(p), sp = zslot3(p + 1);
-        const int g = gb * GWX + ga;
-        const int cq = (gb + 1) * PWX + ga + 1;  // the node in the Q_bar / mu region
-        auto at = [&](int f, int dz, int dx, int dy) {
-            return sq[dz < 0 ? sm : (dz > 0 ? sp : s0)][f][cq + dy * PWX + dx];
-        };
-        const size_t n = (size_t)zz * plane + (unsigned)zwrap(y0 + gb - 1, kp.ny) * kp.nx +
-                         (unsigned)zwrap(x0 + ga - 1, kp.nx);
-        bool fl = zz >= kp.z0 && zz < kp.z1;
-        if constexpr (MASK) fl = fl && !(b.nbr[n] & kSelfBit);
-        if (!fl) {  // solid: no G_bar, no local mu_bar, nothing stored
-            sg[s0][0][g] = sg[s0][1][g] = sg[s0][2][g] = 0.0;
-            return 0.0;
-        }
-        double px = 0, py = 0, pz = 0;
+    Ring3 rq, rm, rg;  // in-plane parts of Q_bar, grad mu, G_bar
+    double mc = 0.0;   // mu of the phi node's newest plane
+    int t = zs - 2;
+    int g4 = zwrap(t - 4, kp.nz), g3 = zwrap(t - 3, kp.nz), g2 = zwrap(t - 2, kp.nz), g1 = zwrap(t - 1, kp.nz),
+        gn = zwrap(t, kp.nz);
+    int s2 = (t - 2 + 6) % 3;  // (t - 2) mod 3; t >= -2
+    load_q(gn, true);
+    load_node(g2, false);
+    for (; t <= ze + 3; ++t) {
 #pragma unroll
-        for (int a = -1; a <= 1; ++a)
+        for (int m = 0; m < PPT; ++m)
+            if (tid + m * PNT < PNR) {
 #pragma unroll
-            for (int c = -1; c <= 1; ++c) {
-                const double w = w1(a) * w1(c) / 6.0;
-                px += w * (at(0, c, 1, a) - at(0, c, -1, a));
-                py += w * (at(1, c, a, 1) - at(1, c, a, -1));
-                pz += w * (at(2, 1, a, c) - at(2, -1, a, c));
+                for (int c = 0; c < 3; ++c) sq[t & 1][c][tid + m * PNT] = (double)qpre[c][m];
+                sq[t & 1][3][tid + m * PNT] = mpre[m];
             }
-        px *= 9.0;
-        py *= 9.0;
-        pz *= 9.0;
-        const double r = b.rho[n], mu = at(3, 0, 0, 0);
-        const real ir = (real)1 / (real)r;
-        const double ux = (double)((j[n] + (real)0.5 * F[n]) * ir);
-        const double uy = (double)((j[N + n] + (real)0.5 * F[N + n]) * ir);
-        const double uz = (double)((j[2 * N + n] + (real)0.5 * F[2 * N + n]) * ir);
-        const double c2 = (double)(real)((1.0 + mu - r) * (1.0 / 3.0));
-        const double pu = px * ux + py * uy + pz * uz;
-        const double utx = (double)aplane<real>(A, A_UB, 0, N)[n] + c2 * px;
-        const double uty = (double)aplane<real>(A, A_UB, 1, N)[n] + c2 * py;
-        const double utz = (double)aplane<real>(A, A_UB, 2, N)[n] + c2 * pz;
-        // u = (j + F/2)/rho: j_bar = u_tilde/rho, F_bar += j_bar/2 (halving
-        // the quotient rounds as dividing the halved numerator does)
-        const double jbx = utx / r, jby = uty / r, jbz = utz / r;
-        const double Fbx = (double)aplane<real>(A, A_FB, 0, N)[n] + 0.5 * jbx;
-        const double Fby = (double)aplane<real>(A, A_FB, 1, N)[n] + 0.5 * jby;
-        const double Fbz = (double)aplane<real>(A, A_FB, 2, N)[n] + 0.5 * jbz;
-        const double c1 = 1.0 / 3.0 - r;
-        sg[s0][0][g] = c1 * Fbx;
-        sg[s0][1][g] = c1 * Fby;
-        sg[s0][2][g] = c1 * Fbz;
-        if (!owned) return 0.0;
-        double pmb = A[A_PMB * N + n], rhob = A[A_RHOB * N + n];
-        pmb += pu;
-        rhob -= pu / 3.0;
-        aplane<real>(A, A_JB, 0, N)[n] = (real)jbx;
-        aplane<real>(A, A_JB, 1, N)[n] = (real)jby;
-        aplane<real>(A, A_JB, 2, N)[n] = (real)jbz;
-        rhob -= (utx * ux + uty * uy + utz * uz) / r;
-        double gx = 0.0, gy = 0.0, gz = 0.0;
-#pragma unroll
-        for (int i = 0; i < 27; ++i) {
-            if (i == kRest) continue;
-            const double m = wi(i) * at(3, czi(i), cxi(i), cyi(i));
-            if (cxi(i)) gx += cxi(i) * m;
-            if (cyi(i)) gy += cyi(i) * m;
-            if (czi(i)) gz += czi(i) * m;
-        }
-        gx *= 3.0;
-        gy *= 3.0;
-        gz *= 3.0;
-        rhob -= Fbx * gx + Fby * gy + Fbz * gz;
-        A[A_RHOB * N + n] = rhob;
-        return pmb / 3.0;  // p_m = (1 + mu)/3
-    };
-    // ring-only G-region node q of thread ZCB + q
-    auto ring_node = [&](int q, int &ga, int &gb) {
-        if (q < GWX) {
-            ga = q, gb = 0;
-        } else if (q < 2 * GWX) {
-            ga = q - GWX, gb = ZTY + 1;
-        } else if (q < 2 * GWX + ZTY) {
-            ga = 0, gb = q - 2 * GWX + 1;
-        } else {
-            ga = GWX - 1, gb = q - 2 * GWX - ZTY + 1;
-        }
-    };
+        gn = next(gn);
+        load_q(gn, t + 1 <= ze + 1);
 
-    double mloc_k = 0.0;  // local mu_bar of the owned node, plane k
-    load(zs - 2);
-    commit(zs - 2);
-    load(zs - 1);
-    commit(zs - 1);
-    load(zs);
-    for (int k = zs - 2; k < ze; ++k) {
-        commit(k + 2);
-        __syncthreads();
-        if (k + 3 <= ze + 1) load(k + 3);
-        // phi part at plane k+1: the tile's nodes and the ring's, one per thread
-        double mloc_next = 0.0;
-        if (tid < ZCB) {
-            mloc_next = phi_node(k + 1, ta + 1, tb + 1, own && k + 1 >= zs && k + 1 < ze);
-        } else if (tid < GNR) {
-            int ga, gb;
-            ring_node(tid - ZCB, ga, gb);
-            phi_node(k + 1, ga, gb, false);
-        }
-        __syncthreads();
-        if (k >= zs && own) {
-            const int sm = zslot3(k - 1), s0 = zslot3(k), sp = zslot3(k + 1);
-            const int g = (tb + 1) * GWX + ta + 1;
-            double sum = 0.0;
+        if (t - 1 >= zs - 2 && t - 2 <= ze) {
+            const int p = t - 2;
+            const double(*q)[PNR] = sq[(t - 1) & 1];
+            const Part3 qn{dx_wy<PWX>(q[0], cq), wx_dy<PWX>(q[1], cq), smooth2<PWX>(q[2], cq)};
+            const Part3 mn{dx_wy<PWX>(q[3], cq), wx_dy<PWX>(q[3], cq), smooth2<PWX>(q[3], cq)};
+            double jb[3] = {0, 0, 0}, Gb[3] = {0, 0, 0}, rhob = 0.0, mloc = 0.0;
+            const bool fplane = p >= zs - 1 && g2 >= kp.z0 && g2 < kp.z1;
+            const bool fl = fplane && !(MASK && (wpre & kSelfBit));
+            if (fl) {
+                const double pb[3] = {1.5 * wz(rq.a.x, rq.b.x, qn.x), 1.5 * wz(rq.a.y, rq.b.y, qn.y), 1.5 * (qn.z - rq.a.z)};
+                const double g[3] = {0.5 * wz(rm.a.x, rm.b.x, mn.x), 0.5 * wz(rm.a.y, rm.b.y, mn.y), 0.5 * (mn.z - rm.a.z)};
+                const double r = rpre, rinv = 1.0 / r;
+                const real ir = (real)1 / (real)r;
+                const double c1 = 1.0 / 3.0 - r, c2 = (double)(real)((1.0 + mc - r) * (1.0 / 3.0));
+                double pu = 0.0, uu = 0.0, fg = 0.0;
 #pragma unroll
-            for (int i = 0; i < 27; ++i) {
-                if (i == kRest) continue;
-                const int sl = czi(i) < 0 ? sm : (czi(i) > 0 ? sp : s0);
-                const int gi = g + cyi(i) * GWX + cxi(i);
-                double d = 0.0;
-                if (cxi(i)) d += cxi(i) * sg[sl][0][gi];
-                if (cyi(i)) d += cyi(i) * sg[sl][1][gi];
-                if (czi(i)) d += czi(i) * sg[sl][2][gi];
-                sum += wi(i) * d;
+                for (int c = 0; c < 3; ++c) {
+                    const double u = (double)((jpre[c] + (real)0.5 * fpre[c]) * ir);
+                    const double ut = (double)upre[c] + c2 * pb[c];
+                    // u = (j + F/2)/rho: j_bar = u_tilde/rho, F_bar += j_bar/2
+                    jb[c] = ut * rinv;
+                    const double Fb = (double)gpre[c] + 0.5 * jb[c];
+                    Gb[c] = c1 * Fb;
+                    pu += pb[c] * u;
+                    uu += ut * u;
+                    fg += Fb * g[c];
+                }
+                rhob = bpre - pu * (1.0 / 3.0) - uu * rinv - fg;
+                mloc = (ppre + pu) * (1.0 / 3.0);  // p_m = (1 + mu)/3
             }
-            const size_t n = (size_t)k * plane + (unsigned)(y0 + tb) * kp.nx + (x0 + ta);
-            const bool fluid = k >= kp.z0 && k < kp.z1;
-            A[A_MUBT * N + n] = (fluid ? mloc_k : 0.0) - 3.0 * sum;
+            if (hasg && p >= zs - 1) {  // (solid: no G_bar, no local mu_bar)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) sg[p & 1][c][tid] = Gb[c];
+                sl[s2][tid] = mloc;
+            }
+            // the fill planes at both ends belong to the neighbouring chunks
+            const unsigned o = fl && owng && p >= zs && p < ze ? noff : kNone;
+            const size_t f = (size_t)g2 * plane;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) pst((real)jb[c], plane_of(aplane<real>(A, A_JB, c, N), f, plane, S), o);
+            pst(rhob, plane_of(A + A_RHOB * N, f, plane, 8), o);
+            rq.push(qn);
+            rm.push(mn);
+            mc = q[3][cq];
         }
-        mloc_k = mloc_next;
+        load_node(g1, t - 1 >= zs - 1 && t - 1 <= ze);
+
+        if (t - 3 >= zs - 1) {
+            const int p3 = t - 3, p = t - 4;
+            const double(*g)[GNR] = sg[p3 & 1];
+            const Part3 n{dx_wy<GWX>(g[0], cg), wx_dy<GWX>(g[1], cg), smooth2<GWX>(g[2], cg)};
+            const double d = 0.5 * wz(rg.a.x, rg.b.x, n.x) + 0.5 * wz(rg.a.y, rg.b.y, n.y) + 0.5 * (n.z - rg.a.z);
+            const double v = sl[s2 == 2 ? 0 : s2 + 1][cg] - d;  // slot (t - 4) mod 3
+            pst(v, plane_of(A + A_MUBT * N, (size_t)g4 * plane, plane, 8), p >= zs ? ooff : kNone);
+            rg.push(n);
+        }
+        __syncthreads();
+        g4 = g3;
+        g3 = g2;
+        g2 = g1;
+        g1 = next(g1);
+        s2 = s2 == 2 ? 0 : s2 + 1;
     }
 }
 
@@ -731,52 +775,104 @@ __global__ __launch_bounds__(kBlock) void k_adj_wall_gather(KP kp, const double 
     dst[(size_t)zf * kp.plane + p] += acc;
 }
 
-// rho_bar_total(y) = [fluid: rho_bar + mu_bar mu0'(rho)] - kappa L[mu_bar_fluid](y);
+// rho_bar_total(y) = [fluid: rho_bar + mu_bar mu0'(rho)] - kappa L[mu_bar_fluid](y), in a
+// z-march like k_adj_phimu's (plane t staged, in-plane parts of t-1, node t-2);
 // per-node dL/dkappa = -mu_bar L[rho].  `mub` is the total mu_bar (solid
 // entries are ignored: the Laplacian's adjoint sees fluid mu_bar only).
+constexpr int RTX = 32, RTY = 16, RNT = RTX * RTY;
+constexpr int RWX = RTX + 2, RNR = RWX * (RTY + 2), RPT = (RNR + RNT - 1) / RNT;
 template <bool MASK>
-__global__ __launch_bounds__(ZCB) void k_adj_rho(KP kp, const double *mub, const double *rhob_local,
+__global__ __launch_bounds__(RNT) void k_adj_rho(KP kp, const double *mub, const double *rhob_local,
                                                  const double *rho, double *rhobt, double *kapc, int cz,
                                                  const unsigned *nbr) {
-    __shared__ double lds[4][2][ZNR];
-    int x0, y0, zs, ze;
-    ztile(kp, cz, 0, kp.nz, x0, y0, zs, ze);
-    ZRing<2> R;
-    R.init(kp, lds, x0, y0);
-    R.src[0] = mub;
-    R.src[1] = rho;
-    R.zmask = 1u;  // mu_bar of solid planes reads as zero
-    R.march(zs, ze, [&](int k) {
-        if (!R.own) return;
-        const double m0 = R.at(0, k, 0, 0);
-        const double r0 = R.at(1, k, 0, 0);
-        double lm = 0.0, lr = 0.0;
+    __shared__ double sd[2][2][RNR];  // mu_bar (0 on solid planes) and rho of plane p (slot p & 1)
+    const int ntx = (kp.nx + RTX - 1) / RTX;
+    int tile, chunk;
+    xcd_tile(tile, chunk);
+    const int x0 = tile % ntx * RTX, y0 = tile / ntx * RTY;
+    const int zs = chunk * cz, ze = min(zs + cz, kp.nz);
+    const unsigned plane = kp.plane;
+    const int tid = threadIdx.x, ta = tid % RTX, tb = tid / RTX;
+    const bool own = x0 + ta < kp.nx && y0 + tb < kp.ny;
+    const unsigned ooff = own ? (unsigned)(y0 + tb) * kp.nx + (x0 + ta) : kNone;
+    const int c = (tb + 1) * RWX + ta + 1;
+    unsigned off[RPT];
 #pragma unroll
-        for (int i = 0; i < 27; ++i) {
-            if (i == kRest) continue;
-            const int p = k + czi(i);
-            lm += wi(i) * (R.at(0, p, cxi(i), cyi(i)) - m0);
-            lr += wi(i) * (R.at(1, p, cxi(i), cyi(i)) - r0);
+    for (int m = 0; m < RPT; ++m) {
+        const int r = tid + m * RNT;
+        off[m] = r < RNR ? (unsigned)zwrap(y0 + r / RWX - 1, kp.ny) * kp.nx + zwrap(x0 + r % RWX - 1, kp.nx) : kNone;
+    }
+    auto next = [&](int g) { return g + 1 == kp.nz ? 0 : g + 1; };
+    auto fluid_plane = [&](int g) { return g >= kp.z0 && g < kp.z1; };
+    // loads run one iteration ahead of their use
+    double pre[2][RPT], lpre;
+    unsigned wpre = 0;
+    auto load = [&](int g, bool ok) {  // ok false: a plane the chunk does not need
+        const size_t f = (size_t)g * plane;
+        const bool fl = ok && fluid_plane(g);
+#pragma unroll
+        for (int m = 0; m < RPT; ++m) {
+            pld(pre[0][m], plane_of(mub, f, plane, 8), fl ? off[m] : kNone);
+            pld(pre[1][m], plane_of(rho, f, plane, 8), ok ? off[m] : kNone);
         }
-        lm *= 6.0;
-        lr *= 6.0;
-        const size_t n = (size_t)k * kp.plane + R.node;
-        bool fluid;
-        if constexpr (MASK)
-            fluid = !(nbr[n] & kSelfBit);
-        else
-            fluid = k >= kp.z0 && k < kp.z1;
-        double out = -kp.kappa * lm;
-        if (fluid) {
-            const double d = 1.0 - kp.b * r0;
-            const double dmu0 = kp.RT / (r0 * d * d) - 2.0 * kp.a;
-            out += rhob_local[n] + m0 * dmu0;
-            kapc[n] = -m0 * lr;
+    };
+    auto load_node = [&](int g, bool ok) {
+        const size_t f = (size_t)g * plane;
+        pld(lpre, plane_of(rhob_local, f, plane, 8), ok ? ooff : kNone);
+        if constexpr (MASK) wpre = own ? nbr[f + ooff] : kSelfBit;
+    };
+    double ma = 0, mb = 0, ra = 0, rb = 0, m0 = 0, r0 = 0;  // Wx Wy of two planes back, one back; values one back
+    int t = zs - 1;
+    int g2 = zwrap(t - 2, kp.nz), g1 = zwrap(t - 1, kp.nz), gn = zwrap(t, kp.nz);
+    load(gn, true);
+    load_node(g2, false);
+    for (; t <= ze + 1; ++t) {
+#pragma unroll
+        for (int m = 0; m < RPT; ++m)
+            if (tid + m * RNT < RNR) {
+                sd[t & 1][0][tid + m * RNT] = pre[0][m];
+                sd[t & 1][1][tid + m * RNT] = pre[1][m];
+            }
+        gn = next(gn);
+        load(gn, t + 1 <= ze);
+        if (t - 1 >= zs - 1) {
+            const double(*d)[RNR] = sd[(t - 1) & 1];
+            const double mn = smooth2<RWX>(d[0], c), rn = smooth2<RWX>(d[1], c);
+            const double lm = 6.0 * (wz(ma, mb, mn) - m0), lr = 6.0 * (wz(ra, rb, rn) - r0);
+            const bool fluid = fluid_plane(g2) && !(MASK && (wpre & kSelfBit));
+            double out = -kp.kappa * lm, kc = 0.0;
+            if (fluid) {
+                const double q = 1.0 - kp.b * r0;
+                const double dmu0 = kp.RT / (r0 * q * q) - 2.0 * kp.a;
+                out += lpre + m0 * dmu0;
+                kc = -m0 * lr;
+            }
+            load_node(g1, t - 1 >= zs && t - 1 < ze);
+            const unsigned o = t - 2 >= zs ? ooff : kNone;
+            const size_t f = (size_t)g2 * plane;
+            pst(kc, plane_of(kapc, f, plane, 8), o);
+            pst(out, plane_of(rhobt, f, plane, 8), o);
+            ma = mb, mb = mn, ra = rb, rb = rn;
+            m0 = d[0][c];
+            r0 = d[1][c];
         } else {
-            kapc[n] = 0.0;
+            load_node(g1, t - 1 >= zs && t - 1 < ze);
         }
-        rhobt[n] = out;
-    });
+        __syncthreads();
+        g2 = g1;
+        g1 = next(g1);
+    }
+}
+
+// Planes per workgroup of the transposed stencils: `slots` workgroups run at
+// once, each paying `fill` planes; the chunk from 64 down to 1 that minimises
+// the busiest slot's plane iterations (the longer on ties).
+static int adj_chunk(size_t tiles, int nz, size_t slots, int fill) {
+    auto iters = [&](int c) { return (tiles * ((nz + c - 1) / c) + slots - 1) / slots * (size_t)(c + fill); };
+    int cz = 64;
+    for (int c = 63; c >= 1; --c)
+        if (iters(c) < iters(cz)) cz = c;
+    return cz;
 }
 
 // Solid nodes: rho_ave_bar = W'(rho_ave) rho_bar(x_s), and the per-node
@@ -1046,6 +1142,24 @@ __global__ __launch_bounds__(kBlock) void k_adj_init_out(KP kp, Bufs b, const do
     out[n] = fluid_node(kp, b, n) ? rhobt[n] : 0.0;
 }
 
+// From 2^20 nodes the wide tile, one workgroup per CU: fewer ring nodes and
+// halo lines (192x192x96 in FP32: 133 against 147 us); below, the narrow one,
+// whose two workgroups per CU cover a small grid in more pieces (48x40x32 in
+// FP64: 18 against 28 us).
+template <int P, bool MASK> void phimu(hipStream_t s, const KP &kp, const Bufs &b) {
+    auto go = [&](auto tx, auto ty, auto nt) {
+        constexpr int TX = decltype(tx)::value, TY = decltype(ty)::value, NT = decltype(nt)::value;
+        const unsigned tiles = (kp.nx + TX - 1) / TX * ((kp.ny + TY - 1) / TY);
+        const int cz = adj_chunk(tiles, kp.nz, 256 * (1024 / NT), 6);
+        k_adj_phimu<P, MASK, TX, TY, NT><<<dim3(tiles, (kp.nz + cz - 1) / cz), NT, 0, s>>>(kp, b, cz);
+    };
+    using std::integral_constant;
+    if (kp.N >= (1u << 20))
+        go(integral_constant<int, 64>{}, integral_constant<int, 13>{}, integral_constant<int, 1024>{});
+    else
+        go(integral_constant<int, 32>{}, integral_constant<int, 12>{}, integral_constant<int, 512>{});
+}
+
 template <class Fn> hipError_t dispatch(int prec, Fn &&fn) {
     switch (prec) {
         case LBFE_FP64: return fn(std::integral_constant<int, LBFE_FP64>{});
@@ -1066,7 +1180,9 @@ hipError_t chain_tail(hipStream_t s, const KP &kp, const Bufs &b, bool with_grad
     double *A = (double *)b.abuf;
     const unsigned gN = nblocks(N), gw = nblocks(2 * (size_t)kp.plane);
     double *mub_tot = A + (with_gradient_transpose ? A_MUBT : A_MUB) * N;
-    const dim3 gall = zgrid(kp, 0, kp.nz);
+    const unsigned tiles = (kp.nx + RTX - 1) / RTX * ((kp.ny + RTY - 1) / RTY);
+    const int cz = adj_chunk(tiles, kp.nz, 256 * 3, 3);
+    const dim3 gall(tiles, (kp.nz + cz - 1) / cz);
     const double *wetc = nullptr;
     unsigned nwet = 0;
     if (kp.masked) {
@@ -1074,8 +1190,8 @@ hipError_t chain_tail(hipStream_t s, const KP &kp, const Bufs &b, bool with_grad
         // then the Laplacian's adjoint with mu_bar zero at solid nodes
         k_adj_wall_gather_m<<<gN, kBlock, 0, s>>>(kp, b.nbr, mub_tot, mub_tot);
         k_adj_fluid_copy_m<<<gN, kBlock, 0, s>>>(kp, b.nbr, mub_tot, A + A_MUB * N);
-        k_adj_rho<true><<<gall, ZCB, 0, s>>>(kp, A + A_MUB * N, A + A_RHOB * N, b.rho, A + A_RHOBT * N,
-                                             A + A_KAPC * N, kZChunk, b.nbr);
+        k_adj_rho<true><<<gall, RNT, 0, s>>>(kp, A + A_MUB * N, A + A_RHOB * N, b.rho, A + A_RHOBT * N,
+                                             A + A_KAPC * N, cz, b.nbr);
         k_adj_wall_rho_solid_m<<<gN, kBlock, 0, s>>>(kp, b.nbr, b.rho, A + A_RHOBT * N, A + A_RAVEB * N,
                                                      A + A_WETC * N);
         k_adj_wall_gather_m<<<gN, kBlock, 0, s>>>(kp, b.nbr, A + A_RAVEB * N, A + A_RHOBT * N);
@@ -1083,8 +1199,8 @@ hipError_t chain_tail(hipStream_t s, const KP &kp, const Bufs &b, bool with_grad
         nwet = (unsigned)N;
     } else {
         if (kp.walls) k_adj_wall_gather<<<gw, kBlock, 0, s>>>(kp, mub_tot, mub_tot);
-        k_adj_rho<false><<<gall, ZCB, 0, s>>>(kp, mub_tot, A + A_RHOB * N, b.rho, A + A_RHOBT * N, A + A_KAPC * N,
-                                              kZChunk, nullptr);
+        k_adj_rho<false><<<gall, RNT, 0, s>>>(kp, mub_tot, A + A_RHOB * N, b.rho, A + A_RHOBT * N, A + A_KAPC * N,
+                                              cz, nullptr);
         if (kp.walls) {
             k_adj_wall_rho_solid<<<gw, kBlock, 0, s>>>(kp, b.rho, A + A_RHOBT * N, A + A_RAVEB * N, A + A_WETC * N);
             k_adj_wall_gather<<<gw, kBlock, 0, s>>>(kp, A + A_RAVEB * N, A + A_RHOBT * N);
@@ -1154,7 +1270,7 @@ hipError_t launch_adj_step(hipStream_t s, int prec, const KP &kp, const Bufs &b,
                 k_adj_collide<P, true, true><<<gf, kBlock, 0, s>>>(kp, b, ft, b.lam[lcur], b.lam[1 - lcur]);
             else
                 k_adj_collide<P, false, true><<<gf, kBlock, 0, s>>>(kp, b, ft, b.lam[lcur], b.lam[1 - lcur]);
-            k_adj_phimu<P, true><<<zgrid(kp, 0, kp.nz), PCB, 0, s>>>(kp, b, kZChunk);
+            phimu<P, true>(s, kp, b);
         } else {
             if (pending)
                 k_adj_collide<P, true, false><<<gf, kBlock, 0, s>>>(kp, b, ft, b.lam[lcur], b.lam[1 - lcur]);
@@ -1167,7 +1283,7 @@ hipError_t launch_adj_step(hipStream_t s, int prec, const KP &kp, const Bufs &b,
                 else
                     k_adj_wall_move<P, false><<<gw, kBlock, 0, s>>>(kp, b, b.lam[lcur]);
             }
-            k_adj_phimu<P, false><<<zgrid(kp, 0, kp.nz), PCB, 0, s>>>(kp, b, kZChunk);
+            phimu<P, false>(s, kp, b);
         }
         hipError_t r = chain_tail(s, kp, b, true, A + A_NUC * (size_t)kp.N);
         if (r != hipSuccess) return r;

@@ -1,0 +1,75 @@
+"""The transposed-stencil marches of the adjoint at the edges of their tiles
+(32 x 12 and, from 2^20 nodes, 64 x 13; 32 x 16 for the density part).
+
+Narrow tiles: one adjoint step against oracle reverse mode on extents of one
+node, one less, equal to and one more than a tile.  Wide tiles: a periodic
+state repeated to more than 2^20 nodes has the repeated adjoint, node by node
+the same sums, so lambda must be equal bit for bit to that of the small box
+(narrow tiles), and the parameter gradients are the number of copies times
+those of the small box (to the rounding of the reductions)."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import droplet_rho, make_sim, oracle_params, rel_err, say
+from oracle import eos, lbm
+from paper_2504_03819_amd import inputs
+from test_gpu_adjoint import _oracle_vjp
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [((1, 1, 1), False), ((2, 13, 33), False), ((5, 12, 32), False), ((4, 11, 31), False), ((3, 25, 65), False),
+          ((5, 13, 33), True), ((4, 17, 31), True)]
+
+
+@pytest.mark.parametrize("shape,walls", SHAPES, ids=[f"{s}{'w' if w else ''}" for s, w in SHAPES])
+def test_tile_edges_match_oracle_reverse_mode(shape, walls):
+    say(f"adjoint tiles {shape} walls={walls}")
+    T = eos.temperature(0.8)
+    nz, ny, nx = shape
+    extra = dict(wet_mode=1, wet_value=1.3) if walls else {}
+    sim = make_sim(nx=nx, ny=ny, nz=nz, T=T, walls_z=int(walls), adjoint=1, **extra)
+    p = oracle_params(sim)
+    g = np.random.Generator(np.random.PCG64(7))
+    f0 = lbm.init(torch.tensor(droplet_rho(shape, T, walls=walls, radius=max(1.0, min(shape) / 3))), p,
+                  torch.tensor(0.03 * g.uniform(-1, 1, (3,) + shape)))
+    f = f0 + torch.tensor(inputs.uniform_noise(tuple(f0.shape), 2e-4, 3)) * (f0 != 0)
+    lam = torch.tensor(g.uniform(-1, 1, (27,) + shape))
+    sl = slice(1, -1) if walls else slice(None)
+    if walls:
+        lam[:, 0] = lam[:, -1] = 0
+    sim.set_populations(f)
+    sim.adjoint_seed_populations(lam)
+    sim.adjoint_step(None)
+    lo, ko, _, no = _oracle_vjp(f, lam, p)
+    gg = sim.adjoint_grads()
+    assert rel_err(sim.adjoint_state().cpu()[:, sl], lo[:, sl]) < 1e-11
+    # a one-node box has no gradient with respect to kappa (its Laplacian vanishes)
+    assert abs(gg["kappa"] - ko) < 1e-9 * max(abs(ko), 1e-3) and abs(gg["nu"] - no) < 1e-9 * max(abs(no), 1e-3)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_repeated_state_has_the_repeated_adjoint(precision):
+    shape, reps = (13, 27, 66), (4, 7, 2)
+    T = eos.temperature(0.85)
+    g = np.random.Generator(np.random.PCG64(11))
+    rho0 = torch.tensor(droplet_rho(shape, T, radius=4.0))
+    u0 = torch.tensor(0.03 * g.uniform(-1, 1, (3,) + shape))
+    seed = torch.tensor(g.uniform(-1, 1, shape))
+    out = []
+    for r in ((1, 1, 1), reps):
+        nz, ny, nx = (a * b for a, b in zip(shape, r))
+        sim = make_sim(nx=nx, ny=ny, nz=nz, T=T, adjoint=1, precision=precision, step_path=1)
+        sim.init_density(rho0.repeat(r), u0.repeat((1,) + r))
+        sim.step(2)
+        st = sim.get_state()
+        sim.adjoint_seed(seed.repeat(r))
+        sim.adjoint_step(st)
+        sim.adjoint_step(st)
+        out.append((sim.adjoint_state(), sim.adjoint_grads()))
+        sim.close()
+    (a, ga), (b, gb) = out
+    assert torch.equal(a.repeat((1,) + reps), b)
+    n = reps[0] * reps[1] * reps[2]
+    for k in ("kappa", "nu"):  # sums of 1.3e6 signed terms of magnitudes up to ~1e2 of the mean
+        assert abs(gb[k] - n * ga[k]) < 1e-9 * abs(n * ga[k]), (k, ga[k], gb[k])
