@@ -80,7 +80,11 @@ template <class real> struct Lam {
     __device__ Lam(void *q, const KP &kp) : p((real *)q), nx((unsigned)kp.nx) {}
     __device__ size_t off(int i, unsigned row, unsigned x) const { return ((size_t)row * 27 + i) * nx + x; }
     __device__ real ld(int i, unsigned row, unsigned x) const { return p[off(i, row, x)]; }
+    __device__ real ld_nt(int i, unsigned row, unsigned x) const { return ldnt(p + off(i, row, x)); }
     __device__ void st(int i, unsigned row, unsigned x, real v) const { p[off(i, row, x)] = v; }
+    __device__ void st_nt(int i, unsigned row, unsigned x, real v) const {
+        __builtin_nontemporal_store(v, p + off(i, row, x));
+    }
 };
 
 // Plane c of a (real) slot group.
@@ -289,7 +293,11 @@ template <int P> __global__ __launch_bounds__(kBlock) void k_adj_pack(KP kp, Buf
 // PEND: lam_in holds only the direct part of lambda(t+1); its last term is
 // added during the gather from the (rho_bar_total, j_bar) pack that the
 // previous adjoint step left (this kernel does not write it).
-template <int P, bool PEND, bool MASK>
+// NT: lambda, F, Q and mu are read once and the node's own lambda row is
+// written once, so from 2^20 nodes, where the lattices exceed the caches, they
+// go non-temporal (192x192x96 in FP32: 342 -> 320 us); a small box keeps them
+// in the caches (48x40x32 in FP64: 17.2 us, 19.2 non-temporal).
+template <int P, bool PEND, bool MASK, bool NT>
 __global__ __launch_bounds__(kBlock) void k_adj_collide(KP kp, Bufs b, const void *ft, const void *lam_in,
                                                         void *lam_out) {
     using real = real_t<P>;
@@ -304,10 +312,13 @@ __global__ __launch_bounds__(kBlock) void k_adj_collide(KP kp, Bufs b, const voi
     const Lam<real> lin(const_cast<void *>(lam_in), kp), lout(lam_out, kp);
     // solid mask: bit i of the neighbour word marks a link that ends on a
     // solid node (bounce-back); a solid node holds no lambda
+    auto ld = [&](const auto *p) { return NT ? ldnt(p) : *p; };
+    auto ldl = [&](int i, unsigned r, unsigned xx) { return NT ? lin.ld_nt(i, r, xx) : lin.ld(i, r, xx); };
+    auto stl = [&](int i, real v) { NT ? lout.st_nt(i, row, (unsigned)x, v) : lout.st(i, row, (unsigned)x, v); };
     const unsigned wm = MASK ? b.nbr[n] : 0u;
     if (MASK && (wm & kSelfBit)) {
 #pragma unroll
-        for (int i = 0; i < 27; ++i) lout.st(i, row, (unsigned)x, (real)0);
+        for (int i = 0; i < 27; ++i) stl(i, (real)0);
         return;
     }
 
@@ -320,11 +331,11 @@ __global__ __launch_bounds__(kBlock) void k_adj_collide(KP kp, Bufs b, const voi
     real jx, jy, jz;
     moments(k, rd, jx, jy, jz);
     const real *F = (const real *)b.F;
-    const real Fx = F[n], Fy = F[kp.N + n], Fz = F[2 * (size_t)kp.N + n];
-    const Kin<real> kin = kinematics(kp, rd, jx, jy, jz, Fx, Fy, Fz, b.mu[n]);
+    const real Fx = ld(F + n), Fy = ld(F + kp.N + n), Fz = ld(F + 2 * (size_t)kp.N + n);
+    const Kin<real> kin = kinematics(kp, rd, jx, jy, jz, Fx, Fy, Fz, ld(b.mu + n));
     const real ux = kin.ux, uy = kin.uy, uz = kin.uz, pm = kin.pm;
     const real *Qa = (const real *)b.Q;
-    const real q200 = Qa[n], q020 = Qa[kp.N + n], q002 = Qa[2 * (size_t)kp.N + n];
+    const real q200 = ld(Qa + n), q020 = ld(Qa + kp.N + n), q002 = ld(Qa + 2 * (size_t)kp.N + n);
     real q220 = 0, q202 = 0, q022 = 0;
     const real third = (real)(1.0 / 3.0);
     if (kp.corr4) {
@@ -363,9 +374,9 @@ __global__ __launch_bounds__(kBlock) void k_adj_collide(KP kp, Bufs b, const voi
         for (int i = 0; i < 27; ++i) {
             const int cz = czi(i);
             if (bounce(i))
-                l[i] = lin.ld(26 - i, row, (unsigned)x) + final_term<real>(pk, 26 - i, n);
+                l[i] = ldl(26 - i, row, (unsigned)x) + final_term<real>(pk, 26 - i, n);
             else
-                l[i] = lin.ld(i, nb.row(cyi(i), cz), nb.xo(cxi(i))) +
+                l[i] = ldl(i, nb.row(cyi(i), cz), nb.xo(cxi(i))) +
                        final_term<real>(pk, i, nb.at(cxi(i), cyi(i), cz));
         }
     } else {
@@ -373,9 +384,9 @@ __global__ __launch_bounds__(kBlock) void k_adj_collide(KP kp, Bufs b, const voi
         for (int i = 0; i < 27; ++i) {
             const int cz = czi(i);
             if (bounce(i))
-                l[i] = lin.ld(26 - i, row, (unsigned)x);
+                l[i] = ldl(26 - i, row, (unsigned)x);
             else
-                l[i] = lin.ld(i, nb.row(cyi(i), cz), nb.xo(cxi(i)));
+                l[i] = ldl(i, nb.row(cyi(i), cz), nb.xo(cxi(i)));
         }
     }
     if constexpr (PEND && sizeof(real) == 4 && !MASK) {
@@ -419,7 +430,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_collide(KP kp, Bufs b, const voi
     ubz -= tz;
     cm_forward_T(l, ux, uy, uz);  // direct part of lambda(t)
 #pragma unroll
-    for (int i = 0; i < 27; ++i) lout.st(i, row, (unsigned)x, l[i]);
+    for (int i = 0; i < 27; ++i) stl(i, l[i]);
 
     // fold the fourth-order correction (Eq. (28)) into Q_bar
     real qb0 = sb.Q[0], qb1 = sb.Q[1], qb2 = sb.Q[2];
@@ -1142,6 +1153,19 @@ __global__ __launch_bounds__(kBlock) void k_adj_init_out(KP kp, Bufs b, const do
     out[n] = fluid_node(kp, b, n) ? rhobt[n] : 0.0;
 }
 
+template <int P, bool MASK>
+void adj_collide(hipStream_t s, const KP &kp, const Bufs &b, const void *ft, int lcur, bool pending) {
+    auto go = [&](auto pend, auto nt) {
+        k_adj_collide<P, decltype(pend)::value, MASK, decltype(nt)::value>
+            <<<nblocks(kp.nfluid), kBlock, 0, s>>>(kp, b, ft, b.lam[lcur], b.lam[1 - lcur]);
+    };
+    const bool nt = kp.N >= (1u << 20);
+    if (pending)
+        nt ? go(std::true_type{}, std::true_type{}) : go(std::true_type{}, std::false_type{});
+    else
+        nt ? go(std::false_type{}, std::true_type{}) : go(std::false_type{}, std::false_type{});
+}
+
 // From 2^20 nodes the wide tile, one workgroup per CU: fewer ring nodes and
 // halo lines (192x192x96 in FP32: 133 against 147 us); below, the narrow one,
 // whose two workgroups per CU cover a small grid in more pieces (48x40x32 in
@@ -1266,16 +1290,10 @@ hipError_t launch_adj_step(hipStream_t s, int prec, const KP &kp, const Bufs &b,
     return dispatch(prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         if (kp.masked) {
-            if (pending)
-                k_adj_collide<P, true, true><<<gf, kBlock, 0, s>>>(kp, b, ft, b.lam[lcur], b.lam[1 - lcur]);
-            else
-                k_adj_collide<P, false, true><<<gf, kBlock, 0, s>>>(kp, b, ft, b.lam[lcur], b.lam[1 - lcur]);
+            adj_collide<P, true>(s, kp, b, ft, lcur, pending);
             phimu<P, true>(s, kp, b);
         } else {
-            if (pending)
-                k_adj_collide<P, true, false><<<gf, kBlock, 0, s>>>(kp, b, ft, b.lam[lcur], b.lam[1 - lcur]);
-            else
-                k_adj_collide<P, false, false><<<gf, kBlock, 0, s>>>(kp, b, ft, b.lam[lcur], b.lam[1 - lcur]);
+            adj_collide<P, false>(s, kp, b, ft, lcur, pending);
             if (kp.moving) {
                 const unsigned gw = nblocks(2 * (size_t)kp.plane);
                 if (pending)
