@@ -6,20 +6,17 @@
 //           u = (j + F/2)/rho, phi = (p_m - rho/3) u
 //   phi  -> Q_aa = -3 d_a phi_a                              (Eq. (27))
 //
-// Each workgroup owns a 64 x 16 column tile and marches in z over a chunk of
-// planes.  The isotropic D3Q27 stencils factor into D1Q3 pieces (weights
-// 1/6, 2/3, 1/6 along each axis), so every stencil is evaluated as an
-// in-plane part, read from one LDS plane, and a z part, combined in a
-// three-plane register ring that each thread keeps for the columns it owns:
+// The isotropic D3Q27 stencils factor into D1Q3 pieces (weights 1/6, 2/3, 1/6
+// along each axis), so every stencil is evaluated as an in-plane part, read
+// from one LDS plane, and a z part, combined in a three-plane register ring
+// that each thread keeps for the columns it owns:
 //   lap_h g = 6 (Wz (Wx Wy g) - g)
 //   d_x g   = 1/2 Wz (Dx Wy g),  d_y g = 1/2 Wz (Wx Dy g),  d_z g = 1/2 Dz (Wx Wy g)
-// with W the D1Q3 weights and D g = g(+1) - g(-1).  LDS holds a ring of three
-// rho planes (tile + 4-node halo), two mu planes (3-node halo) and one phi
-// plane (1-node halo).  Iteration k of the march loads rho(k+3), evaluates
-// mu(k+2) and the in-plane parts of mu(k+2), then F and phi at k+1 and the
-// in-plane parts of phi(k+1), and Q at k; global loads run ahead of their
-// use.  Outputs per fluid node: mu (double), F and Q (compute precision);
-// mu is also written at the solid planes.
+// with W the D1Q3 weights and D g = g(+1) - g(-1).  Three kernels sum in this
+// order, so all of them give the same bits: k_chain_block for small grids,
+// k_chain_march for periodic ones, k_chain between walls.  Outputs per fluid
+// node: mu (double), F and Q (compute precision); mu is also written at the
+// solid planes.
 #include <type_traits>
 
 #include "lbfe_device.h"
@@ -27,7 +24,7 @@
 namespace lbfe {
 namespace {
 
-constexpr int TX = 64, TY = 16;  // 1024 threads, one workgroup per CU (LDS)
+constexpr int TX = 64, TY = 16, NTC = TX * TY;  // 1024 threads, one workgroup per CU (LDS)
 constexpr int CB = TX * TY;                            // threads: one per tile column
 constexpr int WR = TX + 8, HR = TY + 8, NR = WR * HR;  // rho region (halo 4)
 constexpr int WM = TX + 6, HM = TY + 6, NM = WM * HM;  // mu region (halo 3)
@@ -136,10 +133,17 @@ __device__ inline void q_of(real Xa, real Xb, real Xc, real Ya, real Yb, real Yc
     qz = h * (Zc - Za);
 }
 
-template <int P, bool WALLS>
+// The march between walls: each workgroup owns a 64 x 16 column tile and
+// marches in z over a chunk of planes.  LDS holds a ring of three rho planes
+// (tile + 4-node halo), two mu planes (3-node halo) and one phi plane (1-node
+// halo).  Iteration k of the march loads rho(k+3), evaluates mu(k+2) and the
+// in-plane parts of mu(k+2), then F and phi at k+1 and the in-plane parts of
+// phi(k+1), and Q at k; global loads run ahead of their use.  (k_chain_march
+// with the wall planes spills at 16 waves, 192x192x96 FP32 68 against 67 us,
+// and in FP64 its five rho planes do not fit the LDS.)
+template <class real>
 __global__ __launch_bounds__(CB) void k_chain(KP kp, const double *__restrict__ rho, const double *__restrict__ mu0,
                                               const void *jq, double *__restrict__ mu, void *Fq, void *Qq, int cz) {
-    using real = typename Pol<P>::real;
     __shared__ double sr[3][NRP];
     __shared__ double sm[2][NM];
     __shared__ real sp[3][NP];
@@ -163,10 +167,9 @@ __global__ __launch_bounds__(CB) void k_chain(KP kp, const double *__restrict__ 
     real *F = (real *)Fq;
     real *Q = (real *)Qq;
 
-    // WALLS: solid planes z = 0 and z = nz-1 (kp.walls; a template argument,
-    // so the periodic kernel carries none of the wall code)
-    auto fluid = [&](int p) { return WALLS ? (p >= 1 && p <= kp.nz - 2) : true; };
-    auto valid = [&](int p) { return !WALLS || (p >= 0 && p <= kp.nz - 1); };
+    // solid planes z = 0 and z = nz-1
+    auto fluid = [&](int p) { return p >= 1 && p <= kp.nz - 2; };
+    auto valid = [&](int p) { return p >= 0 && p <= kp.nz - 1; };
     auto interior = [&](int a, int b) { return x0 + a < kp.nx && y0 + b < kp.ny; };
     // plane indices wrap periodically; inside the march they advance by one
     auto next = [&](int g) { return g + 1 == kp.nz ? 0 : g + 1; };
@@ -298,7 +301,7 @@ __global__ __launch_bounds__(CB) void k_chain(KP kp, const double *__restrict__ 
             const int s3 = slot3(q3), s2 = slot3(p);
             const bool do_mu = p >= zs - 2 && fluid(p);
             const bool out_plane = p >= zs && p < ze;
-            const bool full = WALLS && (p == 1 || p == kp.nz - 2);
+            const bool full = p == 1 || p == kp.nz - 2;
             const __amdgpu_buffer_rsrc_t rmu = plane_rsrc(mu + pbase(g2), pbytes8);
 #pragma unroll
             for (int m = 0; m < MM; ++m) {
@@ -322,13 +325,11 @@ __global__ __launch_bounds__(CB) void k_chain(KP kp, const double *__restrict__ 
                 bstore(v, rmu, out ? omu[m] : kOOB);
             }
             issue_mu0(g3);
-            if constexpr (WALLS) {
-                if (p == 1 && p >= zs - 2) {  // bottom solid plane, from the first fluid plane
-                    __syncthreads();
-                    wall_mu(0, 1, zs - 1 == 0);
-                } else if (p == kp.nz - 1 && p >= zs - 2) {  // top solid plane
-                    wall_mu(p, p - 1, p == ze);
-                }
+            if (p == 1 && p >= zs - 2) {  // bottom solid plane, from the first fluid plane
+                __syncthreads();
+                wall_mu(0, 1, zs - 1 == 0);
+            } else if (p == kp.nz - 1 && p >= zs - 2) {  // top solid plane
+                wall_mu(p, p - 1, p == ze);
             }
         }
         __syncthreads();
@@ -360,7 +361,7 @@ __global__ __launch_bounds__(CB) void k_chain(KP kp, const double *__restrict__ 
                     if (do_abc) abc(p2, m, Ar[m][2], Br[m][2], Cr[m][2]);
                     // the bottom solid plane's mu only exists from the step
                     // that evaluated the first fluid plane: refresh its entry
-                    if (do_abc && WALLS && p2 == 1) abc(0, m, Ar[m][1], Br[m][1], Cr[m][1]);
+                    if (do_abc && p2 == 1) abc(0, m, Ar[m][1], Br[m][1], Cr[m][1]);
                     if (do_phi && !fl1) sp[0][r] = sp[1][r] = sp[2][r] = (real)0;
                     if (do_phi && fl1) {
                         const double gx = 0.5 * (A1 * Ar[m][0] + A0 * Ar[m][1] + A1 * Ar[m][2]);
@@ -430,6 +431,324 @@ __global__ __launch_bounds__(CB) void k_chain(KP kp, const double *__restrict__ 
         g2 = g3;
         g3 = g4;
         g4 = next(g4);
+    }
+}
+
+// The R-row forms of smooth2, plane_grad and plane_div: R vertically adjacent
+// points from index c of the first, the x parts of a row formed once for the
+// (up to three) points that share it.  Every value is rounded as in the
+// one-point form.
+template <int W, int R> __device__ inline void smooth_rows(const double *g, int c, double (&P)[R], double (&mid)[R]) {
+    double x[R + 2];
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {
+        const double *r = g + c + (i - 1) * W;
+        const double l = r[-1], m = r[0], h = r[1];
+        x[i] = A1 * l + A0 * m + A1 * h;
+        if (i >= 1 && i <= R) mid[i - 1] = m;
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) P[i] = A1 * x[i] + A0 * x[i + 1] + A1 * x[i + 2];
+}
+template <int W, int R>
+__device__ inline void grad_rows(const double *g, int c, double (&A)[R], double (&B)[R], double (&C)[R], double (&mid)[R]) {
+    double l[R + 2], m[R + 2], h[R + 2], s[R + 2];
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {
+        const double *r = g + c + (i - 1) * W;
+        l[i] = r[-1], m[i] = r[0], h[i] = r[1];
+        s[i] = A1 * l[i] + A0 * m[i] + A1 * h[i];
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        A[i] = A1 * (h[i] - l[i]) + A0 * (h[i + 1] - l[i + 1]) + A1 * (h[i + 2] - l[i + 2]);
+        B[i] = A1 * (l[i + 2] - l[i]) + A0 * (m[i + 2] - m[i]) + A1 * (h[i + 2] - h[i]);
+        C[i] = A1 * s[i] + A0 * s[i + 1] + A1 * s[i + 2];
+        mid[i] = m[i + 1];
+    }
+}
+template <int W, int R, class real>
+__device__ inline void div_rows(const real *gx, const real *gy, const real *gz, int c, real (&X)[R], real (&Y)[R],
+                                real (&Z)[R]) {
+    const real w1r = (real)A1, w0r = (real)A0;
+    real dx[R + 2], yl[R + 2], ym[R + 2], yh[R + 2], sz[R + 2];
+#pragma unroll
+    for (int i = 0; i < R + 2; ++i) {
+        const int o = c + (i - 1) * W;
+        dx[i] = gx[o + 1] - gx[o - 1];
+        yl[i] = gy[o - 1], ym[i] = gy[o], yh[i] = gy[o + 1];
+        sz[i] = w1r * gz[o - 1] + w0r * gz[o] + w1r * gz[o + 1];
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        X[i] = w1r * dx[i] + w0r * dx[i + 1] + w1r * dx[i + 2];
+        Y[i] = w1r * (yl[i + 2] - yl[i]) + w0r * (ym[i + 2] - ym[i]) + w1r * (yh[i + 2] - yh[i]);
+        Z[i] = w1r * sz[i] + w0r * sz[i + 1] + w1r * sz[i + 2];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The march of periodic grids.  The three stencils run at the same time on
+// planes one stage apart, each on waves of its own, so that a plane costs one
+// barrier: at iteration t the five mu waves store rho(t) to LDS and evaluate
+// mu(t-2), the seven phi waves F and phi(t-4), the four Q waves Q(t-6), each
+// from what the iteration before left in LDS.  A thread owns 5, 3 or 4 points
+// above one another and forms the x parts of a row once for all of them, and
+// keeps only its own stage's rings (126 VGPRs at 16 waves; one thread that
+// keeps all three needs 204).  rho stays in LDS for five planes, until phi has
+// used it: read again from memory it had left the L2 (256^3: +13 % traffic).
+// The planes zs-3 .. zs-1 are loaded at once, so a chunk of c planes takes
+// c + 6 iterations, and fill planes that a stage does not need have an empty
+// descriptor.  Bound by the halo and fill traffic (us, against the march with
+// three barriers and one point per thread): 128^3 FP64 57 -> 47, FP32 42 ->
+// 34; 192x192x96 83 -> 68, 62 -> 47; 512^3 2920 -> 2720-2870, 1955 -> 1743;
+// 256^3 388 -> 418, 270 -> 246-275.
+// ---------------------------------------------------------------------------
+template <class real>
+__global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__restrict__ rho, const double *__restrict__ mu0,
+                                               const void *jq, double *__restrict__ mu, void *Fq, void *Qq, int cz) {
+    constexpr int HM = 2, HR = 3;  // halos of the mu and rho regions
+    // rows per thread and waves of the mu, phi and Q roles
+    constexpr int RB = 5, RC = 3, RD = 4, VB = 5, VC = 7, VD = 4;
+    constexpr int WM = TX + 2 * HM, YM = TY + 2 * HM, BM = (YM + RB - 1) / RB;  // mu region, row blocks
+    constexpr int WR = TX + 2 * HR, NR = WR * (TY + 2 * HR), NRP = WR * (BM * RB + 2);
+    constexpr int WP = TX + 2, YP = TY + 2, BP = YP / RC;
+    constexpr int MR = (NR + VB * 64 - 1) / (VB * 64);  // rho points per thread of the mu role
+    static_assert((VB + VC + VD) * 64 == NTC && BM * WM <= VB * 64 && BP * RC == YP && BP * WP <= VC * 64 &&
+                      TX * (TY / RD) == VD * 64,
+                  "one unit per thread of a role");
+    constexpr int LR = MR * VB * 64 > NRP ? MR * VB * 64 : NRP;  // whole rounds of the mu role's stores
+    static_assert(NRP >= NR, "rho plane");
+    __shared__ double sr[5][LR];               // rho plane t (slot t mod 5)
+    __shared__ double sm[2][BM * RB * WM];     // mu plane
+    __shared__ real sp[2][3][WP * YP];         // phi plane
+
+    // Workgroups are dealt round-robin to the 8 XCDs in linear order; the
+    // linear id is remapped so that each XCD runs a contiguous range of
+    // (chunk, tile) pairs, tiles of one chunk consecutively: neighbouring
+    // tiles then share their halo planes through that XCD's L2.
+    const int ntx = (kp.nx + TX - 1) / TX;
+    const unsigned ntiles = gridDim.x, nb = gridDim.x * gridDim.y;
+    const unsigned hw = blockIdx.y * gridDim.x + blockIdx.x;
+    const unsigned q = nb >> 3, rem = nb & 7u, xcd = hw & 7u;
+    const unsigned lid = xcd * q + (xcd < rem ? xcd : rem) + (hw >> 3);
+    const int tile = (int)(lid % ntiles), chunk = (int)(lid / ntiles);
+    const int x0 = (tile % ntx) * TX, y0 = (tile / ntx) * TY;
+    const int zs = kp.z0 + chunk * cz;
+    const int ze = min(zs + cz, kp.z1);
+    const size_t N = kp.N;
+    constexpr unsigned S = sizeof(real);
+    const unsigned pbytes8 = kp.plane * 8u, pbytesr = kp.plane * S;
+
+    // plane indices wrap periodically; inside the march they advance by one
+    auto next = [&](int g) { return g + 1 == kp.nz ? 0 : g + 1; };
+    auto pbase = [&](int g) { return (size_t)g * kp.plane; };
+    auto inside = [&](int x, int y) { return x >= 0 && x < TX && y >= 0 && y < TY && x0 + x < kp.nx && y0 + y < kp.ny; };
+    auto node = [&](int x, int y) { return (unsigned)wrap(y0 + y, kp.ny) * kp.nx + (unsigned)wrap(x0 + x, kp.nx); };
+
+    const int tb = zs, te = ze + 5;  // first and last iteration
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (wave < VC) {
+        // ---- F and phi(t-4) from the in-plane parts of mu(t-5 .. t-3)
+        const int u = wave * 64 + lane, pa = u % WP, pb = u / WP * RC;
+        const bool has = u < BP * WP;
+        const int cg = (pb + HM - 1) * WM + pa + HM - 1;  // first point in the mu region
+        const int cp = pb * WP + pa;                      // ... in the phi region
+        const int cd = (pb + HR - 1) * WR + pa + HR - 1;  // ... in the rho region
+        const real *j = (const real *)jq;
+        real *F = (real *)Fq;
+        unsigned off[RC], own = 0;
+#pragma unroll
+        for (int i = 0; i < RC; ++i) {
+            off[i] = has ? S * node(pa - 1, pb + i - 1) : kOOB;
+            if (has && inside(pa - 1, pb + i - 1)) own |= 1u << i;
+        }
+        real pj[RC][3];
+        auto issue = [&](int g, bool ok) {  // j of plane g
+            const size_t base = pbase(g);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const __amdgpu_buffer_rsrc_t rj = plane_rsrc(j + c * N + base, ok ? pbytesr : 0u);
+#pragma unroll
+                for (int i = 0; i < RC; ++i) bload(pj[i][c], rj, off[i]);
+            }
+        };
+        double Aa[RC], Ab[RC], Ba[RC], Bb[RC], Ca[RC], Cb[RC], mc[RC];
+#pragma unroll
+        for (int i = 0; i < RC; ++i) Aa[i] = Ab[i] = Ba[i] = Bb[i] = Ca[i] = Cb[i] = mc[i] = 0.0;
+        int g = wrap(tb - 4, kp.nz);
+        issue(g, false);
+        int s4 = 4;  // slot of plane t - 4; plane zs - 3 is in slot 0
+        __syncthreads();
+        for (int t = tb; t <= te; ++t) {
+            const int p3 = t - 3, p = t - 4;
+            const size_t base = pbase(g);
+            real f[RC][3];
+#pragma unroll
+            for (int i = 0; i < RC; ++i) f[i][0] = f[i][1] = f[i][2] = (real)0;
+            if (p3 >= zs - 2 && p3 <= ze + 1 && has) {
+                double An[RC], Bn[RC], Cn[RC], mid[RC];
+                grad_rows<WM, RC>(sm[p3 & 1], cg, An, Bn, Cn, mid);
+                if (p >= zs - 1) {
+#pragma unroll
+                    for (int i = 0; i < RC; ++i) {
+                        real ph[3];
+                        force_phi(Aa[i], Ab[i], An[i], Ba[i], Bb[i], Bn[i], Ca[i], Cn[i], sr[s4][cd + i * WR], mc[i], pj[i],
+                                  f[i][0], f[i][1], f[i][2], ph);
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) sp[p & 1][c][cp + i * WP] = ph[c];
+                    }
+                }
+#pragma unroll
+                for (int i = 0; i < RC; ++i) {
+                    Aa[i] = Ab[i], Ba[i] = Bb[i], Ca[i] = Cb[i];
+                    Ab[i] = An[i], Bb[i] = Bn[i], Cb[i] = Cn[i];
+                    mc[i] = mid[i];
+                }
+            }
+            // the next plane's loads go ahead of this plane's stores, so that
+            // waiting for them does not wait for the stores
+            g = next(g);
+            issue(g, p + 1 >= zs - 1 && p + 1 <= ze);
+            const bool out = p >= zs && p < ze;
+            const __amdgpu_buffer_rsrc_t r0 = plane_rsrc(F + base, pbytesr);
+            const __amdgpu_buffer_rsrc_t r1 = plane_rsrc(F + N + base, pbytesr);
+            const __amdgpu_buffer_rsrc_t r2 = plane_rsrc(F + 2 * N + base, pbytesr);
+#pragma unroll
+            for (int i = 0; i < RC; ++i) {
+                const unsigned o = out && ((own >> i) & 1u) ? off[i] : kOOB;
+                bstore(f[i][0], r0, o);
+                bstore(f[i][1], r1, o);
+                bstore(f[i][2], r2, o);
+            }
+            s4 = s4 == 4 ? 0 : s4 + 1;
+            __syncthreads();
+        }
+    } else if (wave >= 8 && wave < 8 + VD) {
+        // ---- Q(t-6) from the in-plane parts of phi(t-7 .. t-5)
+        const int u = (wave - 8) * 64 + lane, qa = u % TX, qb = u / TX * RD;
+        const int cq = (qb + 1) * WP + qa + 1;  // first point in the phi region
+        real *Q = (real *)Qq;
+        unsigned off[RD];
+#pragma unroll
+        for (int i = 0; i < RD; ++i) off[i] = inside(qa, qb + i) ? S * node(qa, qb + i) : kOOB;
+        real Xa[RD], Xb[RD], Ya[RD], Yb[RD], Za[RD], Zb[RD];
+#pragma unroll
+        for (int i = 0; i < RD; ++i) Xa[i] = Xb[i] = Ya[i] = Yb[i] = Za[i] = Zb[i] = (real)0;
+        int g = wrap(tb - 6, kp.nz);
+        __syncthreads();
+        for (int t = tb; t <= te; ++t) {
+            if (t - 5 >= zs - 1) {
+                real Xn[RD], Yn[RD], Zn[RD];
+                const int sl = (t - 5) & 1;
+                div_rows<WP, RD>(sp[sl][0], sp[sl][1], sp[sl][2], cq, Xn, Yn, Zn);
+                const size_t base = pbase(g);
+                const __amdgpu_buffer_rsrc_t r0 = plane_rsrc(Q + base, pbytesr);
+                const __amdgpu_buffer_rsrc_t r1 = plane_rsrc(Q + N + base, pbytesr);
+                const __amdgpu_buffer_rsrc_t r2 = plane_rsrc(Q + 2 * N + base, pbytesr);
+#pragma unroll
+                for (int i = 0; i < RD; ++i) {
+                    real qx, qy, qz;
+                    q_of(Xa[i], Xb[i], Xn[i], Ya[i], Yb[i], Yn[i], Za[i], Zn[i], qx, qy, qz);
+                    const unsigned o = t - 6 >= zs ? off[i] : kOOB;
+                    bstore(qx, r0, o);
+                    bstore(qy, r1, o);
+                    bstore(qz, r2, o);
+                    Xa[i] = Xb[i], Ya[i] = Yb[i], Za[i] = Zb[i];
+                    Xb[i] = Xn[i], Yb[i] = Yn[i], Zb[i] = Zn[i];
+                }
+            }
+            g = next(g);
+            __syncthreads();
+        }
+    } else {
+        // ---- rho(t) into LDS; mu(t-2) from Wx Wy rho of planes t-3, t-2, t-1
+        const int u = (wave == VC ? 0 : wave - 11) * 64 + lane, ma = u % WM, mb = u / WM * RB;
+        const bool has = u < BM * WM;
+        const int cr = (mb + 1) * WR + ma + 1;  // first point in the rho region
+        const int cm = mb * WM + ma;            // ... in the mu region
+        unsigned offr[MR], off[RB], own = 0;
+#pragma unroll
+        for (int m = 0; m < MR; ++m) {
+            const int r = u + m * VB * 64;
+            offr[m] = r < NR ? 8u * node(r % WR - HR, r / WR - HR) : kOOB;
+        }
+#pragma unroll
+        for (int i = 0; i < RB; ++i) {
+            off[i] = has && mb + i < YM ? 8u * node(ma - HM, mb + i - HM) : kOOB;
+            if (has && inside(ma - HM, mb + i - HM)) own |= 1u << i;
+        }
+        double pr[MR], m0[RB];
+        auto issue_rho = [&](int g, bool ok) {
+            const __amdgpu_buffer_rsrc_t r = plane_rsrc(rho + pbase(g), ok ? pbytes8 : 0u);
+#pragma unroll
+            for (int m = 0; m < MR; ++m) bload(pr[m], r, offr[m]);
+        };
+        auto issue_mu0 = [&](int g, bool ok) {
+            const __amdgpu_buffer_rsrc_t r = plane_rsrc(mu0 + pbase(g), ok ? pbytes8 : 0u);
+#pragma unroll
+            for (int i = 0; i < RB; ++i) bload(m0[i], r, off[i]);
+        };
+        // planes zs - 3 .. zs - 1 at once, then Wx Wy rho of the first two
+        double P0[RB], P1[RB], rc[RB];
+        int gn = wrap(zs - 3, kp.nz), g2 = next(gn);
+        {
+            double pa[MR], pb[MR];
+            issue_rho(gn, true);
+#pragma unroll
+            for (int m = 0; m < MR; ++m) pa[m] = pr[m];
+            issue_rho(g2, true);
+#pragma unroll
+            for (int m = 0; m < MR; ++m) pb[m] = pr[m];
+            gn = next(g2);
+            issue_rho(gn, true);
+#pragma unroll
+            for (int m = 0; m < MR; ++m) {
+                sr[0][u + m * VB * 64] = pa[m];
+                sr[1][u + m * VB * 64] = pb[m];
+                sr[2][u + m * VB * 64] = pr[m];
+            }
+            gn = next(gn);
+            issue_rho(gn, true);
+            issue_mu0(g2, true);
+            __syncthreads();
+            smooth_rows<WR, RB>(sr[0], cr, P0, rc);
+            smooth_rows<WR, RB>(sr[1], cr, P1, rc);
+        }
+        int s0 = 3;  // slot of plane t
+        for (int t = tb; t <= te; ++t) {
+#pragma unroll
+            for (int m = 0; m < MR; ++m)
+                sr[s0][u + m * VB * 64] = pr[m];
+            gn = next(gn);
+            issue_rho(gn, t + 1 <= ze + 2);
+            const int p = t - 2;
+            double v[RB];
+#pragma unroll
+            for (int i = 0; i < RB; ++i) v[i] = 0.0;
+            if (p <= ze + 1 && has) {
+                double P2[RB], mid[RB];
+                smooth_rows<WR, RB>(sr[s0 == 0 ? 4 : s0 - 1], cr, P2, mid);
+#pragma unroll
+                for (int i = 0; i < RB; ++i) {
+                    const double s27 = A1 * P0[i] + A0 * P1[i] + A1 * P2[i];
+                    v[i] = m0[i] - kp.kappa * 6.0 * (s27 - rc[i]);
+                    P0[i] = P1[i];
+                    P1[i] = P2[i];
+                    rc[i] = mid[i];
+                }
+#pragma unroll
+                for (int i = 0; i < RB; ++i) sm[p & 1][cm + i * WM] = v[i];
+            }
+            const bool out = p >= zs && p < ze;
+            const __amdgpu_buffer_rsrc_t rmu = plane_rsrc(mu + pbase(g2), pbytes8);
+            g2 = next(g2);
+            issue_mu0(g2, p + 1 <= ze + 1);
+#pragma unroll
+            for (int i = 0; i < RB; ++i) bstore(v[i], rmu, out && ((own >> i) & 1u) ? off[i] : kOOB);
+            s0 = s0 == 4 ? 0 : s0 + 1;
+            __syncthreads();
+        }
     }
 }
 
@@ -646,8 +965,10 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
 // Planes per workgroup.  One workgroup fits a CU (LDS), and every march
 // starts with six pipeline-fill planes, so chunks of c planes cost the
 // busiest CU ceil(workgroups / CUs) x (c + 6) plane iterations; the chunk
-// length from 64 down to 1 that minimises it is taken (the longer on ties).
-// (128-plane chunks, which the count favours at 512^3, measured slower.)
+// length from 64 down to 1 that minimises it is taken (the longer on ties;
+// with powers of two only, 160^3 ran 32-plane chunks on 150 CUs, 137 us in
+// FP64 against 76 for 20-plane ones on 240).  (128-plane chunks, which the
+// count favours at 512^3, measured slower.)
 constexpr unsigned kCUs = 256;  // MI355X
 static int chain_chunk(const KP &kp, unsigned tiles) {
     const int nzf = kp.z1 - kp.z0;
@@ -656,20 +977,19 @@ static int chain_chunk(const KP &kp, unsigned tiles) {
         return ((wg + kCUs - 1) / kCUs) * (size_t)(c + 6);
     };
     int cz = 64;
-    for (int c = 32; c >= 1; c /= 2)
+    for (int c = 63; c >= 1; --c)
         if (iters(c) < iters(cz)) cz = c;
     return cz;
 }
 
 // Tile of k_chain_block.
-// The block kernel takes grids below 2^20 fluid nodes, where the march waits
-// for its barriers and its fill planes (us per step, march against block, two-
-// pass path: FP64 16^3 34.8 / 16.2, 32^3 38.7 / 18.8, 64^3 61 / 48, 101x67x53
-// 92 / 77, 96^3 152 / 140; FP32 32^3 30 / 16.4, 64^3 42 / 32, 96^3 95 / 86);
-// beyond, the blocks' recomputed region costs more (128^3 FP64 301 / 329, FP32
-// 165 / 184).  A chunk length that the caller forces and the block kernel does
-// not have (it has 1, 2 and 4) goes to the march.
-constexpr unsigned kBlockNodes = 1u << 20;
+// The block kernel takes grids below 2^19 fluid nodes, where a march waits for
+// its fill planes (us per step, march against block, two-pass path, periodic:
+// FP64 64^3 54.1 / 49.6, 80^3 90.0 / 86.7; FP32 64^3 36.4 / 32.3, 80^3 60.3 /
+// 59.2); beyond, the blocks' recomputed region costs more (96^3 FP64 132.9 /
+// 139.6, FP32 80.3 / 86.0; 128^3 291 / 328).  A chunk length that the caller
+// forces and the block kernel does not have (it has 1, 2 and 4) goes to a march.
+constexpr unsigned kBlockNodes = 1u << 19;
 constexpr int BX = 16, BY = 8;  // 32x8, 32x4 and 16x4 blocks: 0-12 % slower per step
 static bool chain_block_grid(const KP &kp) { return kp.nfluid < kBlockNodes; }
 
@@ -687,7 +1007,10 @@ int chain_chunk_for(const KP &kp) {
 }
 
 template <class real, bool WALLS, int CZ> static void go_block(hipStream_t s, const KP &kp, const Bufs &b) {
-    constexpr int NT = WALLS ? 320 : 256;  // one mu column per thread (308, 240)
+    // 256 threads hold the 240 mu columns; next to walls, with 308, 512 are
+    // faster where a block has work for them (us per step at 96^3 FP64 145
+    // against 148 with 256 and 158 with 320; at 32^3 22.6 against 21.9)
+    constexpr int NT = WALLS && CZ == 4 ? 512 : 256;
     const dim3 g((kp.nx + BX - 1) / BX * ((kp.ny + BY - 1) / BY), (kp.z1 - kp.z0 + CZ - 1) / CZ);
     k_chain_block<real, WALLS, BX, BY, CZ, NT><<<g, NT, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q);
 }
@@ -711,19 +1034,17 @@ hipError_t launch_chain(hipStream_t s, int prec, const KP &kp, const Bufs &b) {
         return hipGetLastError();
     }
     const dim3 grid(ntx * nty, (nzf + cz - 1) / cz);
-    auto go = [&](auto pc) {
-        constexpr int P = decltype(pc)::value;
+    auto go = [&](auto real) {
+        using R = decltype(real);
         if (kp.walls)
-            k_chain<P, true><<<grid, CB, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
+            k_chain<R><<<grid, CB, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
         else
-            k_chain<P, false><<<grid, CB, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
+            k_chain_march<R><<<grid, NTC, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
     };
-    switch (prec) {
-        case LBFE_FP64: go(std::integral_constant<int, LBFE_FP64>{}); break;
-        case LBFE_FP32: go(std::integral_constant<int, LBFE_FP32>{}); break;
-        case LBFE_FP16_DEV: go(std::integral_constant<int, LBFE_FP16_DEV>{}); break;
-        default: go(std::integral_constant<int, LBFE_FP16_DEV_F0FP32>{}); break;
-    }
+    if (prec == LBFE_FP64)
+        go(double{});
+    else
+        go(float{});
     return hipGetLastError();
 }
 

@@ -1,9 +1,10 @@
-"""The block form of the stencil chain (grids below 2^20 fluid nodes) against
-the marching form, bit for bit: both sum every stencil in the same order, so
-the states after a few steps and the fields must be equal.  The sizes sit at
-the edges of the 16 x 8 blocks and their halos: one node, extents below the
-halo, one more and one less than a block, one and two fluid planes between
-walls, a ragged last block in every direction."""
+"""The block form of the stencil chain (grids below 2^19 fluid nodes) against
+the marching forms (periodic, between walls), bit for bit: all sum every
+stencil in the same order, so the states after a few steps and the fields must
+be equal.  The sizes sit at the edges of the 16 x 8 blocks, the 64 x 16 tiles
+and their halos: one node, extents below the halo, one more and one less than
+a block or tile, one and two fluid planes between walls, chunks of one plane
+and longer than the grid, a ragged last block in every direction."""
 import numpy as np
 import pytest
 import torch
@@ -14,8 +15,9 @@ from oracle import eos
 pytestmark = pytest.mark.gpu
 
 OM = [1.0, 1.0, 1.0, 0.5] + [1.0] * 7
-MARCH = 64  # a chunk length that only the marching form has
-SHAPES = [(1, 1, 1), (2, 3, 1), (5, 2, 3), (4, 8, 16), (5, 9, 17), (9, 7, 15), (3, 17, 33), (6, 40, 31)]
+MARCH = (64, 3, 5)  # chunk lengths that only the marching forms have
+SHAPES = [(1, 1, 1), (2, 3, 1), (5, 2, 3), (4, 8, 16), (5, 9, 17), (9, 7, 15), (3, 17, 33), (6, 40, 31),
+          (7, 16, 64), (4, 17, 65), (11, 15, 63), (8, 33, 130)]
 
 
 @pytest.mark.parametrize("walls", [False, True])
@@ -33,7 +35,7 @@ def test_block_chain_equals_the_march(walls, precision):
         rho0 = torch.tensor(droplet_rho((nz, ny, nx), T, walls=walls, radius=max(2.0, min(ny, nx) / 3.0)))
         g = np.random.Generator(np.random.PCG64(4))
         u0 = torch.tensor(0.02 * g.uniform(-1, 1, (3, nz, ny, nx)))
-        sims = [make_sim(chain_chunk=c, **kw) for c in (MARCH, 0, 1, 2, 4)]
+        sims = [make_sim(chain_chunk=c, **kw) for c in (*MARCH, 0, 1, 2, 4)]
         for s in sims:
             s.init_density(rho0, u0)
             s.step(3)
