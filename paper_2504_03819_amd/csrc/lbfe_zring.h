@@ -1,5 +1,5 @@
-// z-marching LDS ring for 27-point stencils over a few scalar fields: the
-// adjoint's transposed stencils and the solid-mask path's FP64 Q stencil.
+// z-marching LDS ring for 27-point stencils over a few scalar fields, summed
+// point by point: the solid-mask path's stencils of the FP32 and FP16 forms.
 #pragma once
 
 #include "lbfe_internal.h"
