@@ -443,6 +443,14 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
     // Planes per workgroup of the stencil chain: chosen per grid unless given.
     k.chain_cz = q.chain_chunk;
     q.chain_chunk = k.chain_cz = chain_chunk_for(k);
+    // mu0(rho): on large periodic grids the chain forms it from the density
+    // that it stages anyway, and no pass stores or reads the field (16 B per
+    // node and the halo's reads).  The logarithms lengthen the chain's busiest
+    // waves, which only the bandwidth-bound sizes hide (us per step, stored
+    // against formed: FP64 160^3 634 / 635, 200^3 1525 / 1470, 256^3 2472 /
+    // 2453; FP32 160^3 309 / 330, 200^3 825 / 832, 256^3 1429 / 1408; FP16
+    // 200^3 563 / 568, 256^3 940 / 885).
+    k.mu0_in_chain = !k.walls && !k.masked && k.N >= (q.precision == LBFE_FP64 ? 6u << 20 : 12u << 20);
     // Step path: the fused collide-stream-moments kernel reads the
     // populations once per step; it has no solid mask, and addresses one
     // z-plane of the lattice with 32-bit offsets.  Measured on

@@ -502,9 +502,10 @@ __device__ inline void div_rows(const real *gx, const real *gy, const real *gz, 
 // descriptor.  Bound by the halo and fill traffic (us, against the march with
 // three barriers and one point per thread): 128^3 FP64 57 -> 47, FP32 42 ->
 // 34; 192x192x96 83 -> 68, 62 -> 47; 512^3 2920 -> 2720-2870, 1955 -> 1743;
-// 256^3 388 -> 418, 270 -> 246-275.
+// 256^3 388 -> 418, 270 -> 246-275.  MU0: mu0(rho) is formed here instead of
+// read (kp.mu0_in_chain).
 // ---------------------------------------------------------------------------
-template <class real>
+template <class real, bool MU0>
 __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__restrict__ rho, const double *__restrict__ mu0,
                                                const void *jq, double *__restrict__ mu, void *Fq, void *Qq, int cz) {
     constexpr int HM = 2, HR = 3;  // halos of the mu and rho regions
@@ -710,7 +711,7 @@ __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__rest
             }
             gn = next(gn);
             issue_rho(gn, true);
-            issue_mu0(g2, true);
+            if (!MU0) issue_mu0(g2, true);
             __syncthreads();
             smooth_rows<WR, RB>(sr[0], cr, P0, rc);
             smooth_rows<WR, RB>(sr[1], cr, P1, rc);
@@ -732,7 +733,7 @@ __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__rest
 #pragma unroll
                 for (int i = 0; i < RB; ++i) {
                     const double s27 = A1 * P0[i] + A0 * P1[i] + A1 * P2[i];
-                    v[i] = m0[i] - kp.kappa * 6.0 * (s27 - rc[i]);
+                    v[i] = (MU0 ? mu_bulk(kp, rc[i]) : m0[i]) - kp.kappa * 6.0 * (s27 - rc[i]);
                     P0[i] = P1[i];
                     P1[i] = P2[i];
                     rc[i] = mid[i];
@@ -743,7 +744,7 @@ __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__rest
             const bool out = p >= zs && p < ze;
             const __amdgpu_buffer_rsrc_t rmu = plane_rsrc(mu + pbase(g2), pbytes8);
             g2 = next(g2);
-            issue_mu0(g2, p + 1 <= ze + 1);
+            if (!MU0) issue_mu0(g2, p + 1 <= ze + 1);
 #pragma unroll
             for (int i = 0; i < RB; ++i) bstore(v[i], rmu, out && ((own >> i) & 1u) ? off[i] : kOOB);
             s0 = s0 == 4 ? 0 : s0 + 1;
@@ -1038,8 +1039,10 @@ hipError_t launch_chain(hipStream_t s, int prec, const KP &kp, const Bufs &b) {
         using R = decltype(real);
         if (kp.walls)
             k_chain<R><<<grid, CB, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
+        else if (kp.mu0_in_chain)
+            k_chain_march<R, true><<<grid, NTC, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
         else
-            k_chain_march<R><<<grid, NTC, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
+            k_chain_march<R, false><<<grid, NTC, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
     };
     if (prec == LBFE_FP64)
         go(double{});

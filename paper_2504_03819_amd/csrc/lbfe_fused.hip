@@ -109,7 +109,7 @@ __global__ __launch_bounds__(NT) void k_fused(KP kp, const void *fin_q, void *fo
         const unsigned o8 = ok ? vn8 : kOOB, orr = ok ? vnr : kOOB;
         const double r = A.r + Lm;
         bst(r, rsrc(rho + pb, b8), o8, 0);
-        bst(mu_bulk(kp, r), rsrc(mu0 + pb, b8), o8, 0);
+        if (!kp.mu0_in_chain) bst(mu_bulk(kp, r), rsrc(mu0 + pb, b8), o8, 0);
         bst((real)A.jx, rsrc(J + pb, br), orr, 0);
         bst((real)A.jy, rsrc(J + N + pb, br), orr, 0);
         bst((real)(A.lp - Lm), rsrc(J + 2 * N + pb, br), orr, 0);

@@ -35,6 +35,7 @@ struct KP {
     int moving;                // some wall velocity is nonzero
     int masked;                // solid voxel mask (Bufs::nbr) instead of planes
     int chain_cz;              // planes per stencil-chain workgroup
+    int mu0_in_chain;          // the chain forms mu0(rho) itself (nothing stores or reads Bufs::mu0)
 };
 
 // Device pointers of one context (all inside the caller's workspace).
@@ -43,7 +44,7 @@ struct Bufs {
     double *rho;         // [N] density (solid planes: Eqs. (37)-(38))
     void *j;             // [3][N] sum_i f_i c_i, compute precision
     double *mu;          // [N] chemical potential (solid: Eq. (36))
-    double *mu0;         // [N] bulk part mu0(rho) of mu at fluid nodes
+    double *mu0;         // [N] bulk part mu0(rho) of mu at fluid nodes (unless kp.mu0_in_chain)
     void *F;             // [3][N] force, compute precision
     void *Q;             // [3][N] Q200, Q020, Q002 of Eq. (27), compute precision, 0 at solid
     unsigned *nbr;       // [N] with a solid mask: bit i set when x + c_i is solid

@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kBlock) void k_moments(KP kp, const void *fq, doubl
     real jx, jy, jz;
     moments(v, r, jx, jy, jz);
     rho[n] = r;
-    mu0[n] = mu_bulk(kp, r);
+    if (!kp.mu0_in_chain) mu0[n] = mu_bulk(kp, r);
     real *j = (real *)jq;
     j[n] = jx;
     j[kp.N + n] = jy;

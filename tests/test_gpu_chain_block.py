@@ -45,3 +45,28 @@ def test_block_chain_equals_the_march(walls, precision):
             f = s.fields()
             for name in ("rho", "u", "mu", "F"):
                 assert torch.equal(f[name], fr[name]), (shape, s.params.chain_chunk, name)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16dev_f0fp32"])
+def test_large_periodic_grid_steps_like_its_small_copy(precision):
+    """From 6 (FP64) or 12 (narrow forms) x 2^20 nodes a periodic chain forms
+    mu0(rho) itself: a state repeated to 17.8e6 nodes must step as the small
+    box does (stored mu0), node by node the same bits."""
+    shape, reps = (13, 27, 66), (6, 8, 16)
+    T = eos.temperature(0.85)
+    rho0 = torch.tensor(droplet_rho(shape, T, radius=4.0), device="cuda:0")
+    g = np.random.Generator(np.random.PCG64(6))
+    u0 = torch.tensor(0.02 * g.uniform(-1, 1, (3,) + shape), device="cuda:0")
+    out = []
+    for r in ((1, 1, 1), reps):
+        nz, ny, nx = (a * b for a, b in zip(shape, r))
+        sim = make_sim(nx=nx, ny=ny, nz=nz, T=T, precision=precision)
+        sim.init_density(rho0.repeat(r), u0.repeat((1,) + r))
+        sim.step(4)
+        mu = sim.field(2)
+        out.append((sim.populations(), mu))
+        sim.close()
+    (fs, ms), (fb, mb) = out
+    assert torch.equal(ms.repeat(reps), mb)
+    for i in range(27):
+        assert torch.equal(fs[i].repeat(reps), fb[i]), i
