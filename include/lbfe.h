@@ -208,10 +208,11 @@ int lbfe_init_density(lbfe_ctx *ctx, const double *rho0_dev, const double *u0_de
  * bounce-back.  Checks the divergence flag every check_every steps and at
  * the end (a synchronisation): E_DIVERGED, with the step in lbfe_last_error.
  * Each step runs as params.step_path says: a moments pass, the stencil
- * chain and a collide-stream pass (LBFE_PATH_TWO_PASS), or the stencil
- * chain and a collide-stream kernel that also forms the next step's density
- * and momentum (LBFE_PATH_FUSED, no moments pass), or through the moment
- * state (LBFE_PATH_STATE); all give bitwise identical states. */
+ * chain and a collide-stream pass (LBFE_PATH_TWO_PASS; on small grids chain
+ * and collide-stream are one kernel), or the stencil chain and a
+ * collide-stream kernel that also forms the next step's density and momentum
+ * (LBFE_PATH_FUSED, no moments pass), or through the moment state
+ * (LBFE_PATH_STATE); all give bitwise identical states. */
 int lbfe_step(lbfe_ctx *ctx, int64_t nsteps);
 
 /* Timing variant of lbfe_step for benchmarks: the same launches, with HIP
@@ -219,11 +220,12 @@ int lbfe_step(lbfe_ctx *ctx, int64_t nsteps);
  * kernel_ms[k] receives the summed milliseconds of class k over the nsteps
  * steps: 0 moments pass (with the wall density after it; on the fused path
  * only after the state was set from outside), 1 stencil chain (mu, force,
- * Q), 2 collide-stream (fused path: with the next step's moments), 3 wall
- * density after the step (fused path, walls only).  On the state path:
- * 0 the moments passes (with the populations at the end and the wall
- * density), 1 the chains, 2 the collide passes (the first from the
- * populations), 3 zero.  Synchronises after every step (host array). */
+ * Q; zero where it runs inside the collide kernel), 2 collide-stream (fused
+ * path: with the next step's moments), 3 wall density after the step (fused
+ * path, walls only).  On the state path: 0 the moments passes (with the
+ * populations at the end and the wall density), 1 the chains, 2 the collide
+ * passes (the first from the populations), 3 zero.  Synchronises after every
+ * step (host array). */
 int lbfe_step_timed(lbfe_ctx *ctx, int64_t nsteps, double kernel_ms[4]);
 
 /* Number of steps taken since lbfe_init_density / lbfe_set_state. */

@@ -442,6 +442,7 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
     k.xcd_remap = q.tile_order == LBFE_ORDER_XCD;
     // Planes per workgroup of the stencil chain: chosen per grid unless given.
     k.chain_cz = q.chain_chunk;
+    k.step_block = step_block_chunk(k, q.precision);
     q.chain_chunk = k.chain_cz = chain_chunk_for(k);
     // mu0(rho): on large periodic grids the chain forms it from the density
     // that it stages anyway, and no pass stores or reads the field (16 B per
@@ -564,7 +565,7 @@ int lbfe_step(lbfe_ctx *c, int64_t nsteps) {
     if (nsteps < 0) return fail(c, LBFE_E_INVAL, "nsteps < 0");
     if (c->state) return step_state(c, nsteps, nullptr);
     for (int64_t s = 0; s < nsteps; ++s) {
-        hipError_t e = launch_step(c->stream, c->p.precision, c->kp, c->b, c->cur, c->fused, !c->aux_ok, nullptr);
+        hipError_t e = launch_step(c->stream, c->p.precision, c->kp, c->b, c->cur, c->fused, !c->aux_ok, false, nullptr);
         if (e != hipSuccess) return hip_fail(c, e, "step");
         c->cur ^= 1;
         c->step++;
@@ -600,7 +601,7 @@ int lbfe_step_timed(lbfe_ctx *c, int64_t nsteps, double kernel_ms[4]) {
     }
     int rc = LBFE_OK;
     for (int64_t s = 0; s < nsteps && rc == LBFE_OK; ++s) {
-        hipError_t e = launch_step(c->stream, c->p.precision, c->kp, c->b, c->cur, c->fused, !c->aux_ok, ev);
+        hipError_t e = launch_step(c->stream, c->p.precision, c->kp, c->b, c->cur, c->fused, !c->aux_ok, false, ev);
         if (e == hipSuccess) e = hipEventSynchronize(ev[4]);
         if (e != hipSuccess) {
             rc = hip_fail(c, e, "step_timed");
@@ -800,7 +801,7 @@ int lbfe_step_aux(lbfe_ctx *c, void *aux) {
     int r = need_init(c);
     if (r) return r;
     if (!aux || ((uintptr_t)aux & 255u)) return fail(c, LBFE_E_INVAL, "aux record null or not 256-byte aligned");
-    hipError_t e = launch_step(c->stream, c->p.precision, c->kp, with_aux(c, aux), c->cur, false, true, nullptr);
+    hipError_t e = launch_step(c->stream, c->p.precision, c->kp, with_aux(c, aux), c->cur, false, true, true, nullptr);
     if (e != hipSuccess) return hip_fail(c, e, "step_aux");
     c->cur ^= 1;
     c->step++;

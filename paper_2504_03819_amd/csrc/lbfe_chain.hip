@@ -765,10 +765,17 @@ __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__rest
 // march is set by latency: at 32^3 in FP64 the march takes 25.6 us (seven
 // iterations of 3.7 us, half of its 64-wide tile empty), this kernel 6 us.
 // ---------------------------------------------------------------------------
-template <class real, bool WALLS, int TX, int TY, int CZ, int NT>
+// With a storage form P the workgroup then collides its own nodes and
+// push-streams them (k_collide's node, same code): F, mu and Q stay in LDS and
+// registers, and the step is two launches instead of three.
+// ---------------------------------------------------------------------------
+constexpr int kFields = -1;  // P: mu, F and Q to memory, no collision
+template <int P, class real, bool WALLS, int TX, int TY, int CZ, int NT>
 __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restrict__ rho,
                                                     const double *__restrict__ mu0, const void *jq,
-                                                    double *__restrict__ mu, void *Fq, void *Qq) {
+                                                    double *__restrict__ mu, void *Fq, void *Qq, const void *fin_q,
+                                                    void *fout_q) {
+    constexpr bool STEP = P != kFields;
     // mu one node wider next to walls: Eq. (36) averages it over x +- 1, y +- 1
     constexpr int HM = WALLS ? 3 : 2, HR = HM + 1;
     constexpr int WR = TX + 2 * HR, NR = WR * (TY + 2 * HR), ZR = CZ + 6;  // rho region
@@ -779,6 +786,7 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
     __shared__ double sr[ZR][NR];
     __shared__ double sm[ZM][NM];
     __shared__ real sp[ZP][3][NP];
+    __shared__ real sf[STEP ? CZ : 1][3][TX * TY];  // F of the owned nodes
 
     const int ntx = (kp.nx + TX - 1) / TX;
     const unsigned ntiles = gridDim.x, nb = gridDim.x * gridDim.y;
@@ -813,6 +821,28 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
             g = g + 1 == kp.nz ? 0 : g + 1;
         }
     }
+
+    // the node of this thread's q-th collision (owned column cc, plane zs + cz)
+    constexpr int NN = TX * TY * CZ, RN = (NN + NT - 1) / NT;
+    auto col_of = [&](int q, int &cc, int &cz) {
+        const int i = tid + q * NT;
+        cc = i % (TX * TY);
+        cz = i / (TX * TY);
+        return i < NN && x0 + cc % TX < kp.nx && y0 + cc / TX < kp.ny && zs + cz < ze;
+    };
+    // its populations (the first node's at once, with the block's other loads)
+    real f[STEP ? 27 : 1];
+    auto load_f = [&](int q) {
+        if constexpr (STEP) {
+            int cc, cz;
+            const Pops<P> fin(fin_q, kp);
+            if (col_of(q, cc, cz)) {
+                const unsigned row = (unsigned)(zs + cz) * (unsigned)kp.ny + (unsigned)(y0 + cc / TX);
+#pragma unroll
+                for (int i = 0; i < 27; ++i) f[i] = fin.ld(i, row, (unsigned)(x0 + cc % TX));
+            }
+        }
+    };
 
     // every load of the block, before the first barrier
     double m0[MM][ZM];
@@ -849,6 +879,7 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
             for (int m = 0; m < MP; ++m)
 #pragma unroll
                 for (int c = 0; c < 3; ++c) pj[m][z][c] = j[c * N + pb[z + 2] + op[m]];
+        load_f(0);
 #pragma unroll
         for (int z = 0; z < ZR; ++z)
 #pragma unroll
@@ -874,7 +905,9 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
             const double v = m0[m][z] - kp.kappa * 6.0 * (s27 - r0);
             if (fluid(p)) {
                 sm[z][r] = v;
-                if (own && p >= zs && p < ze) mu[pb[z + 1] + om[m]] = v;
+                // (with moving walls mu beside them: k_wall_move applies the wall term)
+                if (own && p >= zs && p < ze && (!STEP || (WALLS && kp.moving && (p == 1 || p == kp.nz - 2))))
+                    mu[pb[z + 1] + om[m]] = v;
             }
             P0 = P1;
             P1 = P2;
@@ -891,7 +924,7 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
                 if (r >= NM || a < 1 || a > WM - 2 || b < 1 || b > TY + 2 * HM - 2) continue;
                 const double v = smooth2<WM>(sm[zf], r);
                 sm[zw][r] = v;
-                if (write_out && a >= HM && b >= HM && a < TX + HM && b < TY + HM && x0 + a - HM < kp.nx &&
+                if (!STEP && write_out && a >= HM && b >= HM && a < TX + HM && b < TY + HM && x0 + a - HM < kp.nx &&
                     y0 + b - HM < kp.ny)
                     mu[(size_t)ps * kp.plane + om[m]] = v;
             }
@@ -921,10 +954,17 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
                 force_phi(Aa, Ab, Ac, Ba, Bb, Bc, Ca, Cc, sr[z + 2][cr], sm[z + 1][c], pj[m][z], Fx, Fy, Fz, ph);
                 for (int k = 0; k < 3; ++k) sp[z][k][r] = ph[k];
                 if (own && p >= zs && p < ze) {
-                    const size_t n = pb[z + 2] + op[m];
-                    F[n] = Fx;
-                    F[N + n] = Fy;
-                    F[2 * N + n] = Fz;
+                    if constexpr (STEP) {
+                        const int cc = (b - 1) * TX + a - 1;
+                        sf[p - zs][0][cc] = Fx;
+                        sf[p - zs][1][cc] = Fy;
+                        sf[p - zs][2][cc] = Fz;
+                    } else {
+                        const size_t n = pb[z + 2] + op[m];
+                        F[n] = Fx;
+                        F[N + n] = Fy;
+                        F[2 * N + n] = Fz;
+                    }
                 }
             } else {
                 for (int k = 0; k < 3; ++k) sp[z][k][r] = (real)0;
@@ -935,6 +975,37 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
     }
     __syncthreads();
 
+    if constexpr (STEP) {
+        // Q, collision and push-stream of the owned nodes
+        const Pops<P> fout(fout_q, kp);
+#pragma unroll
+        for (int q = 0; q < RN; ++q) {
+            if (q) load_f(q);
+            int cc, cz;
+            if (!col_of(q, cc, cz)) continue;
+            const int a = cc % TX, b = cc / TX, c = (b + 1) * WP + a + 1;
+            real X[3], Y[3], Z[3], qx, qy, qz;
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                plane_div<WP>(sp[cz + d][0], sp[cz + d][1], sp[cz + d][2], c, X[d], Y[d], Z[d]);
+            q_of(X[0], X[1], X[2], Y[0], Y[1], Y[2], Z[0], Z[2], qx, qy, qz);
+            collide_node(kp, f, sm[cz + 2][(b + HM) * WM + a + HM], sf[cz][0][cc], sf[cz][1][cc], sf[cz][2][cc], qx, qy,
+                         qz);
+            const int z = zs + cz;
+            const Nb nb(kp, x0 + a, y0 + b, z);
+            const unsigned row = nb.row(0, 0), x = (unsigned)(x0 + a);
+            const bool wall_lo = WALLS && z == 1, wall_hi = WALLS && z == kp.nz - 2;
+#pragma unroll
+            for (int i = 0; i < 27; ++i) {
+                const int c3 = czi(i);
+                if ((c3 < 0 && wall_lo) || (c3 > 0 && wall_hi))
+                    fout.st(26 - i, row, x, f[i]);
+                else
+                    fout.st(i, nb.row(cyi(i), c3), nb.xo(cxi(i)), f[i]);
+            }
+        }
+        return;
+    }
     // Q of the owned columns
     const int a = tid % TX, b = tid / TX;
     if (tid < TX * TY && x0 + a < kp.nx && y0 + b < kp.ny) {
@@ -994,32 +1065,76 @@ constexpr unsigned kBlockNodes = 1u << 19;
 constexpr int BX = 16, BY = 8;  // 32x8, 32x4 and 16x4 blocks: 0-12 % slower per step
 static bool chain_block_grid(const KP &kp) { return kp.nfluid < kBlockNodes; }
 
+// the fewest planes that leave one workgroup per CU, else 4 (32^3: 1, 2, 4
+// planes take 16.9, 18.2, 22.1 us per FP64 step; 64^3: 50.8, 44.0, 40.4)
+static int block_chunk(const KP &kp) {
+    const size_t tiles = (size_t)((kp.nx + BX - 1) / BX) * ((kp.ny + BY - 1) / BY);
+    const size_t nzf = kp.z1 - kp.z0;
+    return tiles * nzf <= kCUs ? 1 : (tiles * ((nzf + 1) / 2) <= kCUs ? 2 : 4);
+}
+
 int chain_chunk_for(const KP &kp) {
     if (kp.chain_cz > 0) return kp.chain_cz;
-    if (chain_block_grid(kp)) {
-        // the fewest planes that leave one workgroup per CU, else 4 (32^3: 1,
-        // 2, 4 planes take 18.8, 19.6, 21.2 us per FP64 step; 64^3: 54, 51, 48)
-        const size_t tiles = (size_t)((kp.nx + BX - 1) / BX) * ((kp.ny + BY - 1) / BY);
-        const size_t nzf = kp.z1 - kp.z0;
-        return tiles * nzf <= kCUs ? 1 : (tiles * ((nzf + 1) / 2) <= kCUs ? 2 : 4);
-    }
+    if (chain_block_grid(kp)) return block_chunk(kp);
     const unsigned ntx = (kp.nx + TX - 1) / TX, nty = (kp.ny + TY - 1) / TY;
     return chain_chunk(kp, ntx * nty);
 }
 
-template <class real, bool WALLS, int CZ> static void go_block(hipStream_t s, const KP &kp, const Bufs &b) {
+template <int P, class real, bool WALLS, int CZ>
+static void go_block(hipStream_t s, const KP &kp, const Bufs &b, const void *fin, void *fout) {
     // 256 threads hold the 240 mu columns; next to walls, with 308, 512 are
     // faster where a block has work for them (us per step at 96^3 FP64 145
-    // against 148 with 256 and 158 with 320; at 32^3 22.6 against 21.9)
-    constexpr int NT = WALLS && CZ == 4 ? 512 : 256;
+    // against 148 with 256 and 158 with 320; at 32^3 22.6 against 21.9).
+    // Blocks that also collide: 512 for 4 planes of the narrow forms (80^3
+    // FP16 47.8 against 49.6, walls 52.8 against 56.7), but in FP64 the
+    // populations of 512 nodes leave one block per CU (80^3 85.9 against 72.8)
+    constexpr int NT = CZ == 4 && (WALLS || (P != kFields && sizeof(real) == 4)) ? 512 : 256;
     const dim3 g((kp.nx + BX - 1) / BX * ((kp.ny + BY - 1) / BY), (kp.z1 - kp.z0 + CZ - 1) / CZ);
-    k_chain_block<real, WALLS, BX, BY, CZ, NT><<<g, NT, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q);
+    k_chain_block<P, real, WALLS, BX, BY, CZ, NT>
+        <<<g, NT, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, fin, fout);
 }
-template <class real, bool WALLS> static void go_block(hipStream_t s, const KP &kp, const Bufs &b, int cz) {
-    switch (cz) {
-        case 1: go_block<real, WALLS, 1>(s, kp, b); break;
-        case 2: go_block<real, WALLS, 2>(s, kp, b); break;
-        default: go_block<real, WALLS, 4>(s, kp, b); break;
+template <int P, class real>
+static hipError_t go_block(hipStream_t s, const KP &kp, const Bufs &b, int cz, const void *fin, void *fout) {
+    auto go = [&](auto walls) {
+        constexpr bool W = decltype(walls)::value;
+        switch (cz) {
+            case 1: go_block<P, real, W, 1>(s, kp, b, fin, fout); break;
+            case 2: go_block<P, real, W, 2>(s, kp, b, fin, fout); break;
+            default: go_block<P, real, W, 4>(s, kp, b, fin, fout); break;
+        }
+    };
+    if (kp.walls)
+        go(std::true_type{});
+    else
+        go(std::false_type{});
+    return hipGetLastError();
+}
+
+// Planes per block of the step that runs chain and collide-stream in one
+// launch (0: two).  It saves a launch and the 7 fields between the two, and
+// pays with latency that few resident blocks hide: FP64 gains to 1.5e6 nodes
+// (us per step, two launches / one: 32^3 19.6 / 16.7, 64^3 49.4 / 40.4, 101 x
+// 67 x 53 77.6 / 70.1, 96^3 133 / 123, 112^3 203 / 192, 128^3 293 / 302), FP32
+// to 2^19 (32^3 16.6 / 14.0, 64^3 33.6 / 30.8, 80^3 59.4 / 53.9, 96^3 80.5 /
+// 84.2), FP16 populations to 5 x 2^16 (32^3 16.2 / 13.1, 64^3 34.2 / 31.0,
+// 101 x 67 x 53 between walls 49.0 / 49.8).  Between walls FP64 blocks of 4
+// planes take the LDS of one block per CU: 2 planes (80^3 84.0 against 91.8;
+// two launches 90.5).
+int step_block_chunk(const KP &kp, int prec) {
+    const size_t limit = prec == LBFE_FP64 ? 3u << 19 : (prec == LBFE_FP32 ? 1u << 19 : 5u << 16);
+    if (kp.masked || kp.nfluid >= limit) return 0;
+    if (kp.chain_cz > 0) return kp.chain_cz == 1 || kp.chain_cz == 2 || kp.chain_cz == 4 ? kp.chain_cz : 0;
+    return min(block_chunk(kp), kp.walls && prec == LBFE_FP64 ? 2 : 4);
+}
+
+hipError_t launch_step_block(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur) {
+    const void *fin = b.f[cur];
+    void *fout = b.f[1 - cur];
+    switch (prec) {
+        case LBFE_FP64: return go_block<LBFE_FP64, double>(s, kp, b, kp.step_block, fin, fout);
+        case LBFE_FP32: return go_block<LBFE_FP32, float>(s, kp, b, kp.step_block, fin, fout);
+        case LBFE_FP16_DEV: return go_block<LBFE_FP16_DEV, float>(s, kp, b, kp.step_block, fin, fout);
+        default: return go_block<LBFE_FP16_DEV_F0FP32, float>(s, kp, b, kp.step_block, fin, fout);
     }
 }
 
@@ -1027,13 +1142,9 @@ hipError_t launch_chain(hipStream_t s, int prec, const KP &kp, const Bufs &b) {
     const unsigned ntx = (kp.nx + TX - 1) / TX, nty = (kp.ny + TY - 1) / TY;
     const int cz = chain_chunk_for(kp);
     const int nzf = kp.z1 - kp.z0;
-    if (chain_block_grid(kp) && (cz == 1 || cz == 2 || cz == 4)) {
-        if (prec == LBFE_FP64)
-            kp.walls ? go_block<double, true>(s, kp, b, cz) : go_block<double, false>(s, kp, b, cz);
-        else
-            kp.walls ? go_block<float, true>(s, kp, b, cz) : go_block<float, false>(s, kp, b, cz);
-        return hipGetLastError();
-    }
+    if (chain_block_grid(kp) && (cz == 1 || cz == 2 || cz == 4))
+        return prec == LBFE_FP64 ? go_block<kFields, double>(s, kp, b, cz, nullptr, nullptr)
+                                 : go_block<kFields, float>(s, kp, b, cz, nullptr, nullptr);
     const dim3 grid(ntx * nty, (nzf + cz - 1) / cz);
     auto go = [&](auto real) {
         using R = decltype(real);

@@ -35,6 +35,7 @@ struct KP {
     int moving;                // some wall velocity is nonzero
     int masked;                // solid voxel mask (Bufs::nbr) instead of planes
     int chain_cz;              // planes per stencil-chain workgroup
+    int step_block;            // planes per workgroup of chain + collide in one launch (0: two launches)
     int mu0_in_chain;          // the chain forms mu0(rho) itself (nothing stores or reads Bufs::mu0)
 };
 
@@ -66,8 +67,9 @@ hipError_t launch_aux(hipStream_t s, int prec, const KP &kp, const Bufs &b, int 
 // One step f[cur] -> f[1 - cur].  fused: chain + fused collide-stream-moments
 // (+ wall density), with a moments pass first if `refresh`; otherwise the
 // unfused moments, chain, collide-stream.  ev5: optional timing events.
+// keep: mu, F and Q of f[cur] are wanted in b (lbfe_step_aux).
 hipError_t launch_step(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur, bool fused, bool refresh,
-                       hipEvent_t *ev5);
+                       bool keep, hipEvent_t *ev5);
 // collide + stream + rho, j, mu0 of the streamed state (lbfe_fused.hip);
 // fused_plane_ok: one z-plane of the lattice fits its 32-bit plane offsets
 hipError_t launch_fused(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur);
@@ -100,6 +102,11 @@ hipError_t launch_state_collide(hipStream_t s, int prec, const KP &kp, const Buf
 // planes per workgroup, kp.chain_cz if set, else chosen for the grid
 hipError_t launch_chain(hipStream_t s, int prec, const KP &kp, const Bufs &b);
 int chain_chunk_for(const KP &kp);
+// chain + collide + stream of a small grid in one launch (mu, F, Q not
+// stored); step_block_chunk: its planes per workgroup, 0 where two launches
+// are faster (kp.chain_cz as the caller set it)
+int step_block_chunk(const KP &kp, int prec);
+hipError_t launch_step_block(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur);
 hipError_t launch_export(hipStream_t s, int prec, const KP &kp, const Bufs &b, int which, double *out);
 hipError_t launch_reduce(hipStream_t s, int prec, const KP &kp, const Bufs &b);
 // the same reduction with the block partials in `part` (the static scratch

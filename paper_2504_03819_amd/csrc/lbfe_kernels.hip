@@ -430,8 +430,9 @@ hipError_t aux_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur) {
 // Fused path: rho, j, mu0 of f[cur] are current unless `refresh`; the fused
 // kernel leaves them current for f[1 - cur].
 template <int P>
-hipError_t step_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool fused, bool refresh,
+hipError_t step_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool fused, bool refresh, bool keep,
                      hipEvent_t *ev) {
+    const bool block = kp.step_block && !fused && !keep;  // chain and collide in one launch
     const unsigned gf = nblocks(kp.nfluid), gw = nblocks(2 * (size_t)kp.plane);
     auto mark = [&](int k) {
         if (ev) (void)hipEventRecord(ev[k], s);
@@ -442,10 +443,14 @@ hipError_t step_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool f
         if (kp.walls) k_wall_rho<<<gw, kBlock, 0, s>>>(kp, b.rho);
     }
     mark(1);
-    hipError_t e = launch_chain(s, P, kp, b);
+    hipError_t e = block ? hipSuccess : launch_chain(s, P, kp, b);
     if (e != hipSuccess) return e;
     mark(2);
-    if (fused) {
+    if (block) {
+        e = launch_step_block(s, P, kp, b, cur);
+        if (e != hipSuccess) return e;
+        if (kp.moving) k_wall_move<P><<<gw, kBlock, 0, s>>>(kp, b.f[1 - cur], b.rho, b.mu);
+    } else if (fused) {
         if (kp.moving) k_wall_keep<<<nblocks(kp.plane), kBlock, 0, s>>>(kp, b.rho);
         e = launch_fused(s, P, kp, b, cur);
         if (e != hipSuccess) return e;
@@ -503,10 +508,10 @@ hipError_t launch_aux(hipStream_t s, int prec, const KP &kp, const Bufs &b, int 
 }
 
 hipError_t launch_step(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur, bool fused, bool refresh,
-                       hipEvent_t *ev5) {
+                       bool keep, hipEvent_t *ev5) {
     if (kp.masked) return launch_step_mask(s, prec, kp, b, cur, ev5);
     return dispatch(prec,
-                    [&](auto pc) { return step_impl<decltype(pc)::value>(s, kp, b, cur, fused, refresh, ev5); });
+                    [&](auto pc) { return step_impl<decltype(pc)::value>(s, kp, b, cur, fused, refresh, keep, ev5); });
 }
 
 // Moment-state launch groups (the kernels are in lbfe_moment.hip)

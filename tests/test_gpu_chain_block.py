@@ -1,7 +1,7 @@
-"""The block form of the stencil chain (grids below 2^19 fluid nodes) against
-the marching forms (periodic, between walls), bit for bit: all sum every
-stencil in the same order, so the states after a few steps and the fields must
-be equal.  The sizes sit at the edges of the 16 x 8 blocks, the 64 x 16 tiles
+"""The block form of the stencil chain (grids below 2^19 fluid nodes), alone and
+with the collision in the same launch, against the marching forms (periodic,
+between walls), bit for bit: all sum every stencil in the same order, so the
+states after a few steps and the fields must be equal.  The sizes sit at the edges of the 16 x 8 blocks, the 64 x 16 tiles
 and their halos: one node, extents below the halo, one more and one less than
 a block or tile, one and two fluid planes between walls, chunks of one plane
 and longer than the grid, a ragged last block in every direction."""
@@ -45,6 +45,26 @@ def test_block_chain_equals_the_march(walls, precision):
             f = s.fields()
             for name in ("rho", "u", "mu", "F"):
                 assert torch.equal(f[name], fr[name]), (shape, s.params.chain_chunk, name)
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16dev", "fp16dev_f0fp32"])
+@pytest.mark.parametrize("shape", [(3, 9, 17), (4, 8, 16), (6, 17, 33), (11, 7, 65)])
+def test_block_step_between_moving_walls(shape, precision):
+    """The moving-wall term reads the mu that the block kernel leaves beside
+    the walls; nz = 3 and 4 put both walls in one block."""
+    nz, ny, nx = shape
+    T = eos.temperature(0.8)
+    say(f"block step, moving walls: {shape} {precision}")
+    rho0 = torch.tensor(droplet_rho(shape, T, walls=True, radius=3.0))
+    out = []
+    for chunk in (64, 3, 0, 1, 2, 4):
+        s = make_sim(nx=nx, ny=ny, nz=nz, T=T, walls_z=1, wet_mode=1, wet_value=0.7, omega=OM, precision=precision,
+                     step_path=1, chain_chunk=chunk, wall_u=(-0.01, 0.004, 0.02, 0.0))
+        s.init_density(rho0)
+        s.step(4)
+        out.append(s.get_state())
+    for st in out[1:]:
+        assert torch.equal(st, out[0])
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32", "fp16dev_f0fp32"])
