@@ -122,12 +122,14 @@ template <> struct Pops<LBFE_FP16_DEV_F0FP32> {
 // Work mapping.  Workgroups are handed to the 8 XCDs round-robin; with
 // xcd_remap the tile index is permuted so that every XCD owns one
 // contiguous range of tiles (neighbouring rows share that XCD's L2).
+// A kernel that reads what the one before it wrote last takes its tiles in
+// descending order: the last-level cache (256 MB) still holds the end of it.
 // ---------------------------------------------------------------------------
-__device__ inline unsigned tile_id(const KP &kp) {
+__device__ inline unsigned tile_id(const KP &kp, bool descending = false) {
     const unsigned b = blockIdx.x, nb = gridDim.x;
-    if (!kp.xcd_remap) return b;
-    const unsigned q = nb >> 3, r = nb & 7u, k = b & 7u;
-    return k * q + (k < r ? k : r) + (b >> 3);
+    if (!kp.xcd_remap) return descending ? nb - 1 - b : b;
+    const unsigned q = nb >> 3, r = nb & 7u, k = b & 7u, i = b >> 3;
+    return k * q + (k < r ? k : r) + (descending ? q + (k < r ? 1 : 0) - 1 - i : i);
 }
 
 // Neighbour offsets of node (x, y, z) with periodic wrap: X, Y, Z give node

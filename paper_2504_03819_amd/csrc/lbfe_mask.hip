@@ -55,7 +55,8 @@ template <int P>
 __global__ __launch_bounds__(kBlock) void k_moments_m(KP kp, const unsigned *nbr, const void *fq, double *rho,
                                                       void *jq, int *flag) {
     using real = real_t<P>;
-    const unsigned n = tile_id(kp) * kBlock + threadIdx.x;
+    // (against the order of k_collide_m, as in k_moments)
+    const unsigned n = tile_id(kp, true) * kBlock + threadIdx.x;
     if (n >= kp.N) return;
     // the population loads do not wait for the neighbour word (a solid
     // node's slots hold zeros); only the stores depend on it
