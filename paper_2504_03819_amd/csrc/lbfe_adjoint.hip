@@ -293,7 +293,7 @@ template <int P> __global__ __launch_bounds__(kBlock) void k_adj_pack(KP kp, Buf
 // PEND: lam_in holds only the direct part of lambda(t+1); its last term is
 // added during the gather from the (rho_bar_total, j_bar) pack that the
 // previous adjoint step left (this kernel does not write it).
-// NT: lambda, F, Q and mu are read once and the node's own lambda row is
+// NT: f, lambda, F, Q and mu are read once and the node's own lambda row is
 // written once, so from 2^20 nodes, where the lattices exceed the caches, they
 // go non-temporal (192x192x96 in FP32: 342 -> 320 us); a small box keeps them
 // in the caches (48x40x32 in FP64: 17.2 us, 19.2 non-temporal).
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_collide(KP kp, Bufs b, const voi
     decompose(kp, n, x, y, z);
     const Nb nb(kp, x, y, z);
     const unsigned row = nb.row(0, 0);
-    const Pops<P> fin(ft, kp);
+    const Pops<P, NT> fin(ft, kp);
     const Lam<real> lin(const_cast<void *>(lam_in), kp), lout(lam_out, kp);
     // solid mask: bit i of the neighbour word marks a link that ends on a
     // solid node (bounce-back); a solid node holds no lambda

@@ -770,7 +770,7 @@ __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__rest
 // registers, and the step is two launches instead of three.
 // ---------------------------------------------------------------------------
 constexpr int kFields = -1;  // P: mu, F and Q to memory, no collision
-template <int P, class real, bool WALLS, int TX, int TY, int CZ, int NT>
+template <int P, class real, bool WALLS, int TX, int TY, int CZ, int NT, bool NTL>
 __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restrict__ rho,
                                                     const double *__restrict__ mu0, const void *jq,
                                                     double *__restrict__ mu, void *Fq, void *Qq, const void *fin_q,
@@ -835,7 +835,7 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
     auto load_f = [&](int q) {
         if constexpr (STEP) {
             int cc, cz;
-            const Pops<P> fin(fin_q, kp);
+            const Pops<P, NTL> fin(fin_q, kp);
             if (col_of(q, cc, cz)) {
                 const unsigned row = (unsigned)(zs + cz) * (unsigned)kp.ny + (unsigned)(y0 + cc / TX);
 #pragma unroll
@@ -1090,8 +1090,12 @@ static void go_block(hipStream_t s, const KP &kp, const Bufs &b, const void *fin
     // populations of 512 nodes leave one block per CU (80^3 85.9 against 72.8)
     constexpr int NT = CZ == 4 && (WALLS || (P != kFields && sizeof(real) == 4)) ? 512 : 256;
     const dim3 g((kp.nx + BX - 1) / BX * ((kp.ny + BY - 1) / BY), (kp.z1 - kp.z0 + CZ - 1) / CZ);
-    k_chain_block<P, real, WALLS, BX, BY, CZ, NT>
-        <<<g, NT, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, fin, fout);
+    if (P == kFields || kp.keep2)
+        k_chain_block<P, real, WALLS, BX, BY, CZ, NT, false>
+            <<<g, NT, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, fin, fout);
+    else if constexpr (P != kFields)
+        k_chain_block<P, real, WALLS, BX, BY, CZ, NT, true>
+            <<<g, NT, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, fin, fout);
 }
 template <int P, class real>
 static hipError_t go_block(hipStream_t s, const KP &kp, const Bufs &b, int cz, const void *fin, void *fout) {

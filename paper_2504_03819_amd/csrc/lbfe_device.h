@@ -29,7 +29,7 @@ __host__ __device__ constexpr int K(int a, int b, int g) { return 9 * a + 3 * b 
 template <int P> struct Pol { using real = float; };
 template <> struct Pol<LBFE_FP64> { using real = double; };
 
-template <int P> struct Pops;
+template <int P, bool NT = true> struct Pops;
 
 // Population storage is row-blocked: for every x-row (z, y) the 27
 // populations are stored one after another, each as nx contiguous values,
@@ -37,32 +37,33 @@ template <int P> struct Pops;
 // 64 x-consecutive threads touches one contiguous run per population, and
 // the 27 runs of a row share DRAM pages.
 //
-// Population loads are non-temporal: every kernel reads a population once
-// per pass, and a lattice of a few hundred MB would otherwise push the
-// reused data (aux fields, stencil halos, the freshly written lattice) out
-// of the last-level cache.  Stores stay ordinary (non-temporal stores of the
+// Population loads are non-temporal (NT) where the lattice exceeds the
+// last-level cache: every kernel reads a population once per pass, and a
+// lattice of a few hundred MB would otherwise push the reused data (aux fields,
+// stencil halos, the freshly written lattice) out of it.  Stores stay ordinary (non-temporal stores of the
 // shifted push-stream rows were measured slower).
 __device__ inline double ldnt(const double *p) { return __builtin_nontemporal_load(p); }
 __device__ inline float ldnt(const float *p) { return __builtin_nontemporal_load(p); }
 __device__ inline __half ldnt(const __half *p) {
     return __builtin_bit_cast(__half, __builtin_nontemporal_load((const unsigned short *)p));
 }
-template <> struct Pops<LBFE_FP64> {
+template <bool NT, class T> __device__ inline T ldp(const T *p) { return NT ? ldnt(p) : *p; }
+template <bool NT> struct Pops<LBFE_FP64, NT> {
     double *p;
     unsigned nx;
     __device__ Pops(const void *q, const KP &kp) : p((double *)q), nx((unsigned)kp.nx) {}
     __device__ size_t off(int i, unsigned row, unsigned x) const { return ((size_t)row * 27 + i) * nx + x; }
-    __device__ double ld(int i, unsigned row, unsigned x) const { return ldnt(p + off(i, row, x)); }
+    __device__ double ld(int i, unsigned row, unsigned x) const { return ldp<NT>(p + off(i, row, x)); }
     __device__ void st(int i, unsigned row, unsigned x, double v) const { p[off(i, row, x)] = v; }
     __device__ static double quant(int, double v) { return v; }  // value a store then load returns
 };
 
-template <> struct Pops<LBFE_FP32> {
+template <bool NT> struct Pops<LBFE_FP32, NT> {
     float *p;
     unsigned nx;
     __device__ Pops(const void *q, const KP &kp) : p((float *)q), nx((unsigned)kp.nx) {}
     __device__ size_t off(int i, unsigned row, unsigned x) const { return ((size_t)row * 27 + i) * nx + x; }
-    __device__ float ld(int i, unsigned row, unsigned x) const { return ldnt(p + off(i, row, x)); }
+    __device__ float ld(int i, unsigned row, unsigned x) const { return ldp<NT>(p + off(i, row, x)); }
     __device__ void st(int i, unsigned row, unsigned x, float v) const { p[off(i, row, x)] = v; }
     __device__ static float quant(int, float v) { return v; }
 };
@@ -85,19 +86,19 @@ __device__ inline __half enc16(int i, float f) {
     return __float2half_rn(t);
 }
 
-template <> struct Pops<LBFE_FP16_DEV> {
+template <bool NT> struct Pops<LBFE_FP16_DEV, NT> {
     __half *p;
     unsigned nx;
     __device__ Pops(const void *q, const KP &kp) : p((__half *)q), nx((unsigned)kp.nx) {}
     __device__ size_t off(int i, unsigned row, unsigned x) const { return ((size_t)row * 27 + i) * nx + x; }
-    __device__ float ld(int i, unsigned row, unsigned x) const { return dec16(i, ldnt(p + off(i, row, x))); }
+    __device__ float ld(int i, unsigned row, unsigned x) const { return dec16(i, ldp<NT>(p + off(i, row, x))); }
     __device__ void st(int i, unsigned row, unsigned x, float v) const { p[off(i, row, x)] = enc16(i, v); }
     __device__ static float quant(int i, float v) { return dec16(i, enc16(i, v)); }
 };
 
 // Rest population in float ([z][y][x] plane after the half rows), the 26
 // moving ones as half deviations, row-blocked 26 per row.
-template <> struct Pops<LBFE_FP16_DEV_F0FP32> {
+template <bool NT> struct Pops<LBFE_FP16_DEV_F0FP32, NT> {
     __half *p;
     float *p0;
     unsigned nx;
@@ -107,7 +108,7 @@ template <> struct Pops<LBFE_FP16_DEV_F0FP32> {
     __device__ static int slot(int i) { return i < kRest ? i : i - 1; }
     __device__ size_t off(int i, unsigned row, unsigned x) const { return ((size_t)row * 26 + slot(i)) * nx + x; }
     __device__ float ld(int i, unsigned row, unsigned x) const {
-        return i == kRest ? ldnt(p0 + (size_t)row * nx + x) : dec16(i, ldnt(p + off(i, row, x)));
+        return i == kRest ? ldp<NT>(p0 + (size_t)row * nx + x) : dec16(i, ldp<NT>(p + off(i, row, x)));
     }
     __device__ void st(int i, unsigned row, unsigned x, float v) const {
         if (i == kRest)

@@ -42,7 +42,7 @@ __global__ void k_fill(uint4 *p, size_t n16) {
 }
 
 // --------------------------------------------------------------------------
-template <int P>
+template <int P, bool NT>
 __global__ __launch_bounds__(kBlock) void k_moments(KP kp, const void *fq, double *rho, void *jq, double *mu0,
                                                     int *flag) {
     using real = real_t<P>;
@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kBlock) void k_moments(KP kp, const void *fq, doubl
     if (idx >= kp.nfluid) return;
     const unsigned n = (unsigned)kp.z0 * kp.plane + idx;
     const unsigned row = n / (unsigned)kp.nx, x = n - row * (unsigned)kp.nx;
-    const Pops<P> f(fq, kp);
+    const Pops<P, NT> f(fq, kp);
     real v[27];
 #pragma unroll
     for (int i = 0; i < 27; ++i) v[i] = f.ld(i, row, x);
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(kBlock) void k_mu(KP kp, const double *rho, double 
 
 // Fused collide + stream of one fluid node (push: f*_i(x) -> x + c_i, or
 // -> slot opp(i) of x when x + c_i is solid: halfway bounce-back).
-template <int P>
+template <int P, bool NT>
 __global__ __launch_bounds__(kBlock) void k_collide(KP kp, const void *fin_q, void *fout_q, const double *mu,
                                                     const void *Fq, const void *Qq) {
     using real = real_t<P>;
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kBlock) void k_collide(KP kp, const void *fin_q, vo
     int x, y, z;
     decompose(kp, n, x, y, z);
     const Nb nb(kp, x, y, z);
-    const Pops<P> fin(fin_q, kp);
+    const Pops<P, NT> fin(fin_q, kp);
     const Pops<P> fout(fout_q, kp);
     const unsigned row = nb.row(0, 0);
 
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(kBlock) void k_collide(KP kp, const void *fin_q, vo
     const real *F = (const real *)Fq, *Qa = (const real *)Qq;
     // the aux fields are read once; non-temporal in the FP64 and FP32 forms
     // (measured neutral to slightly slower in the FP16 forms)
-    constexpr bool nt = P == LBFE_FP64 || P == LBFE_FP32;
+    constexpr bool nt = NT && (P == LBFE_FP64 || P == LBFE_FP32);
     auto ld = [&](const auto *p) { return nt ? ldnt(p) : *p; };
     collide_node(kp, f, ld(mu + n), ld(F + n), ld(F + kp.N + n), ld(F + 2 * (size_t)kp.N + n), ld(Qa + n),
                  ld(Qa + kp.N + n), ld(Qa + 2 * (size_t)kp.N + n));
@@ -420,10 +420,19 @@ __global__ __launch_bounds__(kBlock) void k_set_pop(KP kp, void *fq, const unsig
 // One step's launches.  With `ev` non-null, HIP events ev[0..4] bracket the
 // four kernel classes in the order: moments (with the wall density that
 // follows them), chain, collide-stream, wall density after the step.
+// (without non-temporal loads while the lattice stays in the last-level cache)
+template <int P> void moments_pass(hipStream_t s, const KP &kp, const Bufs &b, int cur) {
+    const unsigned g = nblocks(kp.nfluid);
+    if (kp.keep1)
+        k_moments<P, false><<<g, kBlock, 0, s>>>(kp, b.f[cur], b.rho, b.j, b.mu0, b.flag);
+    else
+        k_moments<P, true><<<g, kBlock, 0, s>>>(kp, b.f[cur], b.rho, b.j, b.mu0, b.flag);
+}
+
 template <int P>
 hipError_t aux_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur) {
     const unsigned gf = nblocks(kp.nfluid), gw = nblocks(2 * (size_t)kp.plane);
-    k_moments<P><<<gf, kBlock, 0, s>>>(kp, b.f[cur], b.rho, b.j, b.mu0, b.flag);
+    moments_pass<P>(s, kp, b, cur);
     if (kp.walls) k_wall_rho<<<gw, kBlock, 0, s>>>(kp, b.rho);
     hipError_t e = launch_chain(s, P, kp, b);
     if (e != hipSuccess) return e;
@@ -442,7 +451,7 @@ hipError_t step_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool f
     };
     mark(0);
     if (refresh || !fused) {
-        k_moments<P><<<gf, kBlock, 0, s>>>(kp, b.f[cur], b.rho, b.j, b.mu0, b.flag);
+        moments_pass<P>(s, kp, b, cur);
         if (kp.walls) k_wall_rho<<<gw, kBlock, 0, s>>>(kp, b.rho);
     }
     mark(1);
@@ -459,7 +468,10 @@ hipError_t step_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool f
         if (e != hipSuccess) return e;
         if (kp.moving) k_wall_move_fused<P><<<gw, kBlock, 0, s>>>(kp, b.f[1 - cur], b.rho, b.mu, b.j, b.mu0, b.flag);
     } else {
-        k_collide<P><<<nblocks(kp.nfluid), kBlock, 0, s>>>(kp, b.f[cur], b.f[1 - cur], b.mu, b.F, b.Q);
+        if (kp.keep2)
+            k_collide<P, false><<<gf, kBlock, 0, s>>>(kp, b.f[cur], b.f[1 - cur], b.mu, b.F, b.Q);
+        else
+            k_collide<P, true><<<gf, kBlock, 0, s>>>(kp, b.f[cur], b.f[1 - cur], b.mu, b.F, b.Q);
         if (kp.moving) k_wall_move<P><<<gw, kBlock, 0, s>>>(kp, b.f[1 - cur], b.rho, b.mu);
     }
     mark(3);
@@ -524,7 +536,7 @@ hipError_t launch_state_enter(hipStream_t s, int prec, const KP &kp, const Bufs 
     if (ev) (void)hipEventRecord(ev[0], s);
     if (refresh) {
         hipError_t e = dispatch(prec, [&](auto pc) {
-            k_moments<decltype(pc)::value><<<gf, kBlock, 0, s>>>(kp, b.f[cur], b.rho, b.j, b.mu0, b.flag);
+            moments_pass<decltype(pc)::value>(s, kp, b, cur);
             return hipGetLastError();
         });
         if (e != hipSuccess) return e;

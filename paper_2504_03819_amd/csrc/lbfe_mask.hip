@@ -51,7 +51,7 @@ __global__ __launch_bounds__(kBlock) void k_mask_prep(KP kp, const uint8_t *soli
     nbr[n] = w;
 }
 
-template <int P>
+template <int P, bool NT>
 __global__ __launch_bounds__(kBlock) void k_moments_m(KP kp, const unsigned *nbr, const void *fq, double *rho,
                                                       void *jq, int *flag) {
     using real = real_t<P>;
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(kBlock) void k_moments_m(KP kp, const unsigned *nbr
     // node's slots hold zeros); only the stores depend on it
     const unsigned w = nbr[n];
     const unsigned row = n / (unsigned)kp.nx, x = n - row * (unsigned)kp.nx;
-    const Pops<P> f(fq, kp);
+    const Pops<P, NT> f(fq, kp);
     real v[27];
 #pragma unroll
     for (int i = 0; i < 27; ++i) v[i] = f.ld(i, row, x);
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(kBlock) void k_q_m(KP kp, const unsigned *nbr, cons
     Q[2 * N + n] = solid ? (real)0 : h * sz;
 }
 
-template <int P>
+template <int P, bool NT>
 __global__ __launch_bounds__(kBlock) void k_collide_m(KP kp, const unsigned *nbr, const void *fin_q, void *fout_q,
                                                       const double *mu, const void *Fq, const void *Qq) {
     using real = real_t<P>;
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kBlock) void k_collide_m(KP kp, const unsigned *nbr
     int x, y, z;
     decompose(kp, n, x, y, z);
     const Nb nb(kp, x, y, z);
-    const Pops<P> fin(fin_q, kp);
+    const Pops<P, NT> fin(fin_q, kp);
     const Pops<P> fout(fout_q, kp);
     const unsigned row = nb.row(0, 0);
     real f[27];
@@ -185,7 +185,7 @@ __global__ __launch_bounds__(kBlock) void k_collide_m(KP kp, const unsigned *nbr
     for (int i = 0; i < 27; ++i) f[i] = fin.ld(i, row, (unsigned)x);
     if (solid_at(w)) return;
     const real *F = (const real *)Fq, *Qa = (const real *)Qq;
-    constexpr bool nt = P == LBFE_FP64 || P == LBFE_FP32;  // the aux fields are read once, as in k_collide
+    constexpr bool nt = NT && (P == LBFE_FP64 || P == LBFE_FP32);  // the aux fields are read once, as in k_collide
     auto ld = [&](const auto *p) { return nt ? ldnt(p) : *p; };
     collide_node(kp, f, ld(mu + n), ld(F + n), ld(F + kp.N + n), ld(F + 2 * (size_t)kp.N + n), ld(Qa + n),
                  ld(Qa + kp.N + n), ld(Qa + 2 * (size_t)kp.N + n));
@@ -538,11 +538,18 @@ hipError_t launch_mask_prep(hipStream_t s, const KP &kp, const Bufs &b, const ui
     return hipGetLastError();
 }
 
+template <int P> static void moments_m(hipStream_t s, const KP &kp, const Bufs &b, int cur) {
+    if (kp.keep1)
+        k_moments_m<P, false><<<nblocks(kp.N), kBlock, 0, s>>>(kp, b.nbr, b.f[cur], b.rho, b.j, b.flag);
+    else
+        k_moments_m<P, true><<<nblocks(kp.N), kBlock, 0, s>>>(kp, b.nbr, b.f[cur], b.rho, b.j, b.flag);
+}
+
 hipError_t launch_aux_mask(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur) {
     return dispatch(prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         const unsigned g = nblocks(kp.N);
-        k_moments_m<P><<<g, kBlock, 0, s>>>(kp, b.nbr, b.f[cur], b.rho, b.j, b.flag);
+        moments_m<P>(s, kp, b, cur);
         k_wall_rho_m<<<g, kBlock, 0, s>>>(kp, b.nbr, b.rho);
         chain_m<P>(s, kp, b);
         return hipGetLastError();
@@ -557,12 +564,15 @@ hipError_t launch_step_mask(hipStream_t s, int prec, const KP &kp, const Bufs &b
             if (ev) (void)hipEventRecord(ev[k], s);
         };
         mark(0);
-        k_moments_m<P><<<g, kBlock, 0, s>>>(kp, b.nbr, b.f[cur], b.rho, b.j, b.flag);
+        moments_m<P>(s, kp, b, cur);
         k_wall_rho_m<<<g, kBlock, 0, s>>>(kp, b.nbr, b.rho);
         mark(1);
         chain_m<P>(s, kp, b);
         mark(2);
-        k_collide_m<P><<<g, kBlock, 0, s>>>(kp, b.nbr, b.f[cur], b.f[1 - cur], b.mu, b.F, b.Q);
+        if (kp.keep2)
+            k_collide_m<P, false><<<g, kBlock, 0, s>>>(kp, b.nbr, b.f[cur], b.f[1 - cur], b.mu, b.F, b.Q);
+        else
+            k_collide_m<P, true><<<g, kBlock, 0, s>>>(kp, b.nbr, b.f[cur], b.f[1 - cur], b.mu, b.F, b.Q);
         mark(3);
         mark(4);
         return hipGetLastError();
