@@ -159,10 +159,11 @@ int lbfe_coexistence(double a, double b, double R, double T, double *rho_l, doub
  * NULL = default stream).  Allocates no device memory.
  * E_INVAL on a bad parameter (checked before any device call), E_DEVICE
  * when no GPU is usable.  Schedule fields left at LBFE_AUTO are chosen per
- * grid: the fused step path for FP64 contexts of at least 2^24 nodes where
- * it is allowed, else the two-pass path; the XCD tile order from
- * 2^26 nodes and, without a solid mask, whenever nx or ny is not a power of
- * two; the chain chunk that minimises the busiest CU's plane iterations.
+ * grid: the fused step path for FP64 contexts of at least 5 x 2^20 nodes and
+ * FP32 contexts of at least 19 x 2^20 where it is allowed, else the two-pass
+ * path; the XCD tile order from 2^26 nodes and, without a solid mask,
+ * whenever nx or ny is not a power of two; the chain chunk that minimises the
+ * busiest CU's plane iterations.
  * Asking for the fused path where it is not allowed is E_INVAL. */
 int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out);
 

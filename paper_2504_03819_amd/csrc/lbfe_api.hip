@@ -468,15 +468,22 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
     k.mu0_in_chain = !k.walls && !k.masked && k.N >= (q.precision == LBFE_FP64 ? 6u << 20 : 12u << 20);
     // Step path: the fused collide-stream-moments kernel reads the
     // populations once per step; it has no solid mask, and addresses one
-    // z-plane of the lattice with 32-bit offsets.  Measured on
-    // gfx950 it is faster in FP64 on large grids (256^3: 2.44 against
-    // 2.76 ms per step; 512^3: 19.0 against 22.1 ms) and slower in the FP32
-    // and FP16 forms, whose collide-stream pass alone runs closer to the
-    // bandwidth than the fused kernel with its ring of recollided nodes
-    // (512^3 FP32: 12.6 against 11.6 ms per step).
+    // z-plane of the lattice with 32-bit offsets.  It collides a ring around
+    // every tile, and a small grid leaves it with a nearly empty last round of
+    // workgroups, while the two-pass path there re-reads from the last-level
+    // cache (us per step, two-pass / fused, periodic: FP64 160^3 609 / 664,
+    // 176^3 826 / 774, 200^3 1405 / 1244, 256^3 2705 / 2259, 512^3 21400 /
+    // 16850; FP32 192^3 540 / 650, 256^3 1335 / 1319 but between walls 1384 /
+    // 1475, 301 x 205 x 330 2205 / 1986, 512^3 11400 / 10230).  In the FP16
+    // forms the bytes saved are too few for its instructions (256^3 900 /
+    // 1159, 512^3 7490 / 8460).
     const bool fused_ok = fused_possible(q);
-    if (q.step_path == LBFE_AUTO)
-        q.step_path = fused_ok && q.precision == LBFE_FP64 && k.N >= (1u << 24) ? LBFE_PATH_FUSED : LBFE_PATH_TWO_PASS;
+    if (q.step_path == LBFE_AUTO) {
+        const bool large = q.precision == LBFE_FP64   ? k.N >= (5u << 20)
+                           : q.precision == LBFE_FP32 ? k.N >= (19u << 20)
+                                                      : false;
+        q.step_path = fused_ok && large ? LBFE_PATH_FUSED : LBFE_PATH_TWO_PASS;
+    }
     if (q.step_path == LBFE_PATH_FUSED && !fused_ok) {
         std::fprintf(stderr, "lbfe_create: the fused step path needs no solid mask and a lattice z-plane below "
                              "2 GiB\n");

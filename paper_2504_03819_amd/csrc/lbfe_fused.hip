@@ -11,9 +11,10 @@
 // Tile: TX x TY owned columns plus a one-node ring, marching in z over a
 // chunk of planes.  Per source plane s:
 //   1. every ring-inclusive node (one per lane) collides the populations it
-//      prefetched during the previous plane, issues the loads of plane s+1,
-//      and writes its 27 post-collision values, in their storage encoding,
-//      to one LDS plane [27][(TX+2)(TY+2)];
+//      prefetched during the previous plane, writes its 27 post-collision
+//      values, in their storage encoding, to one LDS plane
+//      [27][(TX+2)(TY+2)], and issues the loads of plane s+1 into the
+//      registers that this frees;
 //   2. every owned column (x, y) reads from LDS the 27 values that arrive
 //      from plane s at (x, y) in the destination planes s-1, s, s+1
 //      (f*_i(x - c_i)), stores them to the output lattice as aligned rows,
@@ -25,6 +26,18 @@
 // consecutive tiles run on one XCD.  The moments are summed in the order of
 // moments() (lbfe_device.h), so rho, j and mu0 are bit for bit those of the
 // separate moments pass over the stored lattice.
+//
+// What bounds it: one workgroup per CU, whose waves pass the two phases
+// together, so an iteration costs its vector instructions (800 a wave and
+// plane in FP32, 770 in FP64) plus what the memory does not hide behind them.
+// FP64 has registers for two waves a SIMD, 512 lanes: 32 x 13 columns and
+// their ring fill 510.  The narrow forms fit three waves in 168 registers
+// since the loads reuse the collided values' registers: 768 lanes, 64 x 9
+// columns.  Collide-stream of 512^3, us: FP64 32 x 12 with the loads before the
+// collision 15850, after it 15110, 32 x 13 14330, without the wall selects
+// 13600-14500 (the floor of its bytes 12400); FP32 10390, 10300, 64 x 9 on 768
+// lanes 8730, without the wall selects 8350 (floor 6300; 64 x 13 on 1024 lanes
+// with spills 8830); FP16 9980, 9620, 7630, 6700.
 #include <type_traits>
 
 #include "lbfe_plane.h"
@@ -34,7 +47,7 @@ namespace {
 
 using namespace plane;
 
-template <int P, int TX, int TY, int NT>
+template <int P, bool WALLS, int TX, int TY, int NT>
 __global__ __launch_bounds__(NT) void k_fused(KP kp, const void *fin_q, void *fout_q, const double *__restrict__ mu,
                                               const void *Fq, const void *Qq, double *__restrict__ rho, void *jq,
                                               double *__restrict__ mu0, int *flag, int cz) {
@@ -69,7 +82,7 @@ __global__ __launch_bounds__(NT) void k_fused(KP kp, const void *fin_q, void *fo
     const real *F = (const real *)Fq, *Qa = (const real *)Qq;
     real *J = (real *)jq;
 
-    auto fluid = [&](int s) { return kp.walls ? (s >= 1 && s <= kp.nz - 2) : true; };
+    auto fluid = [&](int s) { return WALLS ? (s >= 1 && s <= kp.nz - 2) : true; };
     auto zw = [&](int s) { return s < 0 ? s + kp.nz : (s >= kp.nz ? s - kp.nz : s); };  // |s| within one period
 
     // prefetched inputs of the next source plane
@@ -138,9 +151,9 @@ __global__ __launch_bounds__(NT) void k_fused(KP kp, const void *fin_q, void *fo
                     pl.store(L, i, i, kk, v, v0);
                 } else {
                     const int in = dir(cx, cy, c), ir = dir(-cx, -cy, c);
-                    const int kk = refl ? oc : oc - cy * G::WX - cx;
-                    val[t] = refl ? pl.get(ir, kk) : pl.get(in, kk);
-                    pl.store(L, refl ? 26 - ir : in, refl ? ir : in, kk, v, v0);
+                    const int kk = WALLS && refl ? oc : oc - cy * G::WX - cx;
+                    val[t] = WALLS && refl ? pl.get(ir, kk) : pl.get(in, kk);
+                    pl.store(L, WALLS && refl ? 26 - ir : in, WALLS && refl ? ir : in, kk, v, v0);
                 }
             }
             xpartial((double)val[0], (double)val[1], (double)val[2], R[cy + 1], X[cy + 1]);
@@ -157,21 +170,16 @@ __global__ __launch_bounds__(NT) void k_fused(KP kp, const void *fin_q, void *fo
     load(zs - 1, fluid(zs - 1));
     for (int s = zs - 1; s <= ze; ++s) {
         const bool sf = fluid(s);
-        real f[27];
-#pragma unroll
-        for (int i = 0; i < 27; ++i) f[i] = fn[i];
-        const double m = mn;
-        const real Fx = an[0], Fy = an[1], Fz = an[2], q200 = an[3], q020 = an[4], q002 = an[5];
-        load(s + 1, s + 1 <= ze && fluid(s + 1));
         if (sf && coll) {
-            collide_node(kp, f, m, Fx, Fy, Fz, q200, q020, q002);
+            collide_node(kp, fn, mn, an[0], an[1], an[2], an[3], an[4], an[5]);
 #pragma unroll
-            for (int i = 0; i < 27; ++i) pl.put(i, k, f[i]);
+            for (int i = 0; i < 27; ++i) pl.put(i, k, fn[i]);
         }
+        load(s + 1, s + 1 <= ze && fluid(s + 1));
         __syncthreads();
-        if (k < TX * TY) {  // the waves that hold owned columns (wave-uniform)
+        if ((k & ~63) < TX * TY) {  // the waves that hold owned columns
             const int zm = s - 1, zp = s + 1;
-            const bool wall_lo = kp.walls && s == 1, wall_hi = kp.walls && s == kp.nz - 2;
+            const bool wall_lo = WALLS && s == 1, wall_hi = WALLS && s == kp.nz - 2;
             const bool own_m = sf && zm >= zs && zm < ze && fluid(zm);
             const bool own_0 = sf && s >= zs && s < ze;
             const bool own_p = sf && zp >= zs && zp < ze && fluid(zp);
@@ -186,7 +194,7 @@ __global__ __launch_bounds__(NT) void k_fused(KP kp, const void *fin_q, void *fo
             // to the top wall (s = nz-1, solid) with the reflection that the
             // previous plane left in cur
             {
-                const bool top = kp.walls && s == kp.nz - 1;
+                const bool top = WALLS && s == kp.nz - 1;
                 const Layer Lc = top ? Layer{cur.r, cur.jx, cur.jy} : Lm;
                 Acc A = prev;
                 A.jx += Lc.JX;
@@ -207,13 +215,47 @@ __global__ __launch_bounds__(NT) void k_fused(KP kp, const void *fin_q, void *fo
     if (bad) *flag = 1;
 }
 
-template <int P, int TX, int TY, int NT> hipError_t launch(hipStream_t s, const KP &kp, const Bufs &b, int cur) {
-    const unsigned ntx = (kp.nx + TX - 1) / TX, nty = (kp.ny + TY - 1) / TY;
-    const int cz = chunk_planes(kp, ntx * nty);
+// Tile and threads of a storage form (one workgroup per CU)
+template <int P> struct Tile {
+    static constexpr int TX = 64, TY = 9, NT = 768;
+};
+template <> struct Tile<LBFE_FP64> {
+    static constexpr int TX = 32, TY = 13, NT = 512;
+};
+
+unsigned tiles_of(const KP &kp, int tx, int ty) {
+    return (unsigned)((kp.nx + tx - 1) / tx) * (unsigned)((kp.ny + ty - 1) / ty);
+}
+
+// Plane iterations of the busiest CU with chunks of c planes.
+size_t plane_iters(const KP &kp, unsigned tiles, int c) {
     const int nzf = kp.z1 - kp.z0;
-    const dim3 grid(ntx * nty, (nzf + cz - 1) / cz);
-    k_fused<P, TX, TY, NT><<<grid, NT, 0, s>>>(kp, b.f[cur], b.f[1 - cur], b.mu, b.F, b.Q, b.rho, b.j, b.mu0,
-                                                b.flag, cz);
+    const size_t wg = (size_t)tiles * ((nzf + c - 1) / c);
+    return (wg + 255) / 256 * (size_t)(c + 2);
+}
+
+// Planes per workgroup: the fewest iterations of the busiest CU (256^3 FP64: 32
+// planes, 5 rounds of 34 iterations, 1873 us; 64 planes, 3 rounds of 66, 2082).
+int fused_chunk(const KP &kp, unsigned tiles) {
+    int cz = 8;
+    for (int c = 9; c <= 96; ++c)
+        if (plane_iters(kp, tiles, c) < plane_iters(kp, tiles, cz)) cz = c;
+    return cz;
+}
+
+template <int P> hipError_t launch(hipStream_t s, const KP &kp, const Bufs &b, int cur) {
+    constexpr int TX = Tile<P>::TX, TY = Tile<P>::TY, NT = Tile<P>::NT;
+    const unsigned tiles = tiles_of(kp, TX, TY);
+    const int cz = fused_chunk(kp, tiles), nzf = kp.z1 - kp.z0;
+    const dim3 grid(tiles, (nzf + cz - 1) / cz);
+    auto go = [&](auto walls) {
+        k_fused<P, decltype(walls)::value, TX, TY, NT><<<grid, NT, 0, s>>>(kp, b.f[cur], b.f[1 - cur], b.mu, b.F, b.Q,
+                                                                          b.rho, b.j, b.mu0, b.flag, cz);
+    };
+    if (kp.walls)
+        go(std::true_type{});
+    else
+        go(std::false_type{});
     return hipGetLastError();
 }
 
@@ -227,10 +269,10 @@ bool fused_plane_ok(int prec, size_t plane) {
 
 hipError_t launch_fused(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur) {
     switch (prec) {
-        case LBFE_FP64: return launch<LBFE_FP64, 32, 12, 512>(s, kp, b, cur);
-        case LBFE_FP32: return launch<LBFE_FP32, 32, 12, 512>(s, kp, b, cur);
-        case LBFE_FP16_DEV: return launch<LBFE_FP16_DEV, 32, 12, 512>(s, kp, b, cur);
-        default: return launch<LBFE_FP16_DEV_F0FP32, 32, 12, 512>(s, kp, b, cur);
+        case LBFE_FP64: return launch<LBFE_FP64>(s, kp, b, cur);
+        case LBFE_FP32: return launch<LBFE_FP32>(s, kp, b, cur);
+        case LBFE_FP16_DEV: return launch<LBFE_FP16_DEV>(s, kp, b, cur);
+        default: return launch<LBFE_FP16_DEV_F0FP32>(s, kp, b, cur);
     }
 }
 

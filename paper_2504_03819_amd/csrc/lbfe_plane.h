@@ -178,7 +178,6 @@ inline int chunk_planes(const KP &kp, unsigned tiles) {
 template <int TX, int TY, int NT> struct Geo {
     static constexpr int WX = TX + 2, WY = TY + 2, NR = WX * WY;
     static_assert(NR <= NT, "one lane per ring-inclusive node");
-    static_assert(TX * TY % 64 == 0, "owned columns fill whole waves");
 };
 
 }  // namespace plane
