@@ -1205,7 +1205,7 @@ hipError_t launch_adj_step(hipStream_t s, int prec, const KP &kp, const Bufs &b,
     if (recompute) {
         Bufs fb = b;
         fb.f[0] = const_cast<void *>(ft);
-        hipError_t e = launch_aux(s, prec, kp, fb, 0);
+        hipError_t e = launch_aux(s, prec, kp, fb, 0, true);
         if (e != hipSuccess) return e;
     }
     const unsigned gf = nblocks(kp.nfluid);

@@ -42,6 +42,11 @@ template <int P, bool NT = true> struct Pops;
 // lattice of a few hundred MB would otherwise push the reused data (aux fields,
 // stencil halos, the freshly written lattice) out of it.  Stores stay ordinary (non-temporal stores of the
 // shifted push-stream rows were measured slower).
+__device__ inline void stnt(double v, double *p) { __builtin_nontemporal_store(v, p); }
+__device__ inline void stnt(float v, float *p) { __builtin_nontemporal_store(v, p); }
+__device__ inline void stnt(__half v, __half *p) {
+    __builtin_nontemporal_store(__builtin_bit_cast(unsigned short, v), (unsigned short *)p);
+}
 __device__ inline double ldnt(const double *p) { return __builtin_nontemporal_load(p); }
 __device__ inline float ldnt(const float *p) { return __builtin_nontemporal_load(p); }
 __device__ inline __half ldnt(const __half *p) {
@@ -55,6 +60,7 @@ template <bool NT> struct Pops<LBFE_FP64, NT> {
     __device__ size_t off(int i, unsigned row, unsigned x) const { return ((size_t)row * 27 + i) * nx + x; }
     __device__ double ld(int i, unsigned row, unsigned x) const { return ldp<NT>(p + off(i, row, x)); }
     __device__ void st(int i, unsigned row, unsigned x, double v) const { p[off(i, row, x)] = v; }
+    __device__ void st_nt(int i, unsigned row, unsigned x, double v) const { stnt(v, p + off(i, row, x)); }
     __device__ static double quant(int, double v) { return v; }  // value a store then load returns
 };
 
@@ -65,6 +71,7 @@ template <bool NT> struct Pops<LBFE_FP32, NT> {
     __device__ size_t off(int i, unsigned row, unsigned x) const { return ((size_t)row * 27 + i) * nx + x; }
     __device__ float ld(int i, unsigned row, unsigned x) const { return ldp<NT>(p + off(i, row, x)); }
     __device__ void st(int i, unsigned row, unsigned x, float v) const { p[off(i, row, x)] = v; }
+    __device__ void st_nt(int i, unsigned row, unsigned x, float v) const { stnt(v, p + off(i, row, x)); }
     __device__ static float quant(int, float v) { return v; }
 };
 
@@ -93,6 +100,7 @@ template <bool NT> struct Pops<LBFE_FP16_DEV, NT> {
     __device__ size_t off(int i, unsigned row, unsigned x) const { return ((size_t)row * 27 + i) * nx + x; }
     __device__ float ld(int i, unsigned row, unsigned x) const { return dec16(i, ldp<NT>(p + off(i, row, x))); }
     __device__ void st(int i, unsigned row, unsigned x, float v) const { p[off(i, row, x)] = enc16(i, v); }
+    __device__ void st_nt(int i, unsigned row, unsigned x, float v) const { stnt(enc16(i, v), p + off(i, row, x)); }
     __device__ static float quant(int i, float v) { return dec16(i, enc16(i, v)); }
 };
 
@@ -115,6 +123,12 @@ template <bool NT> struct Pops<LBFE_FP16_DEV_F0FP32, NT> {
             p0[(size_t)row * nx + x] = v;
         else
             p[off(i, row, x)] = enc16(i, v);
+    }
+    __device__ void st_nt(int i, unsigned row, unsigned x, float v) const {
+        if (i == kRest)
+            stnt(v, p0 + (size_t)row * nx + x);
+        else
+            stnt(enc16(i, v), p + off(i, row, x));
     }
     __device__ static float quant(int i, float v) { return i == kRest ? v : dec16(i, enc16(i, v)); }
 };

@@ -64,7 +64,8 @@ struct Bufs {
 hipError_t launch_fill(hipStream_t s, void *p, size_t bytes);
 hipError_t launch_init(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur, const double *rho0,
                        const double *u0);
-hipError_t launch_aux(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur);
+// mu, F and Q of f[cur]; refresh: rho, j and mu0 do not hold its moments yet
+hipError_t launch_aux(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur, bool refresh);
 // One step f[cur] -> f[1 - cur].  fused: chain + fused collide-stream-moments
 // (+ wall density), with a moments pass first if `refresh`; otherwise the
 // unfused moments, chain, collide-stream.  ev5: optional timing events.

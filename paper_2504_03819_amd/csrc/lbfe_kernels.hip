@@ -111,10 +111,7 @@ __global__ __launch_bounds__(kBlock) void k_wall_rho(KP kp, double *rho) {
 }
 
 // mu = mu0(rho) - kappa lap_h rho, lap_h g = 6 sum_i w_i (g(x+c_i) - g(x)).
-__global__ __launch_bounds__(kBlock) void k_mu(KP kp, const double *rho, double *mu) {
-    const unsigned idx = tile_id(kp) * kBlock + threadIdx.x;
-    if (idx >= kp.nfluid) return;
-    const unsigned n = (unsigned)kp.z0 * kp.plane + idx;
+__device__ inline double mu_node(const KP &kp, const double *rho, unsigned n) {
     int x, y, z;
     decompose(kp, n, x, y, z);
     const Nb nb(kp, x, y, z);
@@ -125,7 +122,14 @@ __global__ __launch_bounds__(kBlock) void k_mu(KP kp, const double *rho, double 
         if (i == kRest) continue;
         s += wi(i) * (rho[nb.at(cxi(i), cyi(i), czi(i))] - r0);
     }
-    mu[n] = mu_bulk(kp, r0) - kp.kappa * 6.0 * s;
+    return mu_bulk(kp, r0) - kp.kappa * 6.0 * s;
+}
+
+__global__ __launch_bounds__(kBlock) void k_mu(KP kp, const double *rho, double *mu) {
+    const unsigned idx = tile_id(kp) * kBlock + threadIdx.x;
+    if (idx >= kp.nfluid) return;
+    const unsigned n = (unsigned)kp.z0 * kp.plane + idx;
+    mu[n] = mu_node(kp, rho, n);
 }
 
 // Fused collide + stream of one fluid node (push: f*_i(x) -> x + c_i, or
@@ -258,19 +262,22 @@ __global__ __launch_bounds__(kBlock) void k_wall_move_fused(KP kp, void *fq, dou
     if (!(rn > 0.0 && kp.b * rn < 1.0)) *flag = 1;
 }
 
-// Initial populations: inverse CM transform of the Eq. (20) equilibrium.
-template <int P>
-__global__ __launch_bounds__(kBlock) void k_init(KP kp, const double *rho0, const double *u0, const double *mu,
-                                                 void *fq) {
+// Initial populations: inverse CM transform of the Eq. (20) equilibrium at
+// rho, u0 and p_m(mu(rho)).  Bound by the stores of 27 populations; NT: a
+// lattice beyond the last-level cache (us per call with mu formed by a kernel
+// of its own and ordinary stores / this: FP64 128^3 166 / 108, 192 x 192 x 96 264
+// / 163, 512^3 10150 / 9020; FP32 192 x 192 x 96 181 / 110, 512^3 6230 / 5560).
+template <int P, bool NT>
+__global__ __launch_bounds__(kBlock) void k_init(KP kp, const double *rho, const double *u0, void *fq) {
     using real = real_t<P>;
-    const unsigned idx = blockIdx.x * kBlock + threadIdx.x;
+    const unsigned idx = tile_id(kp) * kBlock + threadIdx.x;
     if (idx >= kp.nfluid) return;
     const unsigned n = (unsigned)kp.z0 * kp.plane + idx;
     real k[27];
 #pragma unroll
     for (int i = 0; i < 27; ++i) k[i] = 0;
-    const real pm = (real)((1.0 + mu[n]) / 3.0);
-    k[K(0, 0, 0)] = (real)rho0[n];
+    const real pm = (real)((1.0 + mu_node(kp, rho, n)) / 3.0);
+    k[K(0, 0, 0)] = (real)rho[n];
     k[K(2, 0, 0)] = k[K(0, 2, 0)] = k[K(0, 0, 2)] = pm;
     k[K(2, 2, 0)] = k[K(2, 0, 2)] = k[K(0, 2, 2)] = pm * (real)(1.0 / 3.0);
     k[K(2, 2, 2)] = pm * (real)(1.0 / 9.0);
@@ -284,7 +291,7 @@ __global__ __launch_bounds__(kBlock) void k_init(KP kp, const double *rho0, cons
     const Pops<P> f(fq, kp);
     const unsigned row = n / (unsigned)kp.nx, x = n - row * (unsigned)kp.nx;
 #pragma unroll
-    for (int i = 0; i < 27; ++i) f.st(i, row, x, k[i]);
+    for (int i = 0; i < 27; ++i) NT ? f.st_nt(i, row, x, k[i]) : f.st(i, row, x, k[i]);
 }
 
 __global__ __launch_bounds__(kBlock) void k_copy_fluid(KP kp, const double *src, double *dst) {
@@ -430,10 +437,11 @@ template <int P> void moments_pass(hipStream_t s, const KP &kp, const Bufs &b, i
 }
 
 template <int P>
-hipError_t aux_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur) {
-    const unsigned gf = nblocks(kp.nfluid), gw = nblocks(2 * (size_t)kp.plane);
-    moments_pass<P>(s, kp, b, cur);
-    if (kp.walls) k_wall_rho<<<gw, kBlock, 0, s>>>(kp, b.rho);
+hipError_t aux_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool refresh) {
+    if (refresh) {
+        moments_pass<P>(s, kp, b, cur);
+        if (kp.walls) k_wall_rho<<<nblocks(2 * (size_t)kp.plane), kBlock, 0, s>>>(kp, b.rho);
+    }
     hipError_t e = launch_chain(s, P, kp, b);
     if (e != hipSuccess) return e;
     return hipGetLastError();
@@ -483,10 +491,16 @@ hipError_t step_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool f
 template <int P>
 hipError_t init_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, const double *rho0, const double *u0) {
     const unsigned gf = nblocks(kp.nfluid), gw = nblocks(2 * (size_t)kp.plane);
-    k_copy_fluid<<<gf, kBlock, 0, s>>>(kp, rho0, b.rho);
-    if (kp.walls) k_wall_rho<<<gw, kBlock, 0, s>>>(kp, b.rho);
-    k_mu<<<gf, kBlock, 0, s>>>(kp, b.rho, b.mu);
-    k_init<P><<<gf, kBlock, 0, s>>>(kp, b.rho, u0, b.mu, b.f[cur]);
+    const double *rho = rho0;
+    if (kp.walls) {  // the stencil needs the density of the solid planes
+        k_copy_fluid<<<gf, kBlock, 0, s>>>(kp, rho0, b.rho);
+        k_wall_rho<<<gw, kBlock, 0, s>>>(kp, b.rho);
+        rho = b.rho;
+    }
+    if (kp.keep1)
+        k_init<P, false><<<gf, kBlock, 0, s>>>(kp, rho, u0, b.f[cur]);
+    else
+        k_init<P, true><<<gf, kBlock, 0, s>>>(kp, rho, u0, b.f[cur]);
     return hipGetLastError();
 }
 
@@ -517,9 +531,9 @@ hipError_t launch_init(hipStream_t s, int prec, const KP &kp, const Bufs &b, int
     return dispatch(prec, [&](auto pc) { return init_impl<decltype(pc)::value>(s, kp, b, cur, rho0, u0); });
 }
 
-hipError_t launch_aux(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur) {
+hipError_t launch_aux(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur, bool refresh) {
     if (kp.masked) return launch_aux_mask(s, prec, kp, b, cur);
-    return dispatch(prec, [&](auto pc) { return aux_impl<decltype(pc)::value>(s, kp, b, cur); });
+    return dispatch(prec, [&](auto pc) { return aux_impl<decltype(pc)::value>(s, kp, b, cur, refresh); });
 }
 
 hipError_t launch_step(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur, bool fused, bool refresh,

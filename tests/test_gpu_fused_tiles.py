@@ -41,3 +41,33 @@ def test_fused_tiles_equal_the_two_passes(walls, precision):
             s.step(3)
             out.append((s.get_state(), s.field(2)))
         assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1]), shape
+
+
+@pytest.mark.parametrize("walls", ["none", "still", "moving"])
+@pytest.mark.parametrize("path", [lbfe.PATH_TWO_PASS, lbfe.PATH_FUSED, lbfe.PATH_STATE])
+def test_fields_after_steps_are_those_of_the_stored_state(path, walls):
+    """The fields read the density and momentum that the fused and state paths
+    leave behind, twice the same, and the same as a context that only got the
+    populations."""
+    if path == lbfe.PATH_STATE and walls == "moving":
+        pytest.skip("the state path has no moving walls")
+    shape = (11, 14, 33)
+    T = eos.temperature(0.8)
+    kw = dict(nx=33, ny=14, nz=11, T=T, precision="fp64")
+    if walls != "none":
+        kw.update(walls_z=1, wet_mode=1, wet_value=1.2)
+    if path != lbfe.PATH_STATE and walls != "none":
+        kw.update(omega=OM)
+    if walls == "moving":
+        kw.update(wall_u=(0.01, -0.02, 0.015, 0.0))
+    a, b = make_sim(step_path=path, **kw), make_sim(step_path=path, **kw)
+    a.init_density(torch.tensor(droplet_rho(shape, T, walls=walls != "none", radius=4.0)))
+    for n in (1, 2, 3):
+        a.step(n)
+        b.set_state(a.get_state())
+        fb = b.fields()
+        for _ in range(2):
+            fa = a.fields()
+            for name in fb:
+                assert torch.equal(fa[name], fb[name]), (n, name)
+        assert a.reduce() == b.reduce()
