@@ -17,10 +17,11 @@
 //                   then the transposed gradient stencil -> adjoint of mu
 //                   (all nodes), in one z-march with G_bar kept in LDS
 //   k_adj_wall_gather (walls) wall average of Eq. (36) transposed
-//   k_adj_rho       mu0'(rho) and the (symmetric) Laplacian transposed
-//   k_adj_wall_rho_solid, k_adj_wall_gather (walls) limiter/window of
-//                   Eqs. (37)-(38) transposed
-//   k_adj_pack      (rho_bar_total, j_bar) per node, for the next step's gather
+//   k_adj_rho       mu0'(rho) and the (symmetric) Laplacian transposed;
+//                   kappa and nu gradients
+//   k_adj_tail      (walls) limiter/window of Eqs. (37)-(38) transposed, wet
+//                   value gradient; (rho_bar_total, j_bar) per node, for the
+//                   next step's gather
 //   k_adj_final     lambda_i(t) += rho_bar + c_i . j_bar, applied when lambda
 //                   is read out; between adjoint steps this term is added by
 //                   the next step's gather instead
@@ -62,10 +63,10 @@ enum : int {
     A_RHOB = 10, // rho bar (local part)
     A_JB = 11,   // 3 (real): j bar, rounded to the compute precision
     A_MUB = 14,  // mu bar (all nodes; the wall and mask transposes)
-    A_KAPC = 15, // per-node dL/dkappa contribution
+    A_KAPC = 15, // dL/dkappa, a partial sum per workgroup of k_adj_rho
     A_NUC = 16,  // per-node dL/dnu contribution
-    A_WETC = 17, // dL/d(wet) contribution per wall node, 2 planes packed
-    A_RAVEB = 18,// rho_ave bar at solid nodes
+    A_WETC = 17, // dL/d(wet): a partial sum per workgroup of k_adj_tail, or (mask) per node
+    A_RAVEB = 18,// mask: rho_ave bar at solid nodes; else dL/dnu, a partial sum per workgroup of k_adj_rho
     A_RHOBT = 19,// rho bar total (all nodes)
     A_MUBT = 20, // mu bar total (all nodes)
     A_PACK = 21, // 4 planes: (rho_bar_total, j_bar) per node as 4 compute-precision values
@@ -86,6 +87,20 @@ template <class real> struct Lam {
         __builtin_nontemporal_store(v, p + off(i, row, x));
     }
 };
+
+// Sum of v over the workgroup's NT threads, in a fixed order, on thread 0.
+template <int NT> __device__ inline double block_sum(double v) {
+    __shared__ double w[NT / 64];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o);
+    if ((threadIdx.x & 63u) == 0) w[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double t = 0.0;
+    if (threadIdx.x == 0)
+        for (int q = 0; q < NT / 64; ++q) t += w[q];
+    __syncthreads();
+    return t;
+}
 
 // Plane c of a (real) slot group.
 template <class real> __device__ inline real *aplane(void *abuf, int slot, int c, size_t N) {
@@ -265,7 +280,7 @@ template <class real> __device__ inline real final_term(real rb, real jx, real j
     if (czi(i)) add += (real)czi(i) * jz;
     return add;
 }
-// the same four values packed per node (k_adj_pack), one vector load
+// the same four values packed per node (k_adj_tail), one vector load
 template <class real> using Pack4 = std::conditional_t<std::is_same_v<real, double>, double4, float4>;
 template <class real> __device__ inline real final_term(const Pack4<real> *pk, int i, size_t m) {
     const Pack4<real> t = pk[m];
@@ -279,14 +294,6 @@ template <class real> __device__ inline void store_pack(void *abuf, size_t N, si
     t.z = aplane<real>(abuf, A_JB, 1, N)[n];
     t.w = aplane<real>(abuf, A_JB, 2, N)[n];
     ((Pack4<real> *)((double *)abuf + A_PACK * N))[n] = t;
-}
-
-template <int P> __global__ __launch_bounds__(kBlock) void k_adj_pack(KP kp, Bufs b) {
-    using real = real_t<P>;
-    const unsigned idx = tile_id(kp) * kBlock + threadIdx.x;
-    if (idx >= kp.nfluid) return;
-    const size_t n = (size_t)kp.z0 * kp.plane + idx, N = kp.N;
-    store_pack<real>(b.abuf, N, n, ((const double *)b.abuf)[A_RHOBT * N + n]);
 }
 
 // ---------------------------------------------------------------------------
@@ -722,14 +729,16 @@ __global__ __launch_bounds__(kBlock) void k_adj_wall_gather(KP kp, const double 
 
 // rho_bar_total(y) = [fluid: rho_bar + mu_bar mu0'(rho)] - kappa L[mu_bar_fluid](y), in a
 // z-march like k_adj_phimu's (plane t staged, in-plane parts of t-1, node t-2);
-// per-node dL/dkappa = -mu_bar L[rho].  `mub` is the total mu_bar (solid
+// dL/dkappa = -mu_bar L[rho] and, with nuc, the nodes' dL/dnu are summed per
+// workgroup here (the separate pass that read both from memory took 3.7 us of a
+// 48x40x32 step, 16 of a 192x192x96 one).  `mub` is the total mu_bar (solid
 // entries are ignored: the Laplacian's adjoint sees fluid mu_bar only).
 constexpr int RTX = 32, RTY = 16, RNT = RTX * RTY;
 constexpr int RWX = RTX + 2, RNR = RWX * (RTY + 2), RPT = (RNR + RNT - 1) / RNT;
 template <bool MASK>
 __global__ __launch_bounds__(RNT) void k_adj_rho(KP kp, const double *mub, const double *rhob_local,
-                                                 const double *rho, double *rhobt, double *kapc, int cz,
-                                                 const unsigned *nbr) {
+                                                 const double *rho, const double *nuc, double *rhobt, double *kap,
+                                                 double *nu, int cz, const unsigned *nbr) {
     __shared__ double sd[2][2][RNR];  // mu_bar (0 on solid planes) and rho of plane p (slot p & 1)
     const int ntx = (kp.nx + RTX - 1) / RTX;
     int tile, chunk;
@@ -750,7 +759,7 @@ __global__ __launch_bounds__(RNT) void k_adj_rho(KP kp, const double *mub, const
     auto next = [&](int g) { return g + 1 == kp.nz ? 0 : g + 1; };
     auto fluid_plane = [&](int g) { return g >= kp.z0 && g < kp.z1; };
     // loads run one iteration ahead of their use
-    double pre[2][RPT], lpre;
+    double pre[2][RPT], lpre, npre = 0.0;
     unsigned wpre = 0;
     auto load = [&](int g, bool ok) {  // ok false: a plane the chunk does not need
         const size_t f = (size_t)g * plane;
@@ -764,8 +773,10 @@ __global__ __launch_bounds__(RNT) void k_adj_rho(KP kp, const double *mub, const
     auto load_node = [&](int g, bool ok) {
         const size_t f = (size_t)g * plane;
         pld(lpre, plane_of(rhob_local, f, plane, 8), ok ? ooff : kNone);
+        if (nuc) pld(npre, plane_of(nuc, f, plane, 8), ok ? ooff : kNone);
         if constexpr (MASK) wpre = own ? nbr[f + ooff] : kSelfBit;
     };
+    double ksum = 0, nsum = 0;
     double ma = 0, mb = 0, ra = 0, rb = 0, m0 = 0, r0 = 0;  // Wx Wy of two planes back, one back; values one back
     int t = zs - 1;
     int g2 = zwrap(t - 2, kp.nz), g1 = zwrap(t - 1, kp.nz), gn = zwrap(t, kp.nz);
@@ -785,17 +796,17 @@ __global__ __launch_bounds__(RNT) void k_adj_rho(KP kp, const double *mub, const
             const double mn = smooth2<RWX>(d[0], c), rn = smooth2<RWX>(d[1], c);
             const double lm = 6.0 * (wz(ma, mb, mn) - m0), lr = 6.0 * (wz(ra, rb, rn) - r0);
             const bool fluid = fluid_plane(g2) && !(MASK && (wpre & kSelfBit));
-            double out = -kp.kappa * lm, kc = 0.0;
+            double out = -kp.kappa * lm;
             if (fluid) {
                 const double q = 1.0 - kp.b * r0;
                 const double dmu0 = kp.RT / (r0 * q * q) - 2.0 * kp.a;
                 out += lpre + m0 * dmu0;
-                kc = -m0 * lr;
+                if (own && t - 2 >= zs) ksum -= m0 * lr;
             }
+            nsum += npre;  // 0 outside the chunk and the box
             load_node(g1, t - 1 >= zs && t - 1 < ze);
             const unsigned o = t - 2 >= zs ? ooff : kNone;
             const size_t f = (size_t)g2 * plane;
-            pst(kc, plane_of(kapc, f, plane, 8), o);
             pst(out, plane_of(rhobt, f, plane, 8), o);
             ma = mb, mb = mn, ra = rb, rb = rn;
             m0 = d[0][c];
@@ -807,32 +818,19 @@ __global__ __launch_bounds__(RNT) void k_adj_rho(KP kp, const double *mub, const
         g2 = g1;
         g1 = next(g1);
     }
+    ksum = block_sum<RNT>(ksum);
+    nsum = block_sum<RNT>(nsum);
+    if (tid == 0) {
+        const size_t i = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
+        kap[i] = ksum;
+        nu[i] = nsum;
+    }
 }
 
-// Solid nodes: rho_ave_bar = W'(rho_ave) rho_bar(x_s), and the per-node
-// dL/d(wet_value) = dW/d(wet) rho_bar(x_s) (active branch of Eq. (38)).
-__global__ __launch_bounds__(kBlock) void k_adj_wall_rho_solid(KP kp, const double *rho, const double *rhobt,
-                                                               double *raveb, double *wetc) {
-    const unsigned idx = blockIdx.x * kBlock + threadIdx.x;
-    if (idx >= 2 * kp.plane) return;
-    const int side = idx >= kp.plane;
-    const unsigned p = idx - (side ? kp.plane : 0u);
-    const int y = (int)(p / (unsigned)kp.nx), x = (int)(p - (unsigned)y * kp.nx);
-    const int zs = side ? kp.nz - 1 : 0;
-    const Nb nb(kp, x, y, zs);
-    double num = 0.0, den = 0.0;
-    for (int cz = -1; cz <= 1; ++cz) {
-        const int zz = zs + cz;
-        if (zz < 1 || zz > kp.nz - 2) continue;
-        for (int cy = -1; cy <= 1; ++cy)
-            for (int cx = -1; cx <= 1; ++cx) {
-                num += wq(cx, cy, cz) * rho[nb.at(cx, cy, cz)];
-                den += wq(cx, cy, cz);
-            }
-    }
-    const double rave = num / den;
-    const size_t n = (size_t)zs * kp.plane + p;
-    const double g = rhobt[n];
+// rho_ave_bar = W'(rho_ave) rho_bar(x_s) of a solid node of a wall plane with
+// wall average rave and rho_bar g; wet receives dL/d(wet_value) = dW/d(wet)
+// rho_bar(x_s) (active branch of Eq. (38)).
+__device__ inline double wall_rho_bar(const KP &kp, double rave, double g, double &wet) {
     double dW = 1.0, dwet = 0.0;
     if (rave >= kp.lo && rave <= kp.hi) {
         if (kp.wet_mode == LBFE_WET_PHI) {
@@ -847,8 +845,77 @@ __global__ __launch_bounds__(kBlock) void k_adj_wall_rho_solid(KP kp, const doub
             dwet = inside ? -1.0 : 0.0;
         }
     }
-    raveb[n] = dW * g;
-    wetc[idx] = dwet * g;
+    wet = dwet * g;
+    return dW * g;
+}
+
+// The end of an adjoint step at a fluid node.  WALLS: beside a wall,
+// rho_bar_total takes the transposed wall average of rho_ave_bar over the
+// node's nine solid neighbours, whose rho_bar k_adj_rho left in the solid
+// planes; each is formed again for every neighbour, from the 5 x 5 densities
+// around the node, loaded together: no launches of their own (two of 4 us).
+// PACK: the (rho_bar_total, j_bar) pack of the next step.
+template <int P, bool PACK, bool WALLS>
+__global__ __launch_bounds__(kBlock) void k_adj_tail(KP kp, Bufs b) {
+    using real = real_t<P>;
+    const unsigned idx = tile_id(kp) * kBlock + threadIdx.x;
+    const size_t N = kp.N;
+    double *A = (double *)b.abuf, *rhobt = A + A_RHOBT * N;
+    double wet = 0.0;
+    if (idx < kp.nfluid) {
+        const unsigned n = (unsigned)kp.z0 * kp.plane + idx;
+        double rb = rhobt[n];
+        if constexpr (WALLS) {
+            int x, y, z;
+            decompose(kp, n, x, y, z);
+            if (z == 1 || z == kp.nz - 2) {
+                unsigned X[5], Y[5];
+#pragma unroll
+                for (int k = 0; k < 5; ++k) {
+                    X[k] = (unsigned)zwrap(x + k - 2, kp.nx);
+                    Y[k] = (unsigned)zwrap(y + k - 2, kp.ny) * (unsigned)kp.nx;
+                }
+                // densities of the plane beside the wall and their wall averages
+                double r[5][5], acc = 0.0;
+#pragma unroll
+                for (int v = 0; v < 5; ++v)
+#pragma unroll
+                    for (int u = 0; u < 5; ++u) r[v][u] = b.rho[(size_t)z * kp.plane + Y[v] + X[u]];
+                for (int side = 0; side < 2; ++side) {
+                    if (side ? z != kp.nz - 2 : z != 1) continue;
+                    const int zs = side ? kp.nz - 1 : 0;
+                    double g[3][3];
+#pragma unroll
+                    for (int v = 0; v < 3; ++v)
+#pragma unroll
+                        for (int u = 0; u < 3; ++u) g[v][u] = rhobt[(size_t)zs * kp.plane + Y[v + 1] + X[u + 1]];
+                    const double inv = 1.0 / wall_den(kp, zs);
+#pragma unroll
+                    for (int cy = -1; cy <= 1; ++cy)
+#pragma unroll
+                        for (int cx = -1; cx <= 1; ++cx) {
+                            double num = 0.0, den = 0.0, w;
+#pragma unroll
+                            for (int dy = -1; dy <= 1; ++dy)
+#pragma unroll
+                                for (int dx = -1; dx <= 1; ++dx) {
+                                    num += wq(dx, dy, 1) * r[cy + dy + 2][cx + dx + 2];
+                                    den += wq(dx, dy, 1);
+                                }
+                            acc += wq(cx, cy, 1) * inv * wall_rho_bar(kp, num / den, g[cy + 1][cx + 1], w);
+                            if (cx == 0 && cy == 0) wet += w;
+                        }
+                }
+                rb += acc;
+                rhobt[n] = rb;
+            }
+        }
+        if constexpr (PACK) store_pack<real>(b.abuf, N, n, rb);
+    }
+    if constexpr (WALLS) {
+        wet = block_sum<kBlock>(wet);
+        if (threadIdx.x == 0) A[A_WETC * N + blockIdx.x] = wet;
+    }
 }
 
 // ---- solid voxel masks ------------------------------------------------------
@@ -953,48 +1020,30 @@ template <int P> __global__ __launch_bounds__(kBlock) void k_adj_final(KP kp, Bu
     for (int i = 0; i < 27; ++i) L.st(i, row, x, L.ld(i, row, x) + final_term<real>(pk, i, n));
 }
 
-// Deterministic accumulation: per-block sums of three arrays (a0, a2 of n
-// entries, a1 of n1), then one block adds them (fixed order) to acc[0..2].
-__global__ __launch_bounds__(kBlock) void k_adj_reduce_part(unsigned n, const double *a0, unsigned n1,
-                                                            const double *a1, const double *a2, double *part) {
-    __shared__ double s[3][kBlock];
-    // a fixed grid-stride assignment: the same sums in the same order on
-    // every call
-    double v0 = 0.0, v1 = 0.0, v2 = 0.0;
-    for (unsigned i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-        if (a0) v0 += a0[i];
-        if (a2) v2 += a2[i];
-    }
-    if (a1)
-        for (unsigned i = blockIdx.x * kBlock + threadIdx.x; i < n1; i += gridDim.x * kBlock) v1 += a1[i];
-    s[0][threadIdx.x] = v0;
-    s[1][threadIdx.x] = v1;
-    s[2][threadIdx.x] = v2;
-    __syncthreads();
-    for (int h = kBlock / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h)
-            for (int k = 0; k < 3; ++k) s[k][threadIdx.x] += s[k][threadIdx.x + h];
-        __syncthreads();
-    }
-    if (threadIdx.x < 3) part[(size_t)blockIdx.x * 3 + threadIdx.x] = s[threadIdx.x][0];
+// Per-block sums of n values (a fixed grid-stride assignment: the same sums in
+// the same order on every call).
+__global__ __launch_bounds__(kBlock) void k_adj_reduce_part(unsigned n, const double *a, double *part) {
+    double v = 0.0;
+    for (unsigned i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) v += a[i];
+    v = block_sum<kBlock>(v);
+    if (threadIdx.x == 0) part[blockIdx.x] = v;
 }
 
-__global__ __launch_bounds__(kBlock) void k_adj_reduce_final(unsigned nblk, const double *part, double *acc) {
-    __shared__ double s[3][kBlock];
+// The partial sums of a step, in a fixed order, onto acc[0..2] = kappa, wet
+// value, nu (one workgroup).
+constexpr int kFinal = 1024;
+__global__ __launch_bounds__(kFinal) void k_adj_reduce_final(unsigned nk, const double *kap, const double *nu,
+                                                             unsigned nw, const double *wet, double *acc) {
     double v[3] = {0, 0, 0};
-    for (unsigned q = threadIdx.x; q < nblk; q += kBlock)
-        for (int k = 0; k < 3; ++k) v[k] += part[(size_t)q * 3 + k];
-    for (int k = 0; k < 3; ++k) s[k][threadIdx.x] = v[k];
-    __syncthreads();
-    for (int h = kBlock / 2; h > 0; h >>= 1) {
-        if ((int)threadIdx.x < h)
-            for (int k = 0; k < 3; ++k) s[k][threadIdx.x] += s[k][threadIdx.x + h];
-        __syncthreads();
+    for (unsigned q = threadIdx.x; q < nk; q += kFinal) {
+        v[0] += kap[q];
+        v[2] += nu[q];
     }
-    if (threadIdx.x == 0) {
-        acc[0] += s[0][0];  // kappa
-        acc[1] += s[1][0];  // wet value
-        acc[2] += s[2][0];  // nu
+    for (unsigned q = threadIdx.x; q < nw; q += kFinal) v[1] += wet[q];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        v[k] = block_sum<kFinal>(v[k]);
+        if (threadIdx.x == 0) acc[k] += v[k];
     }
 }
 
@@ -1118,47 +1167,46 @@ template <class Fn> hipError_t dispatch(int prec, Fn &&fn) {
 
 constexpr unsigned kReduceBlocks = 1024;  // blocks of the gradient reduction
 
-// The chain from mu_bar (A_MUBT after k_adj_phimu; in the initialiser's
-// adjoint its local part in A_MUB) to rho_bar_total (A_RHOBT) with walls,
-// and the kappa / wet accumulation.
-hipError_t chain_tail(hipStream_t s, const KP &kp, const Bufs &b, bool with_gradient_transpose,
-                      const double *nuc) {
+// The chain from mu_bar to rho_bar_total (A_RHOBT) with walls, the kappa, wet
+// and nu sums and, in a step, the pack of the next one.  STEP: mu_bar from
+// k_adj_phimu (A_MUBT); otherwise the initialiser's adjoint, its local part
+// (A_MUB).
+template <int P, bool STEP> hipError_t chain_tail(hipStream_t s, const KP &kp, const Bufs &b) {
     const size_t N = kp.N;
     double *A = (double *)b.abuf;
-    const unsigned gN = nblocks(N), gw = nblocks(2 * (size_t)kp.plane);
-    double *mub_tot = A + (with_gradient_transpose ? A_MUBT : A_MUB) * N;
+    const unsigned gN = nblocks(N), gf = nblocks(kp.nfluid), gw = nblocks(2 * (size_t)kp.plane);
+    double *mub_tot = A + (STEP ? A_MUBT : A_MUB) * N;
     const unsigned tiles = (kp.nx + RTX - 1) / RTX * ((kp.ny + RTY - 1) / RTY);
     const int cz = march_chunk(tiles, kp.nz, 256 * 3, 3);
     const dim3 gall(tiles, (kp.nz + cz - 1) / cz);
-    const double *wetc = nullptr;
+    const double *wet = A + A_WETC * N, *nuc = STEP ? A + A_NUC * N : nullptr;
+    // one slot each holds the partial sums: no more workgroups than nodes
+    double *kap = A + A_KAPC * N, *nu = A + (kp.masked ? A_MUBT : A_RAVEB) * N;
     unsigned nwet = 0;
     if (kp.masked) {
         // mu_bar of the solid nodes back to their fluid neighbours (Eq. (36)),
         // then the Laplacian's adjoint with mu_bar zero at solid nodes
         k_adj_wall_gather_m<<<gN, kBlock, 0, s>>>(kp, b.nbr, mub_tot, mub_tot);
         k_adj_fluid_copy_m<<<gN, kBlock, 0, s>>>(kp, b.nbr, mub_tot, A + A_MUB * N);
-        k_adj_rho<true><<<gall, RNT, 0, s>>>(kp, A + A_MUB * N, A + A_RHOB * N, b.rho, A + A_RHOBT * N,
-                                             A + A_KAPC * N, cz, b.nbr);
+        k_adj_rho<true><<<gall, RNT, 0, s>>>(kp, A + A_MUB * N, A + A_RHOB * N, b.rho, nuc, A + A_RHOBT * N, kap,
+                                             nu, cz, b.nbr);
         k_adj_wall_rho_solid_m<<<gN, kBlock, 0, s>>>(kp, b.nbr, b.rho, A + A_RHOBT * N, A + A_RAVEB * N,
                                                      A + A_WETC * N);
         k_adj_wall_gather_m<<<gN, kBlock, 0, s>>>(kp, b.nbr, A + A_RAVEB * N, A + A_RHOBT * N);
-        wetc = A + A_WETC * N;
-        nwet = (unsigned)N;
+        nwet = gN < kReduceBlocks ? gN : kReduceBlocks;
+        k_adj_reduce_part<<<nwet, kBlock, 0, s>>>((unsigned)N, wet, b.agrad + 8);
+        wet = b.agrad + 8;
     } else {
         if (kp.walls) k_adj_wall_gather<<<gw, kBlock, 0, s>>>(kp, mub_tot, mub_tot);
-        k_adj_rho<false><<<gall, RNT, 0, s>>>(kp, mub_tot, A + A_RHOB * N, b.rho, A + A_RHOBT * N, A + A_KAPC * N,
+        k_adj_rho<false><<<gall, RNT, 0, s>>>(kp, mub_tot, A + A_RHOB * N, b.rho, nuc, A + A_RHOBT * N, kap, nu,
                                               cz, nullptr);
-        if (kp.walls) {
-            k_adj_wall_rho_solid<<<gw, kBlock, 0, s>>>(kp, b.rho, A + A_RHOBT * N, A + A_RAVEB * N, A + A_WETC * N);
-            k_adj_wall_gather<<<gw, kBlock, 0, s>>>(kp, A + A_RAVEB * N, A + A_RHOBT * N);
-            wetc = A + A_WETC * N;
-            nwet = 2u * (unsigned)kp.plane;
-        }
+        if (kp.walls) nwet = gf;
     }
-    double *part = b.agrad + 8;
-    const unsigned gr = gN < kReduceBlocks ? gN : kReduceBlocks;
-    k_adj_reduce_part<<<gr, kBlock, 0, s>>>((unsigned)N, A + A_KAPC * N, nwet, wetc, nuc, part);
-    k_adj_reduce_final<<<1, kBlock, 0, s>>>(gr, part, b.agrad);
+    if (kp.walls)
+        k_adj_tail<P, STEP, true><<<gf, kBlock, 0, s>>>(kp, b);
+    else if (STEP)
+        k_adj_tail<P, STEP, false><<<gf, kBlock, 0, s>>>(kp, b);
+    k_adj_reduce_final<<<1, kFinal, 0, s>>>(gall.x * gall.y, kap, nu, nwet, wet, b.agrad);
     return hipGetLastError();
 }
 
@@ -1208,8 +1256,6 @@ hipError_t launch_adj_step(hipStream_t s, int prec, const KP &kp, const Bufs &b,
         hipError_t e = launch_aux(s, prec, kp, fb, 0, true);
         if (e != hipSuccess) return e;
     }
-    const unsigned gf = nblocks(kp.nfluid);
-    double *A = (double *)b.abuf;
     return dispatch(prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         if (kp.masked) {
@@ -1226,10 +1272,7 @@ hipError_t launch_adj_step(hipStream_t s, int prec, const KP &kp, const Bufs &b,
             }
             phimu<P, false>(s, kp, b);
         }
-        hipError_t r = chain_tail(s, kp, b, true, A + A_NUC * (size_t)kp.N);
-        if (r != hipSuccess) return r;
-        k_adj_pack<P><<<gf, kBlock, 0, s>>>(kp, b);
-        return hipGetLastError();  // lambda(t) = direct part; its last term is pending
+        return chain_tail<P, true>(s, kp, b);  // lambda(t) = direct part; its last term is pending
     });
 }
 
@@ -1250,7 +1293,7 @@ hipError_t launch_adj_init(hipStream_t s, int prec, const KP &kp, const Bufs &b,
     return dispatch(prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         k_adj_init_local<P><<<gN, kBlock, 0, s>>>(kp, b, b.lam[lcur], u0);
-        hipError_t r = chain_tail(s, kp, b, false, nullptr);
+        hipError_t r = chain_tail<P, false>(s, kp, b);
         if (r != hipSuccess) return r;
         k_adj_init_out<<<gN, kBlock, 0, s>>>(kp, b, (const double *)b.abuf + A_RHOBT * (size_t)kp.N, out);
         return hipGetLastError();
