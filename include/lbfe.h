@@ -318,6 +318,16 @@ int lbfe_adjoint_step(lbfe_ctx *ctx, const void *state_t_dev);
  * state_t_dev. */
 int lbfe_aux_bytes(const lbfe_ctx *ctx, size_t *bytes);
 int lbfe_step_aux(lbfe_ctx *ctx, void *aux_dev);
+
+/* lbfe_step_aux from a stored state to a stored state: the step from
+ * state_in_dev = f(step) (only read) into state_out_dev, with the record of
+ * state_in_dev in aux_dev; the context's own state stays as it is.  With
+ * state_out_dev NULL the result becomes the context's state, f(step + 1).
+ * Same bits as lbfe_set_state, lbfe_step_aux and lbfe_get_state, without the
+ * copies; entries of solid nodes of state_out_dev are not written.  Both
+ * states: caller-owned device memory of lbfe_state_bytes, 256-byte aligned,
+ * not overlapping (E_INVAL otherwise where that can be seen). */
+int lbfe_step_record(lbfe_ctx *ctx, const void *state_in_dev, int64_t step, void *state_out_dev, void *aux_dev);
 int lbfe_adjoint_step_aux(lbfe_ctx *ctx, const void *state_t_dev, const void *aux_dev);
 
 /* Pull lambda(0) back through the initialiser of lbfe_init_density given

@@ -152,18 +152,27 @@ class LBFEFunction(torch.autograd.Function):
         else:
             for s0 in sorted(ctx.checkpoints, reverse=True):
                 s1 = min(s0 + K, cfg.steps)
-                sim.set_state(ctx.checkpoints[s0], s0)
                 # states[k] = f(s0 + k) for the states that are stepped from
                 # (with the record of their fields if kept); the segment's
-                # last state stays in the simulation
+                # last state is the simulation's
                 states, recs = [ctx.checkpoints[s0]], []
+                if not (cfg.keep_aux and cfg.solid is None and s1 - s0 > 1):
+                    sim.set_state(ctx.checkpoints[s0], s0)
                 for t in range(s0, s1 - 1):
+                    last = t + 1 == s1 - 1
                     if cfg.keep_aux:
                         recs.append(sim.aux_record())
+                    if cfg.keep_aux and cfg.solid is None:
+                        # from stored state to stored state, no copies
+                        if not last:
+                            states.append(torch.empty_like(states[0]))
+                        sim.step_record(states[t - s0], t, recs[-1], None if last else states[-1])
+                        continue
+                    if cfg.keep_aux:
                         sim.step_aux(recs[-1])
                     else:
                         sim.step(1)
-                    if t + 1 < s1 - 1:
+                    if not last:
                         states.append(sim.get_state())
                 sim.adjoint_step(None)  # f(s1 - 1)
                 for t in range(s1 - 2, s0 - 1, -1):

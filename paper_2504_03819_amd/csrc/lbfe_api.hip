@@ -830,6 +830,31 @@ int lbfe_step_aux(lbfe_ctx *c, void *aux) {
     return LBFE_OK;
 }
 
+int lbfe_step_record(lbfe_ctx *c, const void *in, int64_t step, void *out, void *aux) {
+    int r = need_mask(c);
+    if (r) return r;
+    if (!in) return fail(c, LBFE_E_INVAL, "null state");
+    if (((uintptr_t)in & 255u) || ((uintptr_t)out & 255u))
+        return fail(c, LBFE_E_INVAL, "states must be 256-byte aligned");
+    if (in == out) return fail(c, LBFE_E_INVAL, "the step needs two states");
+    if (step < 0) return fail(c, LBFE_E_INVAL, "step < 0");
+    if (!aux || ((uintptr_t)aux & 255u)) return fail(c, LBFE_E_INVAL, "aux record null or not 256-byte aligned");
+    // without `out` into the lattice that is not current (it may hold `in`)
+    const int to = in == c->b.f[1 - c->cur] ? c->cur : 1 - c->cur;
+    Bufs b = with_aux(c, aux);
+    b.f[0] = const_cast<void *>(in);
+    b.f[1] = out ? out : c->b.f[to];
+    hipError_t e = launch_step(c->stream, c->p.precision, c->kp, b, 0, false, true, true, nullptr);
+    if (e != hipSuccess) return hip_fail(c, e, "step_record");
+    c->aux_ok = false;  // mu0 of the workspace is the given state's
+    if (!out) {
+        c->cur = to;
+        c->step = step + 1;
+        c->initialised = true;
+    }
+    return LBFE_OK;
+}
+
 int lbfe_adjoint_step_aux(lbfe_ctx *c, const void *ft, const void *aux) {
     int r = need_bound(c);
     if (r) return r;

@@ -85,6 +85,7 @@ def lib():
         "lbfe_adjoint_grads": (c_int, [V, POINTER(c_double)]),
         "lbfe_aux_bytes": (c_int, [V, POINTER(c_size_t)]),
         "lbfe_step_aux": (c_int, [V, V]),
+        "lbfe_step_record": (c_int, [V, V, c_int64, V, V]),
         "lbfe_adjoint_step_aux": (c_int, [V, V, V]),
         "lbfe_last_error": (ctypes.c_char_p, [V]),
         "lbfe_destroy": (c_int, [V]),
@@ -306,6 +307,11 @@ class Simulation:
     def step_aux(self, record):
         """One step; the fields of the state before it go into `record`."""
         self._check(lib().lbfe_step_aux(self._ctx, _ptr(record)))
+
+    def step_record(self, state, step, record, out=None):
+        """step_aux from the stored state f(step) into the stored state `out`,
+        or into the simulation's own state if None."""
+        self._check(lib().lbfe_step_record(self._ctx, _ptr(state), c_int64(int(step)), _ptr(out), _ptr(record)))
 
     def adjoint_step_aux(self, state_t, record):
         """adjoint_step with the record that step_aux left for state_t."""

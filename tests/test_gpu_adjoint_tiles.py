@@ -13,7 +13,7 @@ import torch
 
 from gpu_util import droplet_rho, make_sim, oracle_params, rel_err, say
 from oracle import eos, lbm
-from paper_2504_03819_amd import inputs
+from paper_2504_03819_amd import inputs, lbfe
 from test_gpu_adjoint import _oracle_vjp
 
 pytestmark = pytest.mark.gpu
@@ -73,3 +73,38 @@ def test_repeated_state_has_the_repeated_adjoint(precision):
     n = reps[0] * reps[1] * reps[2]
     for k in ("kappa", "nu"):  # sums of 1.3e6 signed terms of magnitudes up to ~1e2 of the mean
         assert abs(gb[k] - n * ga[k]) < 1e-9 * abs(n * ga[k]), (k, ga[k], gb[k])
+
+
+@pytest.mark.parametrize("walls", ["none", "still", "moving"])
+@pytest.mark.parametrize("form", ["fp64", "fp32", "fp16dev_f0fp32"])
+def test_step_record_is_step_aux_without_the_copies(form, walls):
+    """Steps between stored states (and at last into the context) against
+    set_state, step_aux and get_state: the same states at the fluid nodes, the
+    same records and lambda."""
+    nz, ny, nx = shape = (9, 10, 21)
+    T = eos.temperature(0.8)
+    kw = dict(nx=nx, ny=ny, nz=nz, T=T, precision=form, adjoint=1)
+    if walls != "none":
+        kw.update(walls_z=1, wet_mode=1, wet_value=1.2)
+    if walls == "moving":
+        kw.update(wall_u=(0.01, -0.02, 0.015, 0.0))
+    a, b = make_sim(**kw), make_sim(**kw)
+    a.init_density(torch.tensor(droplet_rho(shape, T, walls=walls != "none", radius=3.0)))
+    first = a.get_state()
+    sa, ra, sb, rb = [first], [], [first], []
+    for t in range(3):
+        ra.append(a.aux_record().zero_())
+        a.step_aux(ra[-1])
+        sa.append(a.get_state())
+        rb.append(b.aux_record().zero_())
+        sb.append(None if t == 2 else torch.zeros_like(first))
+        b.step_record(sb[t], t, rb[-1], sb[-1])
+    assert torch.equal(a.get_state(), b.get_state()) and b.step_count == 3
+    for t in range(3):
+        assert torch.equal(sa[t], sb[t]) and torch.equal(ra[t], rb[t]), t
+    assert torch.equal(a.fields()["mu"], b.fields()["mu"])
+    bad = torch.zeros(first.numel() + 8, dtype=torch.uint8, device="cuda:0")[8:]
+    for args in ((first, 0, rb[0], first), (bad, 0, rb[0]), (first, -1, rb[0]), (first, 0, rb[0], bad)):
+        with pytest.raises(lbfe.LBFEError) as e:
+            b.step_record(*args)
+        assert e.value.code == lbfe.E_INVAL
