@@ -1086,7 +1086,9 @@ __global__ __launch_bounds__(kBlock) void k_adj_get(KP kp, Bufs b, const void *l
 
 // Initialiser f = T(u0)^{-1} k_eq(rho0, p_m): k_eq_bar = T(u0)^{-T} lambda(0);
 // rho_bar_local = k_eq_bar_000, mu_bar = p_m_bar / 3 (fluid), 0 at solid.
-template <int P>
+// PEND: the last term of lambda(0) is added as it is read (k_adj_final would
+// read and write the lattice for it: 224 us at 192x192x96 in FP32).
+template <int P, bool PEND>
 __global__ __launch_bounds__(kBlock) void k_adj_init_local(KP kp, Bufs b, const void *lam, const double *u0) {
     using real = real_t<P>;
     const unsigned n = blockIdx.x * kBlock + threadIdx.x;
@@ -1104,6 +1106,11 @@ __global__ __launch_bounds__(kBlock) void k_adj_init_local(KP kp, Bufs b, const 
     real l[27];
 #pragma unroll
     for (int i = 0; i < 27; ++i) l[i] = L.ld(i, row, x);
+    if constexpr (PEND) {
+        const Pack4<real> *pk = (const Pack4<real> *)((const double *)b.abuf + A_PACK * N);
+#pragma unroll
+        for (int i = 0; i < 27; ++i) l[i] += final_term<real>(pk, i, n);
+    }
     real ux = 0, uy = 0, uz = 0;
     if (u0) {
         ux = (real)u0[n];
@@ -1215,12 +1222,15 @@ template <int P, bool STEP> hipError_t chain_tail(hipStream_t s, const KP &kp, c
 size_t adjoint_aux_bytes(int, size_t N) { return (size_t)A_COUNT * 8 * N; }
 size_t adjoint_grad_slots() { return 3; }
 
-hipError_t launch_adj_seed(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, const double *g) {
-    hipError_t e = launch_fill(s, b.agrad, 64);
-    if (e != hipSuccess) return e;
-    // solid-node entries of the adjoint arrays must read as zero
-    e = launch_fill(s, b.abuf, adjoint_aux_bytes(prec, kp.N));
-    if (e != hipSuccess) return e;
+hipError_t launch_adj_seed(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, bool clear,
+                           const double *g) {
+    if (clear) {  // a workspace that a sweep has used
+        hipError_t e = launch_fill(s, b.agrad, 64);
+        if (e != hipSuccess) return e;
+        // solid-node entries of the adjoint arrays must read as zero
+        e = launch_fill(s, b.abuf, adjoint_aux_bytes(prec, kp.N));
+        if (e != hipSuccess) return e;
+    }
     return dispatch(prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         k_adj_seed<P><<<nblocks(kp.N), kBlock, 0, s>>>(kp, b, g, b.lam[lcur]);
@@ -1228,11 +1238,15 @@ hipError_t launch_adj_seed(hipStream_t s, int prec, const KP &kp, const Bufs &b,
     });
 }
 
-hipError_t launch_adj_seed_pop(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, const double *g) {
-    hipError_t e = launch_fill(s, b.agrad, 64);
-    if (e != hipSuccess) return e;
-    e = launch_fill(s, b.abuf, adjoint_aux_bytes(prec, kp.N));
-    if (e != hipSuccess) return e;
+hipError_t launch_adj_seed_pop(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, bool clear,
+                               const double *g) {
+    if (clear) {  // a workspace that a sweep has used
+        hipError_t e = launch_fill(s, b.agrad, 64);
+        if (e != hipSuccess) return e;
+        // solid-node entries of the adjoint arrays must read as zero
+        e = launch_fill(s, b.abuf, adjoint_aux_bytes(prec, kp.N));
+        if (e != hipSuccess) return e;
+    }
     return dispatch(prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         k_adj_seed_pop<P><<<nblocks(kp.N), kBlock, 0, s>>>(kp, b, g, b.lam[lcur]);
@@ -1284,15 +1298,18 @@ hipError_t launch_adj_finalize(hipStream_t s, int prec, const KP &kp, const Bufs
     });
 }
 
-hipError_t launch_adj_init(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, const double *rho0,
-                           const double *u0, double *out) {
+hipError_t launch_adj_init(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, bool pending,
+                           const double *rho0, const double *u0, double *out) {
     // forward initialiser quantities: rho (with wall densities) and mu
     const unsigned gN = nblocks(kp.N);
     hipError_t e = launch_init_aux(s, kp, b, rho0);
     if (e != hipSuccess) return e;
     return dispatch(prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
-        k_adj_init_local<P><<<gN, kBlock, 0, s>>>(kp, b, b.lam[lcur], u0);
+        if (pending)
+            k_adj_init_local<P, true><<<gN, kBlock, 0, s>>>(kp, b, b.lam[lcur], u0);
+        else
+            k_adj_init_local<P, false><<<gN, kBlock, 0, s>>>(kp, b, b.lam[lcur], u0);
         hipError_t r = chain_tail<P, false>(s, kp, b);
         if (r != hipSuccess) return r;
         k_adj_init_out<<<gN, kBlock, 0, s>>>(kp, b, (const double *)b.abuf + A_RHOBT * (size_t)kp.N, out);

@@ -135,8 +135,10 @@ hipError_t launch_init_aux_mask(hipStream_t s, const KP &kp, const Bufs &b, cons
 // adjoint (lbfe_adjoint.hip)
 size_t adjoint_aux_bytes(int prec, size_t N);
 size_t adjoint_grad_slots();
-hipError_t launch_adj_seed(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, const double *dLdrho);
-hipError_t launch_adj_seed_pop(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, const double *lam);
+hipError_t launch_adj_seed(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, bool clear,
+                           const double *dLdrho);
+hipError_t launch_adj_seed_pop(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, bool clear,
+                               const double *lam);
 hipError_t launch_adj_get(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, double *out);
 // recompute: evaluate the forward fields of ft first (else b holds them);
 // pending: lam[lcur] holds only the direct part of lambda(t+1).  Leaves
@@ -145,7 +147,7 @@ hipError_t launch_adj_step(hipStream_t s, int prec, const KP &kp, const Bufs &b,
                            bool recompute, bool pending);
 // applies the pending last term to lam[lcur] in place
 hipError_t launch_adj_finalize(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur);
-hipError_t launch_adj_init(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, const double *rho0,
+hipError_t launch_adj_init(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, bool pending, const double *rho0,
                            const double *u0, double *out);
 
 inline unsigned nblocks(size_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }

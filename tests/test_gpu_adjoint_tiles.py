@@ -108,3 +108,31 @@ def test_step_record_is_step_aux_without_the_copies(form, walls):
         with pytest.raises(lbfe.LBFEError) as e:
             b.step_record(*args)
         assert e.value.code == lbfe.E_INVAL
+
+
+@pytest.mark.parametrize("form", ["fp64", "fp32"])
+def test_init_gradient_with_the_last_term_pending(form):
+    """lbfe_adjoint_init_density adds the last term of lambda(0) as it reads
+    it; reading lambda out first (which completes it in place) gives the same
+    gradients, a second call the same again, and a second seed of a used
+    workspace those of a fresh one."""
+    nz, ny, nx = shape = (8, 9, 19)
+    T = eos.temperature(0.8)
+    rho0 = torch.tensor(droplet_rho(shape, T, walls=True, radius=3.0))
+    g = torch.tensor(inputs.uniform_noise(shape, 1.0, 5), device="cuda:0")
+    kw = dict(nx=nx, ny=ny, nz=nz, T=T, precision=form, adjoint=1, walls_z=1, wet_mode=1, wet_value=1.2)
+    out = []
+    for read_first in (False, True):
+        s = make_sim(**kw)
+        for _ in range(2):  # the second time on used arrays
+            s.init_density(rho0)
+            f = s.get_state()
+            s.adjoint_seed(g)
+            s.adjoint_step(f)
+            if read_first:
+                s.adjoint_state()
+            a = s.adjoint_init_density()
+            out.append((a, s.adjoint_grads()))
+        assert torch.equal(s.adjoint_init_density(), a)
+    for a, gr in out[1:]:
+        assert torch.equal(a, out[0][0]) and gr == out[0][1]
