@@ -209,8 +209,8 @@ int lbfe_init_density(lbfe_ctx *ctx, const double *rho0_dev, const double *u0_de
  * bounce-back.  Checks the divergence flag every check_every steps and at
  * the end (a synchronisation): E_DIVERGED, with the step in lbfe_last_error.
  * Each step runs as params.step_path says: a moments pass, the stencil
- * chain and a collide-stream pass (LBFE_PATH_TWO_PASS; on small grids chain
- * and collide-stream are one kernel), or the stencil chain and a
+ * chain and a collide-stream pass (LBFE_PATH_TWO_PASS; on small grids chain,
+ * collide-stream and the wall terms are one kernel), or the stencil chain and a
  * collide-stream kernel that also forms the next step's density and momentum
  * (LBFE_PATH_FUSED, no moments pass), or through the moment state
  * (LBFE_PATH_STATE); all give bitwise identical states. */

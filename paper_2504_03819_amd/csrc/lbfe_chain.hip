@@ -767,7 +767,13 @@ __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__rest
 // ---------------------------------------------------------------------------
 // With a storage form P the workgroup then collides its own nodes and
 // push-streams them (k_collide's node, same code): F, mu and Q stay in LDS and
-// registers, and the step is two launches instead of three.
+// registers.  Between walls it also forms the density of the solid planes from
+// the fluid plane beside them (as k_wall_rho), and with moving walls applies
+// their term to the node's reflected populations after storing them (as
+// k_wall_move): two launches a step instead of five (us per step with the wall
+// kernels apart / inside, moving walls: FP64 32^3 26.2 / 17.3, 101 x 67 x 53 77.0
+// / 68.1; FP32 64^3 37.5 / 30.4; still walls: FP64 32^3 20.5 / 17.6, 64^3 48.8 /
+// 46.1, 80^3 81.6 / 82.5).
 // ---------------------------------------------------------------------------
 constexpr int kFields = -1;  // P: mu, F and Q to memory, no collision
 template <int P, class real, bool WALLS, int TX, int TY, int CZ, int NT, bool NTL>
@@ -886,6 +892,19 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
             for (int m = 0; m < MR; ++m)
                 if (tid + m * NT < NR) sr[z][tid + m * NT] = pr[m][z];
     }
+    if constexpr (STEP && WALLS) {  // the density of the solid planes, as k_wall_rho forms it
+        auto wall = [&](int ps) {
+#pragma unroll
+            for (int m = 0; m < MR; ++m) {
+                const int r = tid + m * NT;
+                if (r < NR)
+                    sr[ps - (zs - 3)][r] =
+                        wall_rho(kp, rho, wrap1(x0 + r % WR - HR, kp.nx), wrap1(y0 + r / WR - HR, kp.ny), ps);
+            }
+        };
+        if (zs <= 3) wall(0);
+        if (zs + CZ + 2 >= kp.nz - 1) wall(kp.nz - 1);
+    }
     __syncthreads();
 
     // mu of planes zs - 2 .. zs + CZ + 1 (fluid ones)
@@ -905,9 +924,7 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
             const double v = m0[m][z] - kp.kappa * 6.0 * (s27 - r0);
             if (fluid(p)) {
                 sm[z][r] = v;
-                // (with moving walls mu beside them: k_wall_move applies the wall term)
-                if (own && p >= zs && p < ze && (!STEP || (WALLS && kp.moving && (p == 1 || p == kp.nz - 2))))
-                    mu[pb[z + 1] + om[m]] = v;
+                if (!STEP && own && p >= zs && p < ze) mu[pb[z + 1] + om[m]] = v;
             }
             P0 = P1;
             P1 = P2;
@@ -1003,6 +1020,9 @@ __global__ __launch_bounds__(NT) void k_chain_block(KP kp, const double *__restr
                 else
                     fout.st(i, nb.row(cyi(i), c3), nb.xo(cxi(i)), f[i]);
             }
+            if (WALLS && kp.moving && (wall_lo || wall_hi))
+                wall_move_node<P>(kp, fout, sr[cz + 3][(b + HR) * WR + a + HR], sm[cz + 2][(b + HM) * WM + a + HM], z,
+                                  row, x);
         }
         return;
     }

@@ -521,4 +521,61 @@ __device__ inline void wall_equilibrium(real rho, real pm, real ux, real uy, rea
     cm_inverse(feq, ux, uy, (real)0);
 }
 
+// Moving walls: the term of k_wall_move at a node of the first or last fluid
+// plane, from its rho and mu.
+template <int P>
+__device__ inline void wall_move_node(const KP &kp, const Pops<P> &f, double rho, double mu, int z, unsigned row,
+                                      unsigned x) {
+    using real = typename Pol<P>::real;
+    const real r = (real)rho, pm = (real)((1.0 + mu) * (1.0 / 3.0));
+    real fe[27];
+    for (int w = 0; w < 2; ++w) {  // bottom, top
+        const bool hit = w == 0 ? z == 1 : z == kp.nz - 2;
+        if (!hit) continue;
+        wall_equilibrium(r, pm, (real)kp.wall_u[2 * w], (real)kp.wall_u[2 * w + 1], fe);
+#pragma unroll
+        for (int i = 0; i < 27; ++i) {
+            const int cz = czi(i);
+            if ((w == 0 && cz < 0) || (w == 1 && cz > 0))
+                f.st(26 - i, row, x, f.ld(26 - i, row, x) - (fe[i] - fe[26 - i]));
+        }
+    }
+}
+
+// Weighted average over fluid neighbours of a solid node (Eqs. (36)/(37));
+// neighbours outside the box or on the solid planes have s_w = 0.
+__device__ inline double wall_average(const KP &kp, const double *g, int x, int y, int zs) {
+    const int xm = x == 0 ? kp.nx - 1 : x - 1, xp = x == kp.nx - 1 ? 0 : x + 1;
+    const int ym = y == 0 ? kp.ny - 1 : y - 1, yp = y == kp.ny - 1 ? 0 : y + 1;
+    const int X[3] = {xm, x, xp}, Y[3] = {ym, y, yp};
+    double num = 0.0, den = 0.0;
+#pragma unroll
+    for (int cz = -1; cz <= 1; ++cz) {
+        const int zz = zs + cz;
+        if (zz < 1 || zz > kp.nz - 2) continue;
+#pragma unroll
+        for (int cy = -1; cy <= 1; ++cy)
+#pragma unroll
+            for (int cx = -1; cx <= 1; ++cx) {
+                const double w = wq(cx, cy, cz);
+                num += w * g[(size_t)zz * kp.plane + (unsigned)Y[cy + 1] * kp.nx + X[cx + 1]];
+                den += w;
+            }
+    }
+    return num / den;
+}
+
+// Density of solid node (x, y) of wall plane zs, Eqs. (37)-(38).
+__device__ inline double wall_rho(const KP &kp, const double *rho, int x, int y, int zs) {
+    const double rave = wall_average(kp, rho, x, y, zs);
+    double out = rave;
+    if (rave >= kp.lo && rave <= kp.hi) {  // contact-line window
+        if (kp.wet_mode == LBFE_WET_PHI)
+            out = fmin(fmax(kp.wet_value * rave, kp.lo), kp.hi);
+        else if (kp.wet_mode == LBFE_WET_DELTA)
+            out = fmin(fmax(rave - kp.wet_value, kp.lo), kp.hi);
+    }
+    return out;
+}
+
 }  // namespace lbfe

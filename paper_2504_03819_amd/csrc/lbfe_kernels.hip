@@ -69,29 +69,6 @@ __global__ __launch_bounds__(kBlock) void k_moments(KP kp, const void *fq, doubl
     if (!(r > 0.0 && kp.b * r < 1.0)) *flag = 1;
 }
 
-// Weighted average over fluid neighbours of a solid node (Eqs. (36)/(37));
-// neighbours outside the box or on the solid planes have s_w = 0.
-__device__ inline double wall_average(const KP &kp, const double *g, int x, int y, int zs) {
-    const int xm = x == 0 ? kp.nx - 1 : x - 1, xp = x == kp.nx - 1 ? 0 : x + 1;
-    const int ym = y == 0 ? kp.ny - 1 : y - 1, yp = y == kp.ny - 1 ? 0 : y + 1;
-    const int X[3] = {xm, x, xp}, Y[3] = {ym, y, yp};
-    double num = 0.0, den = 0.0;
-#pragma unroll
-    for (int cz = -1; cz <= 1; ++cz) {
-        const int zz = zs + cz;
-        if (zz < 1 || zz > kp.nz - 2) continue;
-#pragma unroll
-        for (int cy = -1; cy <= 1; ++cy)
-#pragma unroll
-            for (int cx = -1; cx <= 1; ++cx) {
-                const double w = wq(cx, cy, cz);
-                num += w * g[(size_t)zz * kp.plane + (unsigned)Y[cy + 1] * kp.nx + X[cx + 1]];
-                den += w;
-            }
-    }
-    return num / den;
-}
-
 __global__ __launch_bounds__(kBlock) void k_wall_rho(KP kp, double *rho) {
     const unsigned idx = blockIdx.x * kBlock + threadIdx.x;
     if (idx >= 2 * kp.plane) return;
@@ -99,15 +76,7 @@ __global__ __launch_bounds__(kBlock) void k_wall_rho(KP kp, double *rho) {
     const unsigned p = idx - (side ? kp.plane : 0u);
     const int y = (int)(p / (unsigned)kp.nx), x = (int)(p - (unsigned)y * kp.nx);
     const int zs = side ? kp.nz - 1 : 0;
-    const double rave = wall_average(kp, rho, x, y, zs);
-    double out = rave;
-    if (rave >= kp.lo && rave <= kp.hi) {  // contact-line window
-        if (kp.wet_mode == LBFE_WET_PHI)
-            out = fmin(fmax(kp.wet_value * rave, kp.lo), kp.hi);
-        else if (kp.wet_mode == LBFE_WET_DELTA)
-            out = fmin(fmax(rave - kp.wet_value, kp.lo), kp.hi);
-    }
-    rho[(size_t)zs * kp.plane + p] = out;
+    rho[(size_t)zs * kp.plane + p] = wall_rho(kp, rho, x, y, zs);
 }
 
 // mu = mu0(rho) - kappa lap_h rho, lap_h g = 6 sum_i w_i (g(x+c_i) - g(x)).
@@ -178,7 +147,6 @@ __global__ __launch_bounds__(kBlock) void k_collide(KP kp, const void *fin_q, vo
 // of f(t), the state k_collide collided.
 template <int P> __global__ __launch_bounds__(kBlock) void k_wall_move(KP kp, void *fq, const double *rho,
                                                                        const double *mu) {
-    using real = real_t<P>;
     const unsigned idx = blockIdx.x * kBlock + threadIdx.x;
     if (idx >= 2 * kp.plane) return;
     const int side = idx >= kp.plane;  // 0: next to the bottom wall, 1: top
@@ -188,20 +156,7 @@ template <int P> __global__ __launch_bounds__(kBlock) void k_wall_move(KP kp, vo
     const unsigned y = p / (unsigned)kp.nx, x = p - y * (unsigned)kp.nx;
     const size_t n = (size_t)z * kp.plane + p;
     const unsigned row = (unsigned)z * (unsigned)kp.ny + y;
-    const Pops<P> f(fq, kp);
-    const real r = (real)rho[n], pm = (real)((1.0 + mu[n]) * (1.0 / 3.0));
-    real fe[27];
-    for (int w = 0; w < 2; ++w) {  // bottom, top
-        const bool hit = w == 0 ? z == 1 : z == kp.nz - 2;
-        if (!hit) continue;
-        wall_equilibrium(r, pm, (real)kp.wall_u[2 * w], (real)kp.wall_u[2 * w + 1], fe);
-#pragma unroll
-        for (int i = 0; i < 27; ++i) {
-            const int cz = czi(i);
-            if ((w == 0 && cz < 0) || (w == 1 && cz > 0))
-                f.st(26 - i, row, x, f.ld(26 - i, row, x) - (fe[i] - fe[26 - i]));
-        }
-    }
+    wall_move_node<P>(kp, Pops<P>(fq, kp), rho[n], mu[n], z, row, x);
 }
 
 // Moving walls on the fused path.  k_fused reflects at the walls without the
@@ -452,7 +407,7 @@ hipError_t aux_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool re
 template <int P>
 hipError_t step_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool fused, bool refresh, bool keep,
                      hipEvent_t *ev) {
-    const bool block = kp.step_block && !fused && !keep;  // chain and collide in one launch
+    const bool block = kp.step_block && !fused && !keep;  // wall density, chain, collide, wall term in one launch
     const unsigned gf = nblocks(kp.nfluid), gw = nblocks(2 * (size_t)kp.plane);
     auto mark = [&](int k) {
         if (ev) (void)hipEventRecord(ev[k], s);
@@ -460,7 +415,7 @@ hipError_t step_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool f
     mark(0);
     if (refresh || !fused) {
         moments_pass<P>(s, kp, b, cur);
-        if (kp.walls) k_wall_rho<<<gw, kBlock, 0, s>>>(kp, b.rho);
+        if (kp.walls && !block) k_wall_rho<<<gw, kBlock, 0, s>>>(kp, b.rho);
     }
     mark(1);
     hipError_t e = block ? hipSuccess : launch_chain(s, P, kp, b);
@@ -469,7 +424,6 @@ hipError_t step_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool f
     if (block) {
         e = launch_step_block(s, P, kp, b, cur);
         if (e != hipSuccess) return e;
-        if (kp.moving) k_wall_move<P><<<gw, kBlock, 0, s>>>(kp, b.f[1 - cur], b.rho, b.mu);
     } else if (fused) {
         if (kp.moving) k_wall_keep<<<nblocks(kp.plane), kBlock, 0, s>>>(kp, b.rho);
         e = launch_fused(s, P, kp, b, cur);
