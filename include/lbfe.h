@@ -223,7 +223,7 @@ int lbfe_step(lbfe_ctx *ctx, int64_t nsteps);
  * only after the state was set from outside), 1 stencil chain (mu, force,
  * Q; zero where it runs inside the collide kernel), 2 collide-stream (fused
  * path: with the next step's moments), 3 wall density after the step (fused
- * path, walls only).  On the state path: 0 the moments passes (with the
+ * path, walls only; zero on large grids, whose chain forms it).  On the state path: 0 the moments passes (with the
  * populations at the end and the wall density), 1 the chains, 2 the collide
  * passes (the first from the populations), 3 zero.  Synchronises after every
  * step (host array). */

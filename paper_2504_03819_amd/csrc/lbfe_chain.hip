@@ -14,9 +14,9 @@
 //   d_x g   = 1/2 Wz (Dx Wy g),  d_y g = 1/2 Wz (Wx Dy g),  d_z g = 1/2 Dz (Wx Wy g)
 // with W the D1Q3 weights and D g = g(+1) - g(-1).  Three kernels sum in this
 // order, so all of them give the same bits: k_chain_block for small grids,
-// k_chain_march for periodic ones, k_chain between walls.  Outputs per fluid
-// node: mu (double), F and Q (compute precision); mu is also written at the
-// solid planes.
+// k_chain_march for large ones, k_wall_planes for mu of the solid planes of a
+// large walled grid.  Outputs per fluid node: mu (double), F and Q (compute
+// precision); mu is also written at the solid planes.
 #include <type_traits>
 
 #include "lbfe_device.h"
@@ -25,14 +25,6 @@ namespace lbfe {
 namespace {
 
 constexpr int TX = 64, TY = 16, NTC = TX * TY;  // 1024 threads, one workgroup per CU (LDS)
-constexpr int CB = TX * TY;                            // threads: one per tile column
-constexpr int WR = TX + 8, HR = TY + 8, NR = WR * HR;  // rho region (halo 4)
-constexpr int WM = TX + 6, HM = TY + 6, NM = WM * HM;  // mu region (halo 3)
-constexpr int WP = TX + 2, HP = TY + 2, NP = WP * HP;  // phi region (halo 1)
-constexpr int MR = (NR + CB - 1) / CB;         // rho points per thread
-constexpr int MM = (NM + CB - 1) / CB;         // mu points per thread
-constexpr int MP = (NP + CB - 1) / CB;         // phi points per thread
-constexpr int NRP = MR * CB;                   // rho plane in LDS, padded to whole rounds
 constexpr double A1 = 1.0 / 6.0, A0 = 2.0 / 3.0;       // D1Q3 weights
 
 // Branch-free global access: raw buffer loads/stores through a descriptor
@@ -66,7 +58,6 @@ __device__ inline int wrap(int v, int n) {
     v %= n;
     return v < 0 ? v + n : v;
 }
-__device__ inline int slot3(int p) { return ((p % 3) + 3) % 3; }
 
 // Wx Wy g of the 3x3 in-plane neighbourhood of index c in a row-major LDS
 // plane with row stride W.
@@ -133,307 +124,6 @@ __device__ inline void q_of(real Xa, real Xb, real Xc, real Ya, real Yb, real Yc
     qz = h * (Zc - Za);
 }
 
-// The march between walls: each workgroup owns a 64 x 16 column tile and
-// marches in z over a chunk of planes.  LDS holds a ring of three rho planes
-// (tile + 4-node halo), two mu planes (3-node halo) and one phi plane (1-node
-// halo).  Iteration k of the march loads rho(k+3), evaluates mu(k+2) and the
-// in-plane parts of mu(k+2), then F and phi at k+1 and the in-plane parts of
-// phi(k+1), and Q at k; global loads run ahead of their use.  (k_chain_march
-// with the wall planes spills at 16 waves, 192x192x96 FP32 68 against 67 us,
-// and in FP64 its five rho planes do not fit the LDS.)
-template <class real>
-__global__ __launch_bounds__(CB) void k_chain(KP kp, const double *__restrict__ rho, const double *__restrict__ mu0,
-                                              const void *jq, double *__restrict__ mu, void *Fq, void *Qq, int cz) {
-    __shared__ double sr[3][NRP];
-    __shared__ double sm[2][NM];
-    __shared__ real sp[3][NP];
-
-    // Workgroups are dealt round-robin to the 8 XCDs in linear order; the
-    // linear id is remapped so that each XCD runs a contiguous range of
-    // (chunk, tile) pairs, tiles of one chunk consecutively: neighbouring
-    // tiles then share their halo planes through that XCD's L2.
-    const int ntx = (kp.nx + TX - 1) / TX;
-    const unsigned ntiles = gridDim.x, nb = gridDim.x * gridDim.y;
-    const unsigned hw = blockIdx.y * gridDim.x + blockIdx.x;
-    const unsigned q = nb >> 3, rem = nb & 7u, xcd = hw & 7u;
-    const unsigned lid = xcd * q + (xcd < rem ? xcd : rem) + (hw >> 3);
-    const int tile = (int)(lid % ntiles), chunk = (int)(lid / ntiles);
-    const int x0 = (tile % ntx) * TX, y0 = (tile / ntx) * TY;
-    const int zs = kp.z0 + chunk * cz;
-    const int ze = min(zs + cz, kp.z1);
-    const int tid = threadIdx.x;
-    const size_t N = kp.N;
-    const real *j = (const real *)jq;
-    real *F = (real *)Fq;
-    real *Q = (real *)Qq;
-
-    // solid planes z = 0 and z = nz-1
-    auto fluid = [&](int p) { return p >= 1 && p <= kp.nz - 2; };
-    auto valid = [&](int p) { return p >= 0 && p <= kp.nz - 1; };
-    auto interior = [&](int a, int b) { return x0 + a < kp.nx && y0 + b < kp.ny; };
-    // plane indices wrap periodically; inside the march they advance by one
-    auto next = [&](int g) { return g + 1 == kp.nz ? 0 : g + 1; };
-    auto pbase = [&](int g) { return (size_t)g * kp.plane; };
-
-    // in-plane byte offsets of the owned rho-, mu- and phi-region points
-    // (kOOB for lanes past the region)
-    unsigned offr[MR], offm[MM], offp[MP];
-#pragma unroll
-    for (int m = 0; m < MR; ++m) {
-        const int r = tid + m * CB;
-        offr[m] = r < NR ? 8u * ((unsigned)wrap(y0 + r / WR - 4, kp.ny) * kp.nx + wrap(x0 + r % WR - 4, kp.nx)) : kOOB;
-    }
-#pragma unroll
-    for (int m = 0; m < MM; ++m) {
-        const int r = tid + m * CB;
-        offm[m] = r < NM ? 8u * ((unsigned)wrap(y0 + r / WM - 3, kp.ny) * kp.nx + wrap(x0 + r % WM - 3, kp.nx)) : kOOB;
-    }
-#pragma unroll
-    for (int m = 0; m < MP; ++m) {
-        const int r = tid + m * CB;
-        offp[m] = r < NP ? (unsigned)sizeof(real) *
-                               ((unsigned)wrap(y0 + r / WP - 1, kp.ny) * kp.nx + wrap(x0 + r % WP - 1, kp.nx))
-                         : kOOB;
-    }
-    const unsigned pbytes8 = kp.plane * 8u, pbytesr = kp.plane * (unsigned)sizeof(real);
-    // byte offset of an interior tile point inside its plane, or kOOB
-    auto ioff = [&](bool ok, int a, int b, unsigned esize) {
-        return ok ? esize * ((unsigned)(y0 + b) * kp.nx + (x0 + a)) : kOOB;
-    };
-    // the store offsets of the owned mu-, phi- and tile points, once per
-    // march (kOOB: not a point of the tile inside the grid)
-    unsigned omu[MM], ofp[MP];
-#pragma unroll
-    for (int m = 0; m < MM; ++m) {
-        const int r = tid + m * CB, a = r % WM, b = r / WM;
-        omu[m] = ioff(r < NM && a >= 3 && b >= 3 && a < TX + 3 && b < TY + 3 && interior(a - 3, b - 3), a - 3, b - 3, 8u);
-    }
-#pragma unroll
-    for (int m = 0; m < MP; ++m) {
-        const int r = tid + m * CB, a = r % WP, b = r / WP;
-        ofp[m] = ioff(r < NP && a >= 1 && b >= 1 && a <= TX && b <= TY && interior(a - 1, b - 1), a - 1, b - 1,
-                      (unsigned)sizeof(real));
-    }
-    const unsigned oq = ioff(interior(tid % TX, tid / TX), tid % TX, tid / TX, (unsigned)sizeof(real));
-
-    // Global loads run ahead of their use: rho one iteration ahead, mu0 and
-    // j issued right after the stage that consumed the previous plane.
-    // Loads of every plane index are issued (planes outside a walled box
-    // wrap to valid memory and their values are never used).
-    double pr[MR], m0[MM];
-    real pj[MP][3];
-    auto issue_rho = [&](int g) {
-        const __amdgpu_buffer_rsrc_t rr = plane_rsrc(rho + pbase(g), pbytes8);
-#pragma unroll
-        for (int m = 0; m < MR; ++m) bload(pr[m], rr, offr[m]);
-    };
-    auto issue_mu0 = [&](int g) {
-        const __amdgpu_buffer_rsrc_t rr = plane_rsrc(mu0 + pbase(g), pbytes8);
-#pragma unroll
-        for (int m = 0; m < MM; ++m) bload(m0[m], rr, offm[m]);
-    };
-    auto issue_j = [&](int g) {
-        const size_t base = pbase(g);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const __amdgpu_buffer_rsrc_t rj = plane_rsrc(j + c * N + base, pbytesr);
-#pragma unroll
-            for (int m = 0; m < MP; ++m) bload(pj[m][c], rj, offp[m]);
-        }
-    };
-    // every lane writes (the padding takes the lanes past the region, and a
-    // plane outside a walled box is written but never read), so the commit
-    // has no lane-divergent branch around the wait for its loads
-    auto commit_rho = [&](int p) {
-        const int s = slot3(p);
-#pragma unroll
-        for (int m = 0; m < MR; ++m) sr[s][tid + m * CB] = pr[m];
-    };
-
-    // register rings, index 0/1/2 = planes p-1, p, p+1 of the consumer
-    double Pr[MM][3];                        // Wx Wy rho at owned mu points
-    double Ar[MP][3], Br[MP][3], Cr[MP][3];  // Dx Wy mu, Wx Dy mu, Wx Wy mu at owned phi points
-    real Xr[3], Yr[3], Zr[3];                // in-plane parts of the Q stencils at the tile point
-#pragma unroll
-    for (int m = 0; m < MM; ++m) Pr[m][0] = Pr[m][1] = Pr[m][2] = 0.0;
-#pragma unroll
-    for (int m = 0; m < MP; ++m)
-#pragma unroll
-        for (int t = 0; t < 3; ++t) Ar[m][t] = Br[m][t] = Cr[m][t] = 0.0;
-#pragma unroll
-    for (int t = 0; t < 3; ++t) Xr[t] = Yr[t] = Zr[t] = (real)0;
-
-    // wall average (Eq. (36)) of mu plane pf into mu plane ps, on the points
-    // with a halo of at most 2
-    auto wall_mu = [&](int ps, int pf, bool write_out) {
-        const int ss = ps & 1, sf = pf & 1;
-        for (int r = tid; r < NM; r += CB) {
-            const int a = r % WM, b = r / WM;
-            if (a < 1 || a > WM - 2 || b < 1 || b > HM - 2) continue;
-            const double v = smooth2<WM>(sm[sf], r);
-            sm[ss][r] = v;
-            if (write_out && a >= 3 && b >= 3 && a < TX + 3 && b < TY + 3 && interior(a - 3, b - 3))
-                mu[pbase(ps) + (size_t)(y0 + b - 3) * kp.nx + (x0 + a - 3)] = v;
-        }
-    };
-    // in-plane parts of grad mu from mu plane p at the owned phi point m
-    auto abc = [&](int p, int m, double &Av, double &Bv, double &Cv) {
-        const int r = tid + m * CB;
-        plane_grad<WM>(sm[p & 1], (r / WP + 2) * WM + (r % WP + 2), Av, Bv, Cv);
-    };
-
-    // wrapped indices of planes k, k+1, k+2, k+3, k+4
-    int g0 = wrap(zs - 6, kp.nz);
-    int g1 = next(g0), g2 = next(g1), g3 = next(g2), g4 = next(g3);
-    issue_rho(g3);      // rho(zs - 3)
-    issue_mu0(g2);      // mu0(zs - 4)
-    issue_j(g1);        // j(zs - 5)
-    for (int k = zs - 6; k < ze; ++k) {
-        // ---- A: commit rho(k+3); prefetch rho(k+4)
-        commit_rho(k + 3);
-        __syncthreads();
-        issue_rho(g4);
-
-        // ---- B: Wx Wy rho(k+3) on the mu region; mu(k+2)
-        {
-            const int q3 = k + 3, p = k + 2;
-            const bool pv = valid(q3);
-            const int s3 = slot3(q3), s2 = slot3(p);
-            const bool do_mu = p >= zs - 2 && fluid(p);
-            const bool out_plane = p >= zs && p < ze;
-            const bool full = p == 1 || p == kp.nz - 2;
-            const __amdgpu_buffer_rsrc_t rmu = plane_rsrc(mu + pbase(g2), pbytes8);
-#pragma unroll
-            for (int m = 0; m < MM; ++m) {
-                const int r = tid + m * CB;
-                Pr[m][0] = Pr[m][1];
-                Pr[m][1] = Pr[m][2];
-                const int a = r % WM, b = r / WM;
-                double v = 0.0;
-                bool out = false;
-                if (r < NM) {
-                    const int c = (b + 1) * WR + (a + 1);  // the same point in the rho region
-                    if (pv) Pr[m][2] = smooth2<WR>(sr[s3], c);
-                    if (do_mu && (full || (a >= 1 && a <= WM - 2 && b >= 1 && b <= HM - 2))) {
-                        const double r0 = sr[s2][c];
-                        const double s27 = A1 * Pr[m][0] + A0 * Pr[m][1] + A1 * Pr[m][2];
-                        v = m0[m] - kp.kappa * 6.0 * (s27 - r0);
-                        sm[p & 1][r] = v;
-                        out = out_plane;
-                    }
-                }
-                bstore(v, rmu, out ? omu[m] : kOOB);
-            }
-            issue_mu0(g3);
-            if (p == 1 && p >= zs - 2) {  // bottom solid plane, from the first fluid plane
-                __syncthreads();
-                wall_mu(0, 1, zs - 1 == 0);
-            } else if (p == kp.nz - 1 && p >= zs - 2) {  // top solid plane
-                wall_mu(p, p - 1, p == ze);
-            }
-        }
-        __syncthreads();
-
-        // ---- C: in-plane parts of mu(k+2); F and phi at k+1
-        {
-            const int p2 = k + 2, p1 = k + 1;
-            const bool do_abc = p2 >= zs - 2 && valid(p2);
-            const bool do_phi = p1 >= zs - 1;
-            const bool fl1 = fluid(p1);
-            const bool out_plane = p1 >= zs && p1 < ze;
-            const size_t base1 = pbase(g1);
-            const __amdgpu_buffer_rsrc_t rF0 = plane_rsrc(F + base1, pbytesr);
-            const __amdgpu_buffer_rsrc_t rF1 = plane_rsrc(F + N + base1, pbytesr);
-            const __amdgpu_buffer_rsrc_t rF2 = plane_rsrc(F + 2 * N + base1, pbytesr);
-#pragma unroll
-            for (int m = 0; m < MP; ++m) {
-                const int r = tid + m * CB;
-                Ar[m][0] = Ar[m][1];
-                Ar[m][1] = Ar[m][2];
-                Br[m][0] = Br[m][1];
-                Br[m][1] = Br[m][2];
-                Cr[m][0] = Cr[m][1];
-                Cr[m][1] = Cr[m][2];
-                const int a = r % WP, b = r / WP;
-                real Fx = 0, Fy = 0, Fz = 0;
-                bool out = false;
-                if (r < NP) {
-                    if (do_abc) abc(p2, m, Ar[m][2], Br[m][2], Cr[m][2]);
-                    // the bottom solid plane's mu only exists from the step
-                    // that evaluated the first fluid plane: refresh its entry
-                    if (do_abc && p2 == 1) abc(0, m, Ar[m][1], Br[m][1], Cr[m][1]);
-                    if (do_phi && !fl1) sp[0][r] = sp[1][r] = sp[2][r] = (real)0;
-                    if (do_phi && fl1) {
-                        const double gx = 0.5 * (A1 * Ar[m][0] + A0 * Ar[m][1] + A1 * Ar[m][2]);
-                        const double gy = 0.5 * (A1 * Br[m][0] + A0 * Br[m][1] + A1 * Br[m][2]);
-                        const double gz = 0.5 * (Cr[m][2] - Cr[m][0]);
-                        const double rd = sr[slot3(p1)][(b + 3) * WR + (a + 3)];
-                        const double c1 = 1.0 / 3.0 - rd;
-                        Fx = (real)(c1 * gx);
-                        Fy = (real)(c1 * gy);
-                        Fz = (real)(c1 * gz);
-                        const real ir = (real)1 / (real)rd;
-                        const real ux = (pj[m][0] + (real)0.5 * Fx) * ir;
-                        const real uy = (pj[m][1] + (real)0.5 * Fy) * ir;
-                        const real uz = (pj[m][2] + (real)0.5 * Fz) * ir;
-                        // p_m - rho/3 with p_m = (1 + mu)/3
-                        const real c2 = (real)((1.0 + sm[p1 & 1][(b + 2) * WM + (a + 2)] - rd) * (1.0 / 3.0));
-                        sp[0][r] = c2 * ux;
-                        sp[1][r] = c2 * uy;
-                        sp[2][r] = c2 * uz;
-                        out = out_plane;
-                    }
-                }
-                const unsigned o = out ? ofp[m] : kOOB;
-                bstore(Fx, rF0, o);
-                bstore(Fy, rF1, o);
-                bstore(Fz, rF2, o);
-            }
-            issue_j(g2);
-        }
-        __syncthreads();
-
-        // ---- D: in-plane parts of phi(k+1); Q at k
-        {
-            const int p1 = k + 1, p0 = k;
-            Xr[0] = Xr[1];
-            Xr[1] = Xr[2];
-            Yr[0] = Yr[1];
-            Yr[1] = Yr[2];
-            Zr[0] = Zr[1];
-            Zr[1] = Zr[2];
-            const int a = tid % TX, b = tid / TX;
-            const int c = (b + 1) * WP + (a + 1);
-            const real w1r = (real)A1, w0r = (real)A0;
-            if (p1 >= zs - 1) {
-                const real *gx = sp[0], *gy = sp[1], *gz = sp[2];
-                Xr[2] = w1r * (gx[c - WP + 1] - gx[c - WP - 1]) + w0r * (gx[c + 1] - gx[c - 1]) +
-                        w1r * (gx[c + WP + 1] - gx[c + WP - 1]);
-                Yr[2] = w1r * (gy[c + WP - 1] - gy[c - WP - 1]) + w0r * (gy[c + WP] - gy[c - WP]) +
-                        w1r * (gy[c + WP + 1] - gy[c - WP + 1]);
-                Zr[2] = w1r * (w1r * gz[c - WP - 1] + w0r * gz[c - WP] + w1r * gz[c - WP + 1]) +
-                        w0r * (w1r * gz[c - 1] + w0r * gz[c] + w1r * gz[c + 1]) +
-                        w1r * (w1r * gz[c + WP - 1] + w0r * gz[c + WP] + w1r * gz[c + WP + 1]);
-            }
-            {
-                const real h = (real)(-1.5);
-                const size_t base0 = pbase(g0);
-                const unsigned o = p0 >= zs && fluid(p0) ? oq : kOOB;
-                bstore(h * (w1r * Xr[0] + w0r * Xr[1] + w1r * Xr[2]), plane_rsrc(Q + base0, pbytesr), o);
-                bstore(h * (w1r * Yr[0] + w0r * Yr[1] + w1r * Yr[2]), plane_rsrc(Q + N + base0, pbytesr), o);
-                bstore(h * (Zr[2] - Zr[0]), plane_rsrc(Q + 2 * N + base0, pbytesr), o);
-            }
-        }
-        // no barrier: the next writes to the phi plane (stage C of k+1) and
-        // to the mu ring (stage B of k+1) come after at least one barrier
-        g0 = g1;
-        g1 = g2;
-        g2 = g3;
-        g3 = g4;
-        g4 = next(g4);
-    }
-}
-
 // The R-row forms of smooth2, plane_grad and plane_div: R vertically adjacent
 // points from index c of the first, the x parts of a row formed once for the
 // (up to three) points that share it.  Every value is rounded as in the
@@ -488,7 +178,7 @@ __device__ inline void div_rows(const real *gx, const real *gy, const real *gz, 
 }
 
 // ---------------------------------------------------------------------------
-// The march of periodic grids.  The three stencils run at the same time on
+// The march of large grids.  The three stencils run at the same time on
 // planes one stage apart, each on waves of its own, so that a plane costs one
 // barrier: at iteration t the five mu waves store rho(t) to LDS and evaluate
 // mu(t-2), the seven phi waves F and phi(t-4), the four Q waves Q(t-6), each
@@ -503,9 +193,13 @@ __device__ inline void div_rows(const real *gx, const real *gy, const real *gz, 
 // three barriers and one point per thread): 128^3 FP64 57 -> 47, FP32 42 ->
 // 34; 192x192x96 83 -> 68, 62 -> 47; 512^3 2920 -> 2720-2870, 1955 -> 1743;
 // 256^3 388 -> 418, 270 -> 246-275.  MU0: mu0(rho) is formed here instead of
-// read (kp.mu0_in_chain).
+// read (kp.mu0_in_chain).  WALLS: phi is zero on the solid planes, whose mu
+// stands in mu0 (k_wall_planes).  Before, a march of its own formed the solid
+// planes between walls (us with the wall density, before / now: FP64 128^3 63 /
+// 54, 256^3 411 / 394; FP32 128^3 51 / 40, 192x192x96 67 / 54, 256^3 279 / 267; 211 x
+// 187 x 150 112 / 117).
 // ---------------------------------------------------------------------------
-template <class real, bool MU0>
+template <class real, bool MU0, bool WALLS>
 __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__restrict__ rho, const double *__restrict__ mu0,
                                                const void *jq, double *__restrict__ mu, void *Fq, void *Qq, int cz) {
     constexpr int HM = 2, HR = 3;  // halos of the mu and rho regions
@@ -546,6 +240,8 @@ __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__rest
     auto pbase = [&](int g) { return (size_t)g * kp.plane; };
     auto inside = [&](int x, int y) { return x >= 0 && x < TX && y >= 0 && y < TY && x0 + x < kp.nx && y0 + y < kp.ny; };
     auto node = [&](int x, int y) { return (unsigned)wrap(y0 + y, kp.ny) * kp.nx + (unsigned)wrap(x0 + x, kp.nx); };
+
+    auto solid = [&](int g) { return WALLS && (g == 0 || g == kp.nz - 1); };
 
     const int tb = zs, te = ze + 5;  // first and last iteration
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -590,7 +286,12 @@ __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__rest
             if (p3 >= zs - 2 && p3 <= ze + 1 && has) {
                 double An[RC], Bn[RC], Cn[RC], mid[RC];
                 grad_rows<WM, RC>(sm[p3 & 1], cg, An, Bn, Cn, mid);
-                if (p >= zs - 1) {
+                if (solid(g)) {
+#pragma unroll
+                    for (int i = 0; i < RC; ++i)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) sp[p & 1][c][cp + i * WP] = (real)0;
+                } else if (p >= zs - 1) {
 #pragma unroll
                     for (int i = 0; i < RC; ++i) {
                         real ph[3];
@@ -730,10 +431,12 @@ __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__rest
             if (p <= ze + 1 && has) {
                 double P2[RB], mid[RB];
                 smooth_rows<WR, RB>(sr[s0 == 0 ? 4 : s0 - 1], cr, P2, mid);
+                // (the mu0 of a solid plane is its mu, from k_wall_planes)
+                const double kap6 = solid(g2) ? 0.0 : kp.kappa * 6.0;
 #pragma unroll
                 for (int i = 0; i < RB; ++i) {
                     const double s27 = A1 * P0[i] + A0 * P1[i] + A1 * P2[i];
-                    v[i] = (MU0 ? mu_bulk(kp, rc[i]) : m0[i]) - kp.kappa * 6.0 * (s27 - rc[i]);
+                    v[i] = (MU0 ? mu_bulk(kp, rc[i]) : m0[i]) - kap6 * (s27 - rc[i]);
                     P0[i] = P1[i];
                     P1[i] = P2[i];
                     rc[i] = mid[i];
@@ -750,6 +453,49 @@ __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__rest
             s0 = s0 == 4 ? 0 : s0 + 1;
             __syncthreads();
         }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The solid planes of the march between walls: their density (Eqs. (37)-(38))
+// and mu, the average of mu over the nine nodes beside each (Eq. (36)), which
+// are formed here as the chain forms them.  mu goes to mu0's solid planes too:
+// the march takes it from there like any mu0, so its loop has no branch for
+// the walls (with a pointer or value chosen per plane it ran twice as long).
+// One workgroup per 32 x 8 nodes of a plane.
+// ---------------------------------------------------------------------------
+constexpr int WTX = 32, WTY = 8, WNT = WTX * WTY;
+__global__ __launch_bounds__(WNT) void k_wall_planes(KP kp, double *rho, double *mu0, double *mu) {
+    constexpr int W2 = WTX + 4, N2 = W2 * (WTY + 4), W1 = WTX + 2, N1 = W1 * (WTY + 2);  // rho, mu regions
+    __shared__ double sr[3][N2], sm[N1];
+    const int ntx = (kp.nx + WTX - 1) / WTX;
+    const int x0 = (int)blockIdx.x % ntx * WTX, y0 = (int)blockIdx.x / ntx * WTY;
+    const int ps = blockIdx.y ? kp.nz - 1 : 0, pf = blockIdx.y ? kp.nz - 2 : 1;
+    const int tid = threadIdx.x;
+    auto node = [&](int x, int y) { return (unsigned)wrap(y0 + y, kp.ny) * kp.nx + (unsigned)wrap(x0 + x, kp.nx); };
+    for (int r = tid; r < N2; r += WNT) {
+        const unsigned n = node(r % W2 - 2, r / W2 - 2);
+#pragma unroll
+        for (int z = 0; z < 3; ++z)
+            if (const int p = pf - 1 + z; p != 0 && p != kp.nz - 1) sr[z][r] = rho[(size_t)p * kp.plane + n];
+        const int y = (int)(n / (unsigned)kp.nx), x = (int)(n - (unsigned)y * kp.nx);
+        sr[ps - pf + 1][r] = wall_rho(kp, rho, x, y, ps);
+        if (kp.nz == 3) sr[pf - ps + 1][r] = wall_rho(kp, rho, x, y, 2 * pf - ps);
+    }
+    __syncthreads();
+    for (int r = tid; r < N1; r += WNT) {
+        const int c = (r / W1 + 1) * W2 + r % W1 + 1;
+        const double P0 = smooth2<W2>(sr[0], c), P1 = smooth2<W2>(sr[1], c), P2 = smooth2<W2>(sr[2], c);
+        const double r0 = sr[1][c];
+        const double s27 = A1 * P0 + A0 * P1 + A1 * P2;
+        sm[r] = mu0[(size_t)pf * kp.plane + node(r % W1 - 1, r / W1 - 1)] - kp.kappa * 6.0 * (s27 - r0);
+    }
+    __syncthreads();
+    const int a = tid % WTX, b = tid / WTX;
+    if (x0 + a < kp.nx && y0 + b < kp.ny) {
+        const size_t n = (size_t)ps * kp.plane + (unsigned)(y0 + b) * kp.nx + x0 + a;
+        rho[n] = sr[ps - pf + 1][(b + 2) * W2 + a + 2];
+        mu0[n] = mu[n] = smooth2<W1>(sm, (b + 1) * W1 + a + 1);
     }
 }
 
@@ -1162,22 +908,28 @@ hipError_t launch_step_block(hipStream_t s, int prec, const KP &kp, const Bufs &
     }
 }
 
+static bool chain_is_block(const KP &kp, int cz) { return chain_block_grid(kp) && (cz == 1 || cz == 2 || cz == 4); }
+
+bool chain_forms_walls(const KP &kp) { return kp.walls && !chain_is_block(kp, chain_chunk_for(kp)); }
+
 hipError_t launch_chain(hipStream_t s, int prec, const KP &kp, const Bufs &b) {
     const unsigned ntx = (kp.nx + TX - 1) / TX, nty = (kp.ny + TY - 1) / TY;
     const int cz = chain_chunk_for(kp);
     const int nzf = kp.z1 - kp.z0;
-    if (chain_block_grid(kp) && (cz == 1 || cz == 2 || cz == 4))
+    if (chain_is_block(kp, cz))
         return prec == LBFE_FP64 ? go_block<kFields, double>(s, kp, b, cz, nullptr, nullptr)
                                  : go_block<kFields, float>(s, kp, b, cz, nullptr, nullptr);
     const dim3 grid(ntx * nty, (nzf + cz - 1) / cz);
     auto go = [&](auto real) {
         using R = decltype(real);
-        if (kp.walls)
-            k_chain<R><<<grid, CB, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
-        else if (kp.mu0_in_chain)
-            k_chain_march<R, true><<<grid, NTC, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
+        if (kp.walls) {
+            const unsigned gw = ((kp.nx + WTX - 1) / WTX) * ((kp.ny + WTY - 1) / WTY);
+            k_wall_planes<<<dim3(gw, 2), WNT, 0, s>>>(kp, b.rho, b.mu0, b.mu);
+            k_chain_march<R, false, true><<<grid, NTC, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
+        } else if (kp.mu0_in_chain)
+            k_chain_march<R, true, false><<<grid, NTC, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
         else
-            k_chain_march<R, false><<<grid, NTC, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
+            k_chain_march<R, false, false><<<grid, NTC, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, cz);
     };
     if (prec == LBFE_FP64)
         go(double{});

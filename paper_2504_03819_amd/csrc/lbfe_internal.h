@@ -104,6 +104,7 @@ hipError_t launch_state_collide(hipStream_t s, int prec, const KP &kp, const Buf
 // planes per workgroup, kp.chain_cz if set, else chosen for the grid
 hipError_t launch_chain(hipStream_t s, int prec, const KP &kp, const Bufs &b);
 int chain_chunk_for(const KP &kp);
+bool chain_forms_walls(const KP &kp);  // launch_chain writes the density of the solid planes too
 // chain + collide + stream of a small grid in one launch (mu, F, Q not
 // stored); step_block_chunk: its planes per workgroup, 0 where two launches
 // are faster (kp.chain_cz as the caller set it)

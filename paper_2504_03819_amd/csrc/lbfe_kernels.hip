@@ -391,11 +391,17 @@ template <int P> void moments_pass(hipStream_t s, const KP &kp, const Bufs &b, i
         k_moments<P, true><<<g, kBlock, 0, s>>>(kp, b.f[cur], b.rho, b.j, b.mu0, b.flag);
 }
 
+// Density of the solid planes, where the chain does not form it
+void wall_density(hipStream_t s, const KP &kp, const Bufs &b) {
+    if (kp.walls && !chain_forms_walls(kp))
+        k_wall_rho<<<nblocks(2 * (size_t)kp.plane), kBlock, 0, s>>>(kp, b.rho);
+}
+
 template <int P>
 hipError_t aux_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool refresh) {
     if (refresh) {
         moments_pass<P>(s, kp, b, cur);
-        if (kp.walls) k_wall_rho<<<nblocks(2 * (size_t)kp.plane), kBlock, 0, s>>>(kp, b.rho);
+        wall_density(s, kp, b);
     }
     hipError_t e = launch_chain(s, P, kp, b);
     if (e != hipSuccess) return e;
@@ -415,7 +421,7 @@ hipError_t step_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool f
     mark(0);
     if (refresh || !fused) {
         moments_pass<P>(s, kp, b, cur);
-        if (kp.walls && !block) k_wall_rho<<<gw, kBlock, 0, s>>>(kp, b.rho);
+        if (!block) wall_density(s, kp, b);
     }
     mark(1);
     hipError_t e = block ? hipSuccess : launch_chain(s, P, kp, b);
@@ -437,7 +443,7 @@ hipError_t step_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool f
         if (kp.moving) k_wall_move<P><<<gw, kBlock, 0, s>>>(kp, b.f[1 - cur], b.rho, b.mu);
     }
     mark(3);
-    if (fused && kp.walls) k_wall_rho<<<gw, kBlock, 0, s>>>(kp, b.rho);
+    if (fused) wall_density(s, kp, b);
     mark(4);
     return hipGetLastError();
 }
@@ -508,7 +514,7 @@ hipError_t launch_state_enter(hipStream_t s, int prec, const KP &kp, const Bufs 
             return hipGetLastError();
         });
         if (e != hipSuccess) return e;
-        if (kp.walls) k_wall_rho<<<gw, kBlock, 0, s>>>(kp, b.rho);
+        wall_density(s, kp, b);
     }
     hipError_t e = launch_chain(s, prec, kp, b);
     if (e != hipSuccess) return e;
@@ -523,7 +529,7 @@ hipError_t launch_state_moments(hipStream_t s, int prec, const KP &kp, const Buf
     if (ev) (void)hipEventRecord(ev[0], s);
     hipError_t e = launch_state_pass(s, prec, pops ? kStatePops : kStateMoments, kp, b, b.f[a], pops ? b.f[1 - a] : nullptr);
     if (e != hipSuccess) return e;
-    if (kp.walls) k_wall_rho<<<nblocks(2 * (size_t)kp.plane), kBlock, 0, s>>>(kp, b.rho);
+    wall_density(s, kp, b);
     if (ev) (void)hipEventRecord(ev[1], s);
     return hipGetLastError();
 }
