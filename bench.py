@@ -72,11 +72,12 @@ def kernel_source_hash():
 # form rounds the rest population, which carries the density contrast: mass
 # drifts by 5.9e-2 per 1000 steps and long runs leave the EOS domain)
 INVALID_FORMS = {"fp16dev": "all-FP16 storage: mass drift 5.9e-2 per 1000 steps, diverges in long runs"}
-STEP_KERNELS = ("k_moments", "k_chain", "k_collide", "k_fused", "k_wall_rho", "k_wall_move", "k_mstate")
+STEP_KERNELS = ("k_moments", "k_chain", "k_collide", "k_fused", "k_wall_rho", "k_wall_move", "k_wall_planes",
+                "k_mstate")
 ADJ_COUNTERS = os.path.join(ROOT, "profiles", "adjoint_counters.json")
 # kernels of one adjoint step with the forward fields kept (the seed, the
 # read-out and the initialiser's adjoint are not part of a step)
-ADJ_STEP_KERNELS = ("k_adj_collide", "k_adj_phimu", "k_adj_rho", "k_adj_wall", "k_adj_pack", "k_adj_reduce")
+ADJ_STEP_KERNELS = ("k_adj_collide", "k_adj_phimu", "k_adj_rho", "k_adj_wall", "k_adj_tail", "k_adj_reduce")
 PATH_NAMES = {1: "two-pass", 2: "fused", 3: "state"}
 DOMINANT = {"two-pass": "k_collide (collide + push-stream)",
             "fused": "k_fused (collide + stream + next-step moments)",

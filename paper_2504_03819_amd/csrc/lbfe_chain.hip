@@ -504,7 +504,7 @@ __global__ __launch_bounds__(WNT) void k_wall_planes(KP kp, double *rho, double 
 // loads the block's whole rho region (halo HR in the plane, 3 in z) at once
 // and then runs the three stencils one after the other.  In each, a thread
 // marches the columns it owns through all planes of the region in registers
-// (the sums of k_chain, in the same order, so the same bits), so the block
+// (the sums of the march, in the same order, so the same bits), so the block
 // passes three barriers in all instead of three per plane, and its loads wait
 // for memory once.  The region is recomputed by the neighbouring blocks
 // (mu on 3.5 times the owned nodes at 16 x 8 x 4), which only pays while the

@@ -2,19 +2,20 @@
 // (arXiv:2504.03819, Sec. II B and Sec. III C) for gfx950.
 //
 // One time step t -> t+1 on the post-streaming state f(t):
-//   k_chain     mu, mu at walls, F, u, phi and Q from rho, j, mu0 with
+//   k_moments   rho (double), j = sum f c, mu0(rho)          Eqs. (11), (32)
+//   k_wall_rho  density of the solid nodes (walls only)         Eqs. (37)-(38)
+//   k_chain_*   mu, mu at walls, F, u, phi and Q from rho, j, mu0 with
 //               LDS-staged stencils (lbfe_chain.hip)
 //                                              Eqs. (12), (27), (32), (36)
-//   k_fused     CM transform, collision, inverse, push-stream with halfway
-//               bounce-back, and rho, j, mu0 of f(t+1) (lbfe_fused.hip)
-//                                  Eqs. (10), (11), (21)-(26), (28), (32)
-//   k_wall_rho  density of the solid nodes (walls only)         Eqs. (37)-(38)
-// k_moments forms rho (double), j = sum f c and mu0(rho) from stored
-// populations when they were set from outside (Eqs. (11), (32)); k_collide
-// is the collide-stream alone, for the unfused reference path.  Populations are row-blocked
-// (each x-row holds its 27 populations as 27 contiguous runs); one thread per
-// node, x fastest, so every population load and store of a wave64 is one
-// contiguous 64-element run.
+//   k_collide   CM transform, collision, inverse, push-stream with halfway
+//               bounce-back                  Eqs. (10), (21)-(26), (28)
+// On small grids k_chain_block also collides, streams and forms the walls'
+// density and velocity term (lbfe_chain.hip).  On large FP64 and FP32 grids
+// k_fused (lbfe_fused.hip) collides, streams and forms rho, j, mu0 of f(t+1),
+// and k_moments runs only when the populations were set from outside.
+// Populations are row-blocked (each x-row holds its 27 populations as 27
+// contiguous runs); one thread per node, x fastest, so every population load
+// and store of a wave64 is one contiguous 64-element run.
 #include <mutex>
 #include <type_traits>
 
