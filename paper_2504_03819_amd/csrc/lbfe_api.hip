@@ -444,18 +444,20 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
     // Planes per workgroup of the stencil chain: chosen per grid unless given.
     k.chain_cz = q.chain_chunk;
     // Populations are read non-temporal unless the 256 MB last-level cache
-    // holds them until they are read again.  One lattice below 192 MiB stays
-    // between the moments pass and the collide pass (us per step, moments
-    // non-temporal / plain: FP64 96^3 124.8 / 118.8, 104^3 181 / 175, 112^3 193
-    // / 211; FP32 120^3 154 / 146, 128^3 160 / 166; FP16 144^3 192 / 179, 160^3
-    // 242 / 266); below 112 MiB both lattices and the fields stay from step to
+    // holds them until they are read again.  A lattice that takes less than
+    // 336 MiB with its fields is still there, in good part, when the collide
+    // pass follows the moments pass (us per step, moments non-temporal / plain:
+    // FP64 96^3 124.8 / 118.8, 104^3 181 / 175, 112^3 193 / 211; FP32 120^3 154 /
+    // 146, 128^3 160 / 166; FP16 144^3 192 / 179, 192 x 192 x 96 192 / 201); with
+    // a lattice below 112 MiB both lattices and the fields stay from step to
     // step and the collide pass too reads plain (both / moments only: FP64 64^3
     // 39.7 / 41.8, 80^3 70.5 / 71.3, 101 x 67 x 53 60.0 against 72.8 without
     // either, 96^3 135 / 119; FP32 80^3 47.7 / 54.2, 104^3 101.7 / 99.0; FP16
     // 120^3 114.6 / 115.1).  A reverse sweep also reads lambda and recorded
     // states: half of it (96^3 FP32 forward and back 3555 / 3650 us, plain).
-    const size_t lattice = pop_bytes(q.precision, k.N) * (q.adjoint ? 2 : 1);
-    k.keep1 = lattice < ((size_t)192 << 20);
+    const size_t sets = q.adjoint ? 2 : 1, lattice = pop_bytes(q.precision, k.N) * sets;
+    const size_t fields = (24 + 9 * real_bytes(q.precision)) * k.N * sets;
+    k.keep1 = lattice + fields < ((size_t)336 << 20);
     k.keep2 = lattice < ((size_t)112 << 20);
     k.step_block = step_block_chunk(k, q.precision);
     q.chain_chunk = k.chain_cz = chain_chunk_for(k);

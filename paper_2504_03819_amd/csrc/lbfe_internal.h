@@ -32,7 +32,7 @@ struct KP {
     double wet_value, lo, hi;  // wetting value and contact-line window
     int xcd_remap;             // map consecutive tiles onto one XCD
     double wall_u[4];          // (ux, uy) of the bottom and top walls
-    int keep1, keep2;          // one lattice, two lattices with their fields stay in the last-level cache
+    int keep1, keep2;          // a lattice with its fields, two lattices stay in the last-level cache
     int moving;                // some wall velocity is nonzero
     int masked;                // solid voxel mask (Bufs::nbr) instead of planes
     int chain_cz;              // planes per stencil-chain workgroup
