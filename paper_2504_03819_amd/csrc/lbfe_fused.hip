@@ -47,7 +47,7 @@ namespace {
 
 using namespace plane;
 
-template <int P, bool WALLS, int TX, int TY, int NT>
+template <int P, bool WALLS, bool MU0, int TX, int TY, int NT>
 __global__ __launch_bounds__(NT) void k_fused(KP kp, const void *fin_q, void *fout_q, const double *__restrict__ mu,
                                               const void *Fq, const void *Qq, double *__restrict__ rho, void *jq,
                                               double *__restrict__ mu0, int *flag, int cz) {
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(NT) void k_fused(KP kp, const void *fin_q, void *fo
         const unsigned o8 = ok ? vn8 : kOOB, orr = ok ? vnr : kOOB;
         const double r = A.r + Lm;
         bst(r, rsrc(rho + pb, b8), o8, 0);
-        if (!kp.mu0_in_chain) bst(mu_bulk(kp, r), rsrc(mu0 + pb, b8), o8, 0);
+        if constexpr (MU0) bst(mu_bulk(kp, r), rsrc(mu0 + pb, b8), o8, 0);
         bst((real)A.jx, rsrc(J + pb, br), orr, 0);
         bst((real)A.jy, rsrc(J + N + pb, br), orr, 0);
         bst((real)(A.lp - Lm), rsrc(J + 2 * N + pb, br), orr, 0);
@@ -248,14 +248,18 @@ template <int P> hipError_t launch(hipStream_t s, const KP &kp, const Bufs &b, i
     const unsigned tiles = tiles_of(kp, TX, TY);
     const int cz = fused_chunk(kp, tiles), nzf = kp.z1 - kp.z0;
     const dim3 grid(tiles, (nzf + cz - 1) / cz);
-    auto go = [&](auto walls) {
-        k_fused<P, decltype(walls)::value, TX, TY, NT><<<grid, NT, 0, s>>>(kp, b.f[cur], b.f[1 - cur], b.mu, b.F, b.Q,
-                                                                          b.rho, b.j, b.mu0, b.flag, cz);
+    // mu0 stored: a template argument, as a branch around the store would keep
+    // the compiler from counting the stores in flight
+    auto go = [&](auto walls, auto mu0) {
+        k_fused<P, decltype(walls)::value, decltype(mu0)::value, TX, TY, NT><<<grid, NT, 0, s>>>(
+            kp, b.f[cur], b.f[1 - cur], b.mu, b.F, b.Q, b.rho, b.j, b.mu0, b.flag, cz);
     };
-    if (kp.walls)
-        go(std::true_type{});
+    if (kp.walls)  // (mu0_in_chain is for periodic grids)
+        go(std::true_type{}, std::true_type{});
+    else if (kp.mu0_in_chain)
+        go(std::false_type{}, std::false_type{});
     else
-        go(std::false_type{});
+        go(std::false_type{}, std::true_type{});
     return hipGetLastError();
 }
 
