@@ -287,6 +287,15 @@ template <class real> __device__ inline real final_term(const Pack4<real> *pk, i
     return final_term<real>(t.x, t.y, t.z, t.w, i);
 }
 
+// Adjoint sources that the stencils and sums read at solid nodes too: zero
+// there, written by the seed (wall planes) or by k_adj_collide (masks), so that
+// a sweep does not depend on what its workspace held.
+template <class real> __device__ inline void zero_sources(void *abuf, size_t N, size_t n) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) aplane<real>(abuf, A_QB, c, N)[n] = (real)0;
+    ((double *)abuf)[A_NUC * N + n] = 0.0;
+}
+
 template <class real> __device__ inline void store_pack(void *abuf, size_t N, size_t n, double rhobt) {
     Pack4<real> t;
     t.x = (real)rhobt;
@@ -326,6 +335,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_collide(KP kp, Bufs b, const voi
     if (MASK && (wm & kSelfBit)) {
 #pragma unroll
         for (int i = 0; i < 27; ++i) stl(i, (real)0);
+        zero_sources<real>(b.abuf, kp.N, n);
         return;
     }
 
@@ -1048,12 +1058,19 @@ __global__ __launch_bounds__(kFinal) void k_adj_reduce_final(unsigned nk, const 
 }
 
 // ---- seed and initialiser ---------------------------------------------------
+// lambda(T), zero gradient accumulators and zero sources at the solid nodes
+__device__ inline void zero_grads(const Bufs &b) {
+    if (blockIdx.x == 0 && threadIdx.x < 8) b.agrad[threadIdx.x] = 0.0;
+}
+
 template <int P> __global__ __launch_bounds__(kBlock) void k_adj_seed(KP kp, Bufs b, const double *g, void *lam) {
     using real = real_t<P>;
     const unsigned n = blockIdx.x * kBlock + threadIdx.x;
+    zero_grads(b);
     if (n >= kp.N) return;
     const unsigned row = n / (unsigned)kp.nx, x = n - row * (unsigned)kp.nx;
     const bool fluid = fluid_node(kp, b, n);
+    if (!fluid) zero_sources<real>(b.abuf, kp.N, n);
     const real v = fluid ? (real)g[n] : (real)0;
     const Lam<real> L(lam, kp);
 #pragma unroll
@@ -1064,9 +1081,11 @@ template <int P>
 __global__ __launch_bounds__(kBlock) void k_adj_seed_pop(KP kp, Bufs b, const double *g, void *lam) {
     using real = real_t<P>;
     const unsigned n = blockIdx.x * kBlock + threadIdx.x;
+    zero_grads(b);
     if (n >= kp.N) return;
     const unsigned row = n / (unsigned)kp.nx, x = n - row * (unsigned)kp.nx;
     const bool fluid = fluid_node(kp, b, n);
+    if (!fluid) zero_sources<real>(b.abuf, kp.N, n);
     const Lam<real> L(lam, kp);
 #pragma unroll
     for (int i = 0; i < 27; ++i) L.st(i, row, x, fluid ? (real)g[(size_t)i * kp.N + n] : (real)0);
@@ -1222,15 +1241,7 @@ template <int P, bool STEP> hipError_t chain_tail(hipStream_t s, const KP &kp, c
 size_t adjoint_aux_bytes(int, size_t N) { return (size_t)A_COUNT * 8 * N; }
 size_t adjoint_grad_slots() { return 3; }
 
-hipError_t launch_adj_seed(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, bool clear,
-                           const double *g) {
-    if (clear) {  // a workspace that a sweep has used
-        hipError_t e = launch_fill(s, b.agrad, 64);
-        if (e != hipSuccess) return e;
-        // solid-node entries of the adjoint arrays must read as zero
-        e = launch_fill(s, b.abuf, adjoint_aux_bytes(prec, kp.N));
-        if (e != hipSuccess) return e;
-    }
+hipError_t launch_adj_seed(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, const double *g) {
     return dispatch(prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         k_adj_seed<P><<<nblocks(kp.N), kBlock, 0, s>>>(kp, b, g, b.lam[lcur]);
@@ -1238,15 +1249,7 @@ hipError_t launch_adj_seed(hipStream_t s, int prec, const KP &kp, const Bufs &b,
     });
 }
 
-hipError_t launch_adj_seed_pop(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, bool clear,
-                               const double *g) {
-    if (clear) {  // a workspace that a sweep has used
-        hipError_t e = launch_fill(s, b.agrad, 64);
-        if (e != hipSuccess) return e;
-        // solid-node entries of the adjoint arrays must read as zero
-        e = launch_fill(s, b.abuf, adjoint_aux_bytes(prec, kp.N));
-        if (e != hipSuccess) return e;
-    }
+hipError_t launch_adj_seed_pop(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, const double *g) {
     return dispatch(prec, [&](auto pc) {
         constexpr int P = decltype(pc)::value;
         k_adj_seed_pop<P><<<nblocks(kp.N), kBlock, 0, s>>>(kp, b, g, b.lam[lcur]);

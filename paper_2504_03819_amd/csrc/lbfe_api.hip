@@ -29,7 +29,6 @@ struct lbfe_ctx {
     bool state = false;   // moment-representation state (LBFE_PATH_STATE)
     bool aux_ok = false;  // rho, j, mu0 hold the moments of f[cur]
     bool mask_set = false;  // a solid mask has been given (solid_mask = 1)
-    bool adj_clean = false;    // the adjoint arrays are zero (as bound)
     bool lam_pending = false;  // lam[lcur] lacks its last term (see the adjoint kernels)
     std::string err;
 };
@@ -538,7 +537,6 @@ int lbfe_bind_workspace(lbfe_ctx *c, void *ws, size_t bytes) {
     c->aux_ok = false;
     c->mask_set = false;
     c->adj_seeded = false;
-    c->adj_clean = true;
     c->cur = 0;
     c->step = 0;
     return LBFE_OK;
@@ -768,9 +766,8 @@ int lbfe_adjoint_seed(lbfe_ctx *c, const double *dLdrho) {
     if (!dLdrho) return fail(c, LBFE_E_INVAL, "null dL/drho");
     c->lcur = 0;
     c->lam_pending = false;
-    hipError_t e = launch_adj_seed(c->stream, c->p.precision, c->kp, c->b, c->lcur, !c->adj_clean, dLdrho);
+    hipError_t e = launch_adj_seed(c->stream, c->p.precision, c->kp, c->b, c->lcur, dLdrho);
     if (e != hipSuccess) return hip_fail(c, e, "adjoint_seed");
-    c->adj_clean = false;
     c->adj_seeded = true;
     return LBFE_OK;
 }
@@ -782,9 +779,8 @@ int lbfe_adjoint_seed_populations(lbfe_ctx *c, const double *g) {
     if (!g) return fail(c, LBFE_E_INVAL, "null dL/df");
     c->lcur = 0;
     c->lam_pending = false;
-    hipError_t e = launch_adj_seed_pop(c->stream, c->p.precision, c->kp, c->b, c->lcur, !c->adj_clean, g);
+    hipError_t e = launch_adj_seed_pop(c->stream, c->p.precision, c->kp, c->b, c->lcur, g);
     if (e != hipSuccess) return hip_fail(c, e, "adjoint_seed_populations");
-    c->adj_clean = false;
     c->adj_seeded = true;
     return LBFE_OK;
 }

@@ -136,10 +136,8 @@ hipError_t launch_init_aux_mask(hipStream_t s, const KP &kp, const Bufs &b, cons
 // adjoint (lbfe_adjoint.hip)
 size_t adjoint_aux_bytes(int prec, size_t N);
 size_t adjoint_grad_slots();
-hipError_t launch_adj_seed(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, bool clear,
-                           const double *dLdrho);
-hipError_t launch_adj_seed_pop(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, bool clear,
-                               const double *lam);
+hipError_t launch_adj_seed(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, const double *dLdrho);
+hipError_t launch_adj_seed_pop(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, const double *lam);
 hipError_t launch_adj_get(hipStream_t s, int prec, const KP &kp, const Bufs &b, int lcur, double *out);
 // recompute: evaluate the forward fields of ft first (else b holds them);
 // pending: lam[lcur] holds only the direct part of lambda(t+1).  Leaves
