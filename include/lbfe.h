@@ -325,8 +325,9 @@ int lbfe_step_aux(lbfe_ctx *ctx, void *aux_dev);
  * state_out_dev NULL the result becomes the context's state, f(step + 1).
  * Same bits as lbfe_set_state, lbfe_step_aux and lbfe_get_state, without the
  * copies; entries of solid nodes of state_out_dev are not written.  Both
- * states: caller-owned device memory of lbfe_state_bytes, 256-byte aligned,
- * not overlapping (E_INVAL otherwise where that can be seen). */
+ * states: caller-owned device memory of lbfe_state_bytes, 256-byte aligned.
+ * E_INVAL where states, record and the context's workspace overlap
+ * (state_in_dev may be a whole lattice of the workspace). */
 int lbfe_step_record(lbfe_ctx *ctx, const void *state_in_dev, int64_t step, void *state_out_dev, void *aux_dev);
 int lbfe_adjoint_step_aux(lbfe_ctx *ctx, const void *state_t_dev, const void *aux_dev);
 

@@ -241,6 +241,11 @@ AuxLayout aux_layout(const lbfe_params &p) {
     return L;
 }
 
+bool overlap(const void *p, size_t n, const void *q, size_t m) {
+    const uintptr_t a = (uintptr_t)p, b = (uintptr_t)q;
+    return a < b + m && b < a + n;
+}
+
 // the context's buffers with the aux fields redirected into a record
 Bufs with_aux(const lbfe_ctx *c, const void *aux) {
     const AuxLayout L = aux_layout(c->p);
@@ -838,9 +843,14 @@ int lbfe_step_record(lbfe_ctx *c, const void *in, int64_t step, void *out, void 
     if (!in) return fail(c, LBFE_E_INVAL, "null state");
     if (((uintptr_t)in & 255u) || ((uintptr_t)out & 255u))
         return fail(c, LBFE_E_INVAL, "states must be 256-byte aligned");
-    if (in == out) return fail(c, LBFE_E_INVAL, "the step needs two states");
     if (step < 0) return fail(c, LBFE_E_INVAL, "step < 0");
     if (!aux || ((uintptr_t)aux & 255u)) return fail(c, LBFE_E_INVAL, "aux record null or not 256-byte aligned");
+    const size_t sb = pop_bytes(c->p.precision, c->kp.N), ab = aux_layout(c->p).total, wb = layout(c->p).total;
+    // a lattice of the context itself is read as a whole; nothing else may overlap
+    const bool own = in == c->b.f[0] || in == c->b.f[1];
+    if (overlap(aux, ab, in, sb) || overlap(aux, ab, c->ws, wb) || (!own && overlap(in, sb, c->ws, wb)) ||
+        (out && (overlap(out, sb, in, sb) || overlap(out, sb, aux, ab) || overlap(out, sb, c->ws, wb))))
+        return fail(c, LBFE_E_INVAL, "states, record and workspace must not overlap");
     // without `out` into the lattice that is not current (it may hold `in`)
     const int to = in == c->b.f[1 - c->cur] ? c->cur : 1 - c->cur;
     Bufs b = with_aux(c, aux);
