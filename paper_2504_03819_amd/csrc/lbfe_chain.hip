@@ -820,16 +820,18 @@ static int chain_chunk(const KP &kp, unsigned tiles) {
     return cz;
 }
 
-// Tile of k_chain_block.
 // The block kernel takes grids below 2^19 fluid nodes, where a march waits for
 // its fill planes (us per step, march against block, two-pass path, periodic:
 // FP64 64^3 54.1 / 49.6, 80^3 90.0 / 86.7; FP32 64^3 36.4 / 32.3, 80^3 60.3 /
 // 59.2); beyond, the blocks' recomputed region costs more (96^3 FP64 132.9 /
 // 139.6, FP32 80.3 / 86.0; 128^3 291 / 328).  A chunk length that the caller
-// forces and the block kernel does not have (it has 1, 2 and 4) goes to a march.
+// forces and the block kernel does not have (it has 1, 2 and 4) goes to a march,
+// and so does a grid so long that its chunks exceed a launch's y dimension.
 constexpr unsigned kBlockNodes = 1u << 19;
 constexpr int BX = 16, BY = 8;  // 32x8, 32x4 and 16x4 blocks: 0-12 % slower per step
-static bool chain_block_grid(const KP &kp) { return kp.nfluid < kBlockNodes; }
+constexpr int kMaxGridY = 65535;
+static bool block_chunks_fit(const KP &kp, int cz) { return (kp.z1 - kp.z0 + cz - 1) / cz <= kMaxGridY; }
+static bool chain_block_grid(const KP &kp) { return kp.nfluid < kBlockNodes && block_chunks_fit(kp, 4); }
 
 // the fewest planes that leave one workgroup per CU, else 4 (32^3: 1, 2, 4
 // planes take 16.9, 18.2, 22.1 us per FP64 step; 64^3: 50.8, 44.0, 40.4)
@@ -893,8 +895,10 @@ static hipError_t go_block(hipStream_t s, const KP &kp, const Bufs &b, int cz, c
 int step_block_chunk(const KP &kp, int prec) {
     const size_t limit = prec == LBFE_FP64 ? 3u << 19 : (prec == LBFE_FP32 ? 1u << 19 : 5u << 16);
     if (kp.masked || kp.nfluid >= limit) return 0;
-    if (kp.chain_cz > 0) return kp.chain_cz == 1 || kp.chain_cz == 2 || kp.chain_cz == 4 ? kp.chain_cz : 0;
-    return min(block_chunk(kp), kp.walls && prec == LBFE_FP64 ? 2 : 4);
+    const int given = kp.chain_cz;
+    if (given > 0) return (given == 1 || given == 2 || given == 4) && block_chunks_fit(kp, given) ? given : 0;
+    const int cz = min(block_chunk(kp), kp.walls && prec == LBFE_FP64 ? 2 : 4);
+    return block_chunks_fit(kp, cz) ? cz : 0;
 }
 
 hipError_t launch_step_block(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur) {
@@ -908,7 +912,9 @@ hipError_t launch_step_block(hipStream_t s, int prec, const KP &kp, const Bufs &
     }
 }
 
-static bool chain_is_block(const KP &kp, int cz) { return chain_block_grid(kp) && (cz == 1 || cz == 2 || cz == 4); }
+static bool chain_is_block(const KP &kp, int cz) {
+    return chain_block_grid(kp) && (cz == 1 || cz == 2 || cz == 4) && block_chunks_fit(kp, cz);
+}
 
 bool chain_forms_walls(const KP &kp) { return kp.walls && !chain_is_block(kp, chain_chunk_for(kp)); }
 
