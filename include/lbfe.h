@@ -98,11 +98,14 @@ typedef struct lbfe_params {
                             by lbfe_set_solid (needs walls_z = 0 and resting
                             walls); 0: none or the wall planes */
     /* Schedule.  None of these changes a result bit; 0 lets lbfe_create
-     * choose per grid, and lbfe_get_params reports the choice made. */
+     * choose per grid, and lbfe_get_params reports the choice made: a context
+     * created from what it reports runs the same schedule. */
     int32_t step_path;   /* LBFE_PATH_*: how one step is split into kernels */
     int32_t tile_order;  /* LBFE_ORDER_*: how tiles are dealt to the XCDs   */
     int32_t chain_chunk; /* z-planes per workgroup of the stencil chain,
-                            1..64                                          */
+                            1..64; where a small grid's step is one launch,
+                            another value than the chosen one also sets that
+                            launch's (1, 2 or 4) or splits it in two       */
 } lbfe_params;
 
 /* ---- schedule choices (lbfe_params.step_path, .tile_order) ------------- */
@@ -163,7 +166,8 @@ int lbfe_coexistence(double a, double b, double R, double T, double *rho_l, doub
  * FP32 contexts of at least 19 x 2^20 where it is allowed, else the two-pass
  * path; the XCD tile order from 2^26 nodes and, without a solid mask,
  * whenever nx or ny is not a power of two; the chain chunk that minimises the
- * busiest CU's plane iterations.
+ * busiest CU's plane iterations, on grids below 2^19 fluid nodes the fewest of
+ * 1, 2 and 4 planes that leave one workgroup per CU.
  * Asking for the fused path where it is not allowed is E_INVAL. */
 int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out);
 

@@ -445,8 +445,6 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
     if (q.tile_order == LBFE_AUTO)
         q.tile_order = (k.N >= (1u << 26) || (irregular && !k.masked)) ? LBFE_ORDER_XCD : LBFE_ORDER_ROUND_ROBIN;
     k.xcd_remap = q.tile_order == LBFE_ORDER_XCD;
-    // Planes per workgroup of the stencil chain: chosen per grid unless given.
-    k.chain_cz = q.chain_chunk;
     // Populations are read non-temporal unless the 256 MB last-level cache
     // holds them until they are read again.  A lattice that takes less than
     // 336 MiB with its fields is still there, in good part, when the collide
@@ -463,8 +461,15 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
     const size_t fields = (24 + 9 * real_bytes(q.precision)) * k.N * sets;
     k.keep1 = lattice + fields < ((size_t)336 << 20);
     k.keep2 = lattice < ((size_t)112 << 20);
+    // Planes per workgroup of the stencil chain, chosen per grid unless given.
+    // Given as it would be chosen (lbfe_get_params reports the choice), the
+    // rest of the schedule is the chosen one too.
+    k.chain_cz = 0;
+    const int chunk = chain_chunk_for(k);
+    if (q.chain_chunk != chunk) k.chain_cz = q.chain_chunk;
     k.step_block = step_block_chunk(k, q.precision);
-    q.chain_chunk = k.chain_cz = chain_chunk_for(k);
+    if (q.chain_chunk == LBFE_AUTO) q.chain_chunk = chunk;
+    k.chain_cz = q.chain_chunk;
     // mu0(rho): on large periodic grids the chain forms it from the density
     // that it stages anyway, and no pass stores or reads the field (16 B per
     // node and the halo's reads).  The logarithms lengthen the chain's busiest

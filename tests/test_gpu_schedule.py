@@ -1,0 +1,31 @@
+"""The schedules that lbfe_create chooses."""
+import pytest
+import torch
+
+from gpu_util import droplet_rho, make_sim, say
+from oracle import eos
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("shape", [(96, 96, 96), (100, 70, 130)])
+def test_reported_parameters_give_the_same_schedule(shape):
+    """One launch for chain and collision, and a march where the chain runs
+    alone, whose length lbfe_get_params reports.  Inside the collide kernel the
+    chain's interval holds no launch: a small part of the moments pass, on
+    grids whose moments pass is long against the events themselves."""
+    nz, ny, nx = shape
+    T = eos.temperature(0.8)
+    a = make_sim(nx=nx, ny=ny, nz=nz, T=T)
+    b = make_sim(params=a.params)
+    rho0 = torch.tensor(droplet_rho(shape, T))
+    part = []
+    for s in (a, b):
+        s.init_density(rho0)
+        s.step(10)
+        t = min((s.step_timed(20) for _ in range(5)), key=lambda v: v["chain"])
+        part.append(t["chain"] / t["moments"])
+    say(f"chain / moments {shape}: {part[0]:.3f} chosen, {part[1]:.3f} from the reported parameters")
+    assert bytes(a.params) == bytes(b.params)
+    assert torch.equal(a.get_state(), b.get_state())
+    assert max(part) < 0.5
