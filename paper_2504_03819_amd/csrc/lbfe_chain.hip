@@ -834,11 +834,13 @@ static bool block_chunks_fit(const KP &kp, int cz) { return (kp.z1 - kp.z0 + cz 
 static bool chain_block_grid(const KP &kp) { return kp.nfluid < kBlockNodes && block_chunks_fit(kp, 4); }
 
 // the fewest planes that leave one workgroup per CU, else 4 (32^3: 1, 2, 4
-// planes take 16.9, 18.2, 22.1 us per FP64 step; 64^3: 50.8, 44.0, 40.4)
+// planes take 16.9, 18.2, 22.1 us per FP64 step; 64^3: 50.8, 44.0, 40.4), but no
+// more than the grid has (one plane of 700 x 700, chunks of 4 / 1: FP64 101 / 77,
+// FP32 83 / 55)
 static int block_chunk(const KP &kp) {
     const size_t tiles = (size_t)((kp.nx + BX - 1) / BX) * ((kp.ny + BY - 1) / BY);
     const size_t nzf = kp.z1 - kp.z0;
-    return tiles * nzf <= kCUs ? 1 : (tiles * ((nzf + 1) / 2) <= kCUs ? 2 : 4);
+    return tiles * nzf <= kCUs || nzf == 1 ? 1 : (tiles * ((nzf + 1) / 2) <= kCUs || nzf == 2 ? 2 : 4);
 }
 
 int chain_chunk_for(const KP &kp) {

@@ -29,3 +29,18 @@ def test_reported_parameters_give_the_same_schedule(shape):
     assert bytes(a.params) == bytes(b.params)
     assert torch.equal(a.get_state(), b.get_state())
     assert max(part) < 0.5
+
+
+@pytest.mark.parametrize("shape,precision", [((1, 300, 700), "fp64"), ((2, 301, 701), "fp32"), ((5, 512, 512), "fp64")])
+def test_thin_periodic_routes_equal_the_march(shape, precision):
+    nz, ny, nx = shape
+    T = eos.temperature(0.8)
+    say(f"thin route: {shape} {precision}")
+    rho0 = torch.tensor(droplet_rho(shape, T, radius=8.0))
+    out = []
+    for chunk in (0, 64):
+        sim = make_sim(nx=nx, ny=ny, nz=nz, T=T, precision=precision, chain_chunk=chunk)
+        sim.init_density(rho0)
+        sim.step(3)
+        out.append((sim.get_state(), sim.field(2)))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
