@@ -833,13 +833,14 @@ constexpr int kMaxGridY = 65535;
 static bool block_chunks_fit(const KP &kp, int cz) { return (kp.z1 - kp.z0 + cz - 1) / cz <= kMaxGridY; }
 static bool chain_block_grid(const KP &kp) { return kp.nfluid < kBlockNodes && block_chunks_fit(kp, 4); }
 
+static size_t block_tiles(const KP &kp) { return (size_t)((kp.nx + BX - 1) / BX) * ((kp.ny + BY - 1) / BY); }
+
 // the fewest planes that leave one workgroup per CU, else 4 (32^3: 1, 2, 4
 // planes take 16.9, 18.2, 22.1 us per FP64 step; 64^3: 50.8, 44.0, 40.4), but no
 // more than the grid has (one plane of 700 x 700, chunks of 4 / 1: FP64 101 / 77,
 // FP32 83 / 55)
 static int block_chunk(const KP &kp) {
-    const size_t tiles = (size_t)((kp.nx + BX - 1) / BX) * ((kp.ny + BY - 1) / BY);
-    const size_t nzf = kp.z1 - kp.z0;
+    const size_t tiles = block_tiles(kp), nzf = kp.z1 - kp.z0;
     return tiles * nzf <= kCUs || nzf == 1 ? 1 : (tiles * ((nzf + 1) / 2) <= kCUs || nzf == 2 ? 2 : 4);
 }
 
@@ -884,23 +885,36 @@ static hipError_t go_block(hipStream_t s, const KP &kp, const Bufs &b, int cz, c
     return hipGetLastError();
 }
 
+// Node slots that the blocks of a one-launch FP64 step work through: whole
+// tiles and chunks, and once more a chunk for every solid plane that its region
+// of three planes beyond it reaches, whose density it forms.
+static size_t block_slots(const KP &kp, int cz) {
+    const size_t chunks = (kp.z1 - kp.z0 + cz - 1) / cz, beside = min(chunks, (size_t)(2 / cz + 1));
+    return block_tiles(kp) * BX * BY * cz * (chunks + (kp.walls ? 2 * beside : 0));
+}
+
 // Planes per block of the step that runs chain and collide-stream in one
 // launch (0: two).  It saves a launch and the 7 fields between the two, and
-// pays with latency that few resident blocks hide: FP64 gains to 1.5e6 nodes
-// (us per step, two launches / one: 32^3 19.6 / 16.7, 64^3 49.4 / 40.4, 101 x
-// 67 x 53 77.6 / 70.1, 96^3 133 / 123, 112^3 203 / 192, 128^3 293 / 302), FP32
-// to 2^19 (32^3 16.6 / 14.0, 64^3 33.6 / 30.8, 80^3 59.4 / 53.9, 96^3 80.5 /
-// 84.2), FP16 populations to 5 x 2^16 (32^3 16.2 / 13.1, 64^3 34.2 / 31.0,
-// 101 x 67 x 53 between walls 49.0 / 49.8).  Between walls FP64 blocks of 4
-// planes take the LDS of one block per CU: 2 planes (80^3 84.0 against 91.8;
-// two launches 90.5).
+// pays with latency that few resident blocks hide and with the slots of its
+// last tiles and chunks.  FP64 gains to 1.5e6 slots (us per step, two launches /
+// one: 32^3 19.6 / 16.7, 64^3 49.4 / 40.4, 101 x 67 x 53 77.6 / 70.1, 96^3 135 /
+// 122, 112^3 199 / 193, but 116^3 262 / 273 and 512 x 512 x 5 189 / 245 on 1.8e6
+// and 2.1e6 slots), between walls to 2^20 (still, moving: 80^3 89 / 84, 95 / 83;
+// 88^3 119 / 116, 127 / 122; 96^3 139 / 136, 145 / 146; but 104^3 180 / 197, 187 /
+// 201; 192 x 192 x 24 132 / 138, 141 / 157; 400 x 400 x 5 89 / 113, 102 / 128).  FP32
+// gains to 2^19 nodes (32^3 16.6 / 14.0, 64^3 33.6 / 30.8, 80^3 53.2 / 46.9, walls
+// 58.6 / 49.8, moving 67.6 / 51.0, 96^3 80.5 / 84.2), FP16 populations to 5 x 2^16
+// (32^3 16.6 / 12.9, 64^3 31.4 / 27.6, 101 x 67 x 45 33.4 / 34.6, walls 40.9 / 37.3).
+// Between walls FP64 blocks of 4 planes take the LDS of one block per CU: 2
+// planes (80^3 83 against 88).
 int step_block_chunk(const KP &kp, int prec) {
-    const size_t limit = prec == LBFE_FP64 ? 3u << 19 : (prec == LBFE_FP32 ? 1u << 19 : 5u << 16);
-    if (kp.masked || kp.nfluid >= limit) return 0;
+    if (kp.masked) return 0;
     const int given = kp.chain_cz;
-    if (given > 0) return (given == 1 || given == 2 || given == 4) && block_chunks_fit(kp, given) ? given : 0;
-    const int cz = min(block_chunk(kp), kp.walls && prec == LBFE_FP64 ? 2 : 4);
-    return block_chunks_fit(kp, cz) ? cz : 0;
+    if (given > 0 && given != 1 && given != 2 && given != 4) return 0;
+    const int cz = given > 0 ? given : min(block_chunk(kp), kp.walls && prec == LBFE_FP64 ? 2 : 4);
+    const bool small = prec == LBFE_FP64 ? block_slots(kp, cz) < (kp.walls ? 1u << 20 : 3u << 19)
+                                         : kp.nfluid < (prec == LBFE_FP32 ? 1u << 19 : 5u << 16);
+    return small && block_chunks_fit(kp, cz) ? cz : 0;
 }
 
 hipError_t launch_step_block(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur) {

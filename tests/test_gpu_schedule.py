@@ -31,6 +31,29 @@ def test_reported_parameters_give_the_same_schedule(shape):
     assert max(part) < 0.5
 
 
+OM = [1.0, 1.0, 1.0, 0.5] + [1.0] * 7
+
+
+@pytest.mark.parametrize("wall_u", [(0.0, 0.0, 0.0, 0.0), (0.02, 0.0, -0.01, 0.01)])
+@pytest.mark.parametrize("shape,precision", [((90, 88, 90), "fp64"),     # one launch, non-temporal population loads
+                                             ((3, 701, 700), "fp32"),    # the same, both walls beside the one plane
+                                             ((5, 400, 400), "fp64"),    # two launches: mostly blocks beside a wall
+                                             ((4, 350, 701), "fp16dev_f0fp32")])  # chunks of the grid's two planes
+def test_walled_routes_equal_the_march(shape, precision, wall_u):
+    nz, ny, nx = shape
+    T = eos.temperature(0.8)
+    say(f"walled route: {shape} {precision} {wall_u}")
+    rho0 = torch.tensor(droplet_rho(shape, T, walls=True, radius=8.0))
+    out = []
+    for chunk in (0, 64):
+        sim = make_sim(nx=nx, ny=ny, nz=nz, T=T, walls_z=1, wet_mode=1, wet_value=1.2, omega=OM, precision=precision,
+                       wall_u=wall_u, chain_chunk=chunk)
+        sim.init_density(rho0)
+        sim.step(3)
+        out.append((sim.get_state(), sim.field(2)))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 @pytest.mark.parametrize("shape,precision", [((1, 300, 700), "fp64"), ((2, 301, 701), "fp32"), ((5, 512, 512), "fp64")])
 def test_thin_periodic_routes_equal_the_march(shape, precision):
     nz, ny, nx = shape
