@@ -163,8 +163,9 @@ int lbfe_coexistence(double a, double b, double R, double T, double *rho_l, doub
  * E_INVAL on a bad parameter (checked before any device call), E_DEVICE
  * when no GPU is usable.  Schedule fields left at LBFE_AUTO are chosen per
  * grid: the fused step path for FP64 contexts of at least 5 x 2^20 nodes and
- * FP32 contexts of at least 19 x 2^20 where it is allowed, else the two-pass
- * path; the XCD tile order from 2^26 nodes and, without a solid mask,
+ * FP32 contexts of at least 19 x 2^20 where it is allowed and the columns fill
+ * its tiles (or their rows and planes suit the two passes badly), else the
+ * two-pass path; the XCD tile order from 2^26 nodes and, without a solid mask,
  * whenever nx or ny is not a power of two; the chain chunk that minimises the
  * busiest CU's plane iterations, on grids below 2^19 fluid nodes the fewest of
  * 1, 2 and 4 planes that leave one workgroup per CU.

@@ -488,13 +488,14 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
     // 16850; FP32 192^3 540 / 650, 256^3 1335 / 1319 but between walls 1384 /
     // 1475, 301 x 205 x 330 2205 / 1986, 512^3 11400 / 10230).  In the FP16
     // forms the bytes saved are too few for its instructions (256^3 900 /
-    // 1159, 512^3 7490 / 8460).
+    // 1159, 512^3 7490 / 8460).  Grids whose columns leave its tiles half empty:
+    // fused_fills.
     const bool fused_ok = fused_possible(q);
     if (q.step_path == LBFE_AUTO) {
         const bool large = q.precision == LBFE_FP64   ? k.N >= (5u << 20)
                            : q.precision == LBFE_FP32 ? k.N >= (19u << 20)
                                                       : false;
-        q.step_path = fused_ok && large ? LBFE_PATH_FUSED : LBFE_PATH_TWO_PASS;
+        q.step_path = fused_ok && large && fused_fills(q.precision, k.nx, k.ny) ? LBFE_PATH_FUSED : LBFE_PATH_TWO_PASS;
     }
     if (q.step_path == LBFE_PATH_FUSED && !fused_ok) {
         std::fprintf(stderr, "lbfe_create: the fused step path needs no solid mask and a lattice z-plane below "

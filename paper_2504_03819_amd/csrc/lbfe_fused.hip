@@ -271,6 +271,27 @@ bool fused_plane_ok(int prec, size_t plane) {
     return bytes < kOOB;
 }
 
+// Its work goes by whole tiles, while the two passes lose only where rows are no
+// whole 128-byte lines (the shifted stores then write parts of lines) and three
+// planes of the lattice, which the stream of stores spans, exceed the 4 MiB of
+// an XCD's L2.  So a grid takes it whose columns fill the tiles, or whose rows
+// and planes are of that kind (us per step, two passes / fused, periodic: FP64
+// filled to 0.96, 160 x 150 x 394 1489 / 1366; to 0.51 with small planes, 300 x 14 x
+// 1399 1007 / 1334; to 0.70 with large ones, 70 x 300 x 749 3445 / 3165; FP32 to 0.46
+// with small planes, 65 x 65 x 4964 2514 / 2923; to 0.50 in whole lines, 32 x 544 x
+// 1982 3204 / 3962; to 0.76 in part lines, 97 x 708 x 442 3770 / 3274).  The line is
+// lower in FP64, whose bytes hide more of the work: whole-line rows filled to
+// 0.80, 80 x 226 x 762, are 8 % faster fused, in FP32 to 0.82, 160 x 150 x 874, 6 %
+// slower.
+bool fused_fills(int prec, unsigned nx, unsigned ny) {
+    const bool wide = prec == LBFE_FP64;
+    const unsigned tx = wide ? Tile<LBFE_FP64>::TX : Tile<LBFE_FP32>::TX, ty = wide ? Tile<LBFE_FP64>::TY : Tile<LBFE_FP32>::TY;
+    const size_t plane = (size_t)nx * ny, slots = (size_t)((nx + tx - 1) / tx * tx) * ((ny + ty - 1) / ty * ty);
+    if (plane * 100 >= slots * (wide ? 70 : 85)) return true;
+    const size_t row = nx * real_bytes(prec);
+    return row % 128 != 0 && 3 * 27 * ny * row > ((size_t)4 << 20);
+}
+
 hipError_t launch_fused(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur) {
     switch (prec) {
         case LBFE_FP64: return launch<LBFE_FP64>(s, kp, b, cur);

@@ -73,9 +73,11 @@ hipError_t launch_aux(hipStream_t s, int prec, const KP &kp, const Bufs &b, int 
 hipError_t launch_step(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur, bool fused, bool refresh,
                        bool keep, hipEvent_t *ev5);
 // collide + stream + rho, j, mu0 of the streamed state (lbfe_fused.hip);
-// fused_plane_ok: one z-plane of the lattice fits its 32-bit plane offsets
+// fused_plane_ok: one z-plane of the lattice fits its 32-bit plane offsets;
+// fused_fills: a large grid of nx x ny columns is faster with it (FP64, FP32)
 hipError_t launch_fused(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur);
 bool fused_plane_ok(int prec, size_t plane);
+bool fused_fills(int prec, unsigned nx, unsigned ny);
 // Moment-representation state (lbfe_moment.hip), for unit rates but omega_1:
 // passes over a state lattice `sin` (16 values per node): kStateMoments forms
 // rho, j, mu0 of the streamed state, kStatePops also writes its populations

@@ -1,9 +1,12 @@
 """The schedules that lbfe_create chooses."""
+import ctypes
+
 import pytest
 import torch
 
 from gpu_util import droplet_rho, make_sim, say
 from oracle import eos
+from paper_2504_03819_amd import lbfe
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +70,22 @@ def test_thin_periodic_routes_equal_the_march(shape, precision):
         sim.step(3)
         out.append((sim.get_state(), sim.field(2)))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("nx,ny,nz,precision,path", [
+    (256, 256, 256, "fp64", 2), (160, 150, 245, "fp64", 2), (200, 90, 327, "fp64", 2), (80, 226, 762, "fp64", 2),
+    (50, 95, 1300, "fp64", 2),
+    (70, 300, 280, "fp64", 2), (33, 200, 890, "fp64", 2),                          # part lines, large planes
+    (300, 14, 1399, "fp64", 1), (40, 40, 3671, "fp64", 1), (65, 65, 1390, "fp64", 1), (96, 27, 2266, "fp64", 1),
+    (512, 512, 512, "fp32", 2), (320, 320, 320, "fp32", 2), (301, 205, 330, "fp32", 2), (97, 708, 442, "fp32", 2),
+    (65, 65, 4964, "fp32", 1), (40, 40, 13108, "fp32", 1), (32, 544, 1982, "fp32", 1), (160, 150, 874, "fp32", 1),
+    (160, 160, 160, "fp64", 1), (256, 256, 256, "fp32", 1), (512, 512, 512, "fp16dev_f0fp32", 1)])
+def test_step_path_of_large_grids(nx, ny, nz, precision, path):
+    """The path chosen: fused where the columns fill its tiles, or where their
+    rows are no whole lines and their planes exceed an XCD's L2."""
+    p = lbfe.default_params(nx=nx, ny=ny, nz=nz, precision=precision)
+    ctx, q = ctypes.c_void_p(), lbfe.Params()
+    assert lbfe.lib().lbfe_create(ctypes.byref(p), None, ctypes.byref(ctx)) == lbfe.OK
+    assert lbfe.lib().lbfe_get_params(ctx, ctypes.byref(q)) == lbfe.OK
+    lbfe.lib().lbfe_destroy(ctx)
+    assert q.step_path == path
