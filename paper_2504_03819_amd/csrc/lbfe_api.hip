@@ -446,20 +446,27 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
         q.tile_order = (k.N >= (1u << 26) || (irregular && !k.masked)) ? LBFE_ORDER_XCD : LBFE_ORDER_ROUND_ROBIN;
     k.xcd_remap = q.tile_order == LBFE_ORDER_XCD;
     // Populations are read non-temporal unless the 256 MB last-level cache
-    // holds them until they are read again.  A lattice that takes less than
-    // 336 MiB with its fields is still there, in good part, when the collide
-    // pass follows the moments pass (us per step, moments non-temporal / plain:
-    // FP64 96^3 124.8 / 118.8, 104^3 181 / 175, 112^3 193 / 211; FP32 120^3 154 /
-    // 146, 128^3 160 / 166; FP16 144^3 192 / 179, 192 x 192 x 96 192 / 201); with
-    // a lattice below 112 MiB both lattices and the fields stay from step to
-    // step and the collide pass too reads plain (both / moments only: FP64 64^3
-    // 39.7 / 41.8, 80^3 70.5 / 71.3, 101 x 67 x 53 60.0 against 72.8 without
+    // holds them until they are read again.  Where a lattice with the fields of
+    // its path is little larger than that, a good part is still there when the
+    // collide pass follows the moments pass.  The limits are crossovers of
+    // measured steps, not properties of the cache: of 150 boxes from 150 to 450
+    // MiB, those with rows of whole 128-byte lines gain from plain moments loads
+    // up to about 300 MiB, the others to 345 (plain / non-temporal step time:
+    // whole lines, FP64 0.90 at 150 MiB, 0.96 at 300, 1.02 at 340, 1.10 at 400, FP32
+    // 0.97, 1.01, 1.02, 1.12, FP16 0.95, 0.98, 0.99, 1.08; else FP64 0.90, 0.96, 0.99,
+    // 1.08, FP32 0.97, 0.94, 0.98, 1.08, FP16 0.95, 0.97, 0.98, 1.06).  With a
+    // lattice below 112 MiB both lattices and the fields stay from step to
+    // step and the collide pass too reads plain (us per step, both / moments only:
+    // FP64 64^3 39.7 / 41.8, 80^3 70.5 / 71.3, 101 x 67 x 53 60.0 against 72.8 without
     // either, 96^3 135 / 119; FP32 80^3 47.7 / 54.2, 104^3 101.7 / 99.0; FP16
     // 120^3 114.6 / 115.1).  A reverse sweep also reads lambda and recorded
     // states: half of it (96^3 FP32 forward and back 3555 / 3650 us, plain).
     const size_t sets = q.adjoint ? 2 : 1, lattice = pop_bytes(q.precision, k.N) * sets;
-    const size_t fields = (24 + 9 * real_bytes(q.precision)) * k.N * sets;
-    k.keep1 = lattice + fields < ((size_t)336 << 20);
+    const size_t real = real_bytes(q.precision);
+    size_t node = 24 + 9 * real;  // rho, mu, mu0; j, F, Q
+    if (k.masked) node += 4 + (q.precision == LBFE_FP64 ? 0 : 3 * real);  // neighbour word, phi
+    const size_t row = k.nx * (q.precision == LBFE_FP64 ? 8 : (q.precision == LBFE_FP32 ? 4 : 2));
+    k.keep1 = lattice + node * k.N * sets < ((size_t)(row % 128 == 0 ? 304 : 344) << 20);
     k.keep2 = lattice < ((size_t)112 << 20);
     // Planes per workgroup of the stencil chain, chosen per grid unless given.
     // Given as it would be chosen (lbfe_get_params reports the choice), the
