@@ -138,13 +138,15 @@ template <bool NT> struct Pops<LBFE_FP16_DEV_F0FP32, NT> {
 // xcd_remap the tile index is permuted so that every XCD owns one
 // contiguous range of tiles (neighbouring rows share that XCD's L2).
 // A kernel that reads what the one before it wrote last takes its tiles in
-// descending order: the last-level cache (256 MB) still holds the end of it.
+// descending order, each XCD its own: the last-level cache (256 MB) still holds
+// the end of it, or the XCD's L2 all of a small grid.
 // ---------------------------------------------------------------------------
 __device__ inline unsigned tile_id(const KP &kp, bool descending = false) {
     const unsigned b = blockIdx.x, nb = gridDim.x;
-    if (!kp.xcd_remap) return descending ? nb - 1 - b : b;
-    const unsigned q = nb >> 3, r = nb & 7u, k = b & 7u, i = b >> 3;
-    return k * q + (k < r ? k : r) + (descending ? q + (k < r ? 1 : 0) - 1 - i : i);
+    if (!kp.xcd_remap && !descending) return b;
+    const unsigned q = nb >> 3, r = nb & 7u, k = b & 7u;
+    const unsigned i = descending ? q + (k < r ? 1 : 0) - 1 - (b >> 3) : b >> 3;
+    return kp.xcd_remap ? k * q + (k < r ? k : r) + i : i * 8 + k;
 }
 
 // Neighbour offsets of node (x, y, z) with periodic wrap: X, Y, Z give node
