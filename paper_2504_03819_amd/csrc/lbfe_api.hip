@@ -451,7 +451,7 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
     // collide pass follows the moments pass.  The limits are crossovers of
     // measured steps, not properties of the cache: of 150 boxes from 150 to 450
     // MiB, those with rows of whole 128-byte lines gain from plain moments loads
-    // up to about 300 MiB, the others to 345 (plain / non-temporal step time:
+    // up to about 320 MiB, the others to 345 (plain / non-temporal step time:
     // whole lines, FP64 0.90 at 150 MiB, 0.96 at 300, 1.02 at 340, 1.10 at 400, FP32
     // 0.97, 1.01, 1.02, 1.12, FP16 0.95, 0.98, 0.99, 1.08; else FP64 0.90, 0.96, 0.99,
     // 1.08, FP32 0.97, 0.94, 0.98, 1.08, FP16 0.95, 0.97, 0.98, 1.06).  With a
@@ -466,7 +466,7 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
     size_t node = 24 + 9 * real;  // rho, mu, mu0; j, F, Q
     if (k.masked) node += 4 + (q.precision == LBFE_FP64 ? 0 : 3 * real);  // neighbour word, phi
     const size_t row = k.nx * (q.precision == LBFE_FP64 ? 8 : (q.precision == LBFE_FP32 ? 4 : 2));
-    k.keep1 = lattice + node * k.N * sets < ((size_t)(row % 128 == 0 ? 304 : 344) << 20);
+    k.keep1 = lattice + node * k.N * sets < ((size_t)(row % 128 == 0 ? 320 : 344) << 20);
     k.keep2 = lattice < ((size_t)112 << 20);
     // Planes per workgroup of the stencil chain, chosen per grid unless given.
     // Given as it would be chosen (lbfe_get_params reports the choice), the
