@@ -89,3 +89,30 @@ def test_step_path_of_large_grids(nx, ny, nz, precision, path):
     assert lbfe.lib().lbfe_get_params(ctx, ctypes.byref(q)) == lbfe.OK
     lbfe.lib().lbfe_destroy(ctx)
     assert q.step_path == path
+
+
+@pytest.mark.parametrize("wall_u", [(0.0, 0.0, 0.0, 0.0), (0.02, 0.0, -0.01, 0.01)])
+@pytest.mark.parametrize("shape,precision", [((3, 14, 33), "fp64"), ((4, 9, 65), "fp32"), ((11, 27, 40), "fp64"),
+                                             ((9, 10, 64), "fp16dev_f0fp32")])
+def test_fused_step_with_the_march_between_walls(shape, precision, wall_u):
+    """On large grids the march, not the fused step, leaves the solid planes'
+    density: until the chain runs they hold what the step kept there.  State,
+    every field and the reductions against the two-pass block form."""
+    nz, ny, nx = shape
+    T = eos.temperature(0.8)
+    say(f"fused step and march: {shape} {precision} {wall_u}")
+    rho0 = torch.tensor(droplet_rho(shape, T, walls=True, radius=4.0))
+    kw = dict(nx=nx, ny=ny, nz=nz, T=T, walls_z=1, wet_mode=1, wet_value=1.2, omega=OM, precision=precision, wall_u=wall_u)
+    ref = make_sim(step_path=lbfe.PATH_TWO_PASS, **kw)
+    sims = [make_sim(step_path=lbfe.PATH_FUSED, chain_chunk=c, **kw) for c in (3, 64)]
+    for s in (ref, *sims):
+        s.init_density(rho0)
+    for n in (1, 2):
+        ref.step(n)
+        for s in sims:
+            s.step(n)
+            red = s.reduce()  # the first reader after a step
+            assert red == ref.reduce()
+            for which in range(6):
+                assert torch.equal(s.field(which), ref.field(which)), (n, which)
+            assert torch.equal(s.get_state(), ref.get_state())
