@@ -856,15 +856,19 @@ static void go_block(hipStream_t s, const KP &kp, const Bufs &b, const void *fin
     // 256 threads hold the 240 mu columns; next to walls, with 308, 512 are
     // faster where a block has work for them (us per step at 96^3 FP64 145
     // against 148 with 256 and 158 with 320; at 32^3 22.6 against 21.9).
-    // Blocks that also collide: 512 for 4 planes of the narrow forms (80^3
-    // FP16 47.8 against 49.6, walls 52.8 against 56.7), but in FP64 the
-    // populations of 512 nodes leave one block per CU (80^3 85.9 against 72.8)
+    // Blocks that also collide: 512 for 4 planes of the narrow forms (80^3 FP32
+    // 46.5 against 47.5, walls 49.5 / 52.1; 67 x 63 x 61 FP16 32.4 / 33.7, walls 35.7 /
+    // 40.0; 64^3 periodic alone 28.2 / 27.3), but in FP64 the populations of 512
+    // nodes leave one block per CU (80^3 85.9 against 72.8)
     constexpr int NT = CZ == 4 && (WALLS || (P != kFields && sizeof(real) == 4)) ? 512 : 256;
-    const dim3 g((kp.nx + BX - 1) / BX * ((kp.ny + BY - 1) / BY), (kp.z1 - kp.z0 + CZ - 1) / CZ);
-    if (P == kFields || kp.keep2)
+    // a step's lattice that the last-level cache does not hold: not in the FP16
+    // forms, 105 MiB at most at their limit of nodes
+    constexpr bool beyond = P == LBFE_FP64 || P == LBFE_FP32;
+    const dim3 g(block_tiles(kp), (kp.z1 - kp.z0 + CZ - 1) / CZ);
+    if (!beyond || kp.keep2)
         k_chain_block<P, real, WALLS, BX, BY, CZ, NT, false>
             <<<g, NT, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, fin, fout);
-    else if constexpr (P != kFields)
+    else if constexpr (beyond)
         k_chain_block<P, real, WALLS, BX, BY, CZ, NT, true>
             <<<g, NT, 0, s>>>(kp, b.rho, b.mu0, b.j, b.mu, b.F, b.Q, fin, fout);
 }

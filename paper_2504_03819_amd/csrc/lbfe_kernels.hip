@@ -189,20 +189,8 @@ __global__ __launch_bounds__(kBlock) void k_wall_move_fused(KP kp, void *fq, dou
     const size_t n = (size_t)z * kp.plane + p;
     const unsigned row = (unsigned)z * (unsigned)kp.ny + y;
     const Pops<P> f(fq, kp);
-    const double rt = rho[(size_t)(side ? kp.nz - 1 : 0) * kp.plane + p];  // rho(t), kept by k_wall_keep
-    const real r = (real)rt, pm = (real)((1.0 + mu[n]) * (1.0 / 3.0));
-    real fe[27];
-    for (int w = 0; w < 2; ++w) {  // bottom, top
-        const bool hit = w == 0 ? z == 1 : z == kp.nz - 2;
-        if (!hit) continue;
-        wall_equilibrium(r, pm, (real)kp.wall_u[2 * w], (real)kp.wall_u[2 * w + 1], fe);
-#pragma unroll
-        for (int i = 0; i < 27; ++i) {
-            const int cz = czi(i);
-            if ((w == 0 && cz < 0) || (w == 1 && cz > 0))
-                f.st(26 - i, row, x, f.ld(26 - i, row, x) - (fe[i] - fe[26 - i]));
-        }
-    }
+    // rho(t), kept by k_wall_keep
+    wall_move_node<P>(kp, f, rho[(size_t)(side ? kp.nz - 1 : 0) * kp.plane + p], mu[n], z, row, x);
     real v[27];
 #pragma unroll
     for (int i = 0; i < 27; ++i) v[i] = f.ld(i, row, x);
@@ -380,10 +368,8 @@ __global__ __launch_bounds__(kBlock) void k_set_pop(KP kp, void *fq, const unsig
 }
 
 // --------------------------------------------------------------------------
-// One step's launches.  With `ev` non-null, HIP events ev[0..4] bracket the
-// four kernel classes in the order: moments (with the wall density that
-// follows them), chain, collide-stream, wall density after the step.
-// (without non-temporal loads while the lattice stays in the last-level cache)
+// rho, j and mu0 of f[cur] (without non-temporal loads while the lattice stays
+// in the last-level cache)
 template <int P> void moments_pass(hipStream_t s, const KP &kp, const Bufs &b, int cur) {
     const unsigned g = nblocks(kp.nfluid);
     if (kp.keep1)
@@ -409,6 +395,9 @@ hipError_t aux_impl(hipStream_t s, const KP &kp, const Bufs &b, int cur, bool re
     return hipGetLastError();
 }
 
+// One step's launches.  With `ev` non-null, HIP events ev[0..4] bracket the
+// four kernel classes in the order: moments (with the wall density that
+// follows them), chain, collide-stream, wall density after the step.
 // Fused path: rho, j, mu0 of f[cur] are current unless `refresh`; the fused
 // kernel leaves them current for f[1 - cur].
 template <int P>
@@ -507,7 +496,6 @@ hipError_t launch_step(hipStream_t s, int prec, const KP &kp, const Bufs &b, int
 // Moment-state launch groups (the kernels are in lbfe_moment.hip)
 hipError_t launch_state_enter(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur, bool refresh,
                               hipEvent_t *ev) {
-    const unsigned gf = nblocks(kp.nfluid), gw = nblocks(2 * (size_t)kp.plane);
     if (ev) (void)hipEventRecord(ev[0], s);
     if (refresh) {
         hipError_t e = dispatch(prec, [&](auto pc) {

@@ -250,22 +250,21 @@ __global__ __launch_bounds__(kBlock) void k_check_rho_m(KP kp, const unsigned *n
 // grad_h mu = 3 sum_i w_i c_i mu(x + c_i), F = (1/3 - rho) grad_h mu,
 // u = (j + F/2)/rho, phi = (p_m - rho/3) u; F = phi = 0 at solid nodes.
 __global__ __launch_bounds__(ZCB) void k_mu_z(KP kp, const unsigned *nbr, const double *rho, double *mu, int cz) {
-    __shared__ double lds[4][1][ZNR];
+    __shared__ double lds[4][ZNR];
     int x0, y0, zs, ze;
-    ztile(kp, cz, 0, kp.nz, x0, y0, zs, ze);
-    ZRing<1> R;
-    R.init(kp, lds, x0, y0);
-    R.src[0] = rho;
+    ztile(kp, cz, x0, y0, zs, ze);
+    ZRing R;
+    R.init(kp, lds, rho, x0, y0);
     R.march(zs, ze, [&](int k) {
         if (!R.own) return;
         const size_t n = (size_t)k * kp.plane + R.node;
         if (solid_at(nbr[n])) return;
-        const double r0 = R.at(0, k, 0, 0);
+        const double r0 = R.at(k, 0, 0);
         double s = 0.0;
 #pragma unroll
         for (int i = 0; i < 27; ++i) {
             if (i == kRest) continue;
-            s += wi(i) * (R.at(0, k + czi(i), cxi(i), cyi(i)) - r0);
+            s += wi(i) * (R.at(k + czi(i), cxi(i), cyi(i)) - r0);
         }
         mu[n] = mu_bulk(kp, r0) - kp.kappa * 6.0 * s;
     });
@@ -275,15 +274,14 @@ template <int P>
 __global__ __launch_bounds__(ZCB) void k_fphi_z(KP kp, const unsigned *nbr, const double *rho, const void *jq,
                                                 const double *mu, void *Fq, void *phiq, int cz) {
     using real = real_t<P>;
-    __shared__ double lds[4][1][ZNR];
+    __shared__ double lds[4][ZNR];
     int x0, y0, zs, ze;
-    ztile(kp, cz, 0, kp.nz, x0, y0, zs, ze);
+    ztile(kp, cz, x0, y0, zs, ze);
     const size_t N = kp.N;
     real *F = (real *)Fq, *phi = (real *)phiq;
     const real *j = (const real *)jq;
-    ZRing<1> R;
-    R.init(kp, lds, x0, y0);
-    R.src[0] = mu;
+    ZRing R;
+    R.init(kp, lds, mu, x0, y0);
     R.march(zs, ze, [&](int k) {
         if (!R.own) return;
         const size_t n = (size_t)k * kp.plane + R.node;
@@ -295,7 +293,7 @@ __global__ __launch_bounds__(ZCB) void k_fphi_z(KP kp, const unsigned *nbr, cons
 #pragma unroll
         for (int i = 0; i < 27; ++i) {
             if (i == kRest) continue;
-            const double v = 3.0 * wi(i) * R.at(0, k + czi(i), cxi(i), cyi(i));
+            const double v = 3.0 * wi(i) * R.at(k + czi(i), cxi(i), cyi(i));
             if (cxi(i)) gx += cxi(i) * v;
             if (cyi(i)) gy += cyi(i) * v;
             if (czi(i)) gz += czi(i) * v;
@@ -307,7 +305,7 @@ __global__ __launch_bounds__(ZCB) void k_fphi_z(KP kp, const unsigned *nbr, cons
         const real ux = (j[n] + (real)0.5 * Fx) * ir;
         const real uy = (j[N + n] + (real)0.5 * Fy) * ir;
         const real uz = (j[2 * N + n] + (real)0.5 * Fz) * ir;
-        const real c2 = (real)((1.0 + R.at(0, k, 0, 0) - rd) * (1.0 / 3.0));  // p_m - rho/3
+        const real c2 = (real)((1.0 + R.at(k, 0, 0) - rd) * (1.0 / 3.0));  // p_m - rho/3
         F[n] = Fx;
         F[N + n] = Fy;
         F[2 * N + n] = Fz;
@@ -514,7 +512,7 @@ template <int P> void chain_m(hipStream_t s, const KP &kp, const Bufs &b) {
         k_wall_mu_m<<<g, kBlock, 0, s>>>(kp, b.nbr, b.mu);
         fq_f(s, kp, b);
     } else {
-        const dim3 gz = zgrid(kp, 0, kp.nz);
+        const dim3 gz = zgrid(kp);
         k_mu_z<<<gz, ZCB, 0, s>>>(kp, b.nbr, b.rho, b.mu, kZChunk);
         k_wall_mu_m<<<g, kBlock, 0, s>>>(kp, b.nbr, b.mu);
         k_fphi_z<P><<<gz, ZCB, 0, s>>>(kp, b.nbr, b.rho, b.j, b.mu, b.F, b.phi, kZChunk);

@@ -1,5 +1,5 @@
-// z-marching LDS ring for 27-point stencils over a few scalar fields, summed
-// point by point: the solid-mask path's stencils of the FP32 and FP16 forms.
+// z-marching LDS ring for 27-point stencils of one scalar field, summed point by
+// point: the solid-mask path's stencils of the FP32 and FP16 forms.
 #pragma once
 
 #include "lbfe_internal.h"
@@ -9,12 +9,11 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // z-marching stencil tiles.  A workgroup owns a 32 x 16 column tile of one
-// z-chunk.  The stencil inputs of four consecutive planes (tile + one-node
-// halo) sit in an LDS ring; plane k+2 is loaded into
+// z-chunk.  The field on four consecutive planes (tile + one-node
+// halo) sits in an LDS ring; plane k+2 is loaded into
 // registers while plane k is evaluated, so one barrier per plane suffices
 // (the slot written at plane k+1 was last read at plane k-2).  Plane indices
-// wrap periodically, as in the forward kernels; in a walled box the
-// wrapped planes are solid and the fields read there are zero or unused.
+// wrap periodically.
 // ---------------------------------------------------------------------------
 constexpr int ZTX = 32, ZTY = 16, ZWX = ZTX + 2, ZNR = ZWX * (ZTY + 2), ZCB = ZTX * ZTY;
 constexpr int ZM = (ZNR + ZCB - 1) / ZCB;  // halo-region points per thread
@@ -24,24 +23,20 @@ __device__ inline int zwrap(int v, int n) {
     return v < 0 ? v + n : v;
 }
 
-template <int NF> struct ZRing {
-    double (*lds)[NF][ZNR];  // [4][NF][ZNR]
-    const double *src[NF];
-    const float *srcf[NF];  // field f is read from here instead when bit f of fmask is set
-    unsigned fmask;
+struct ZRing {
+    double (*lds)[ZNR];  // [4][ZNR]
+    const double *src;
     int a, b, tid, nz;
     bool own;       // the tile point is inside the grid
     unsigned node;  // its in-plane index
     unsigned plane;
     unsigned off[ZM];
     bool has[ZM];
-    double pre[NF][ZM];
-    unsigned zmask;  // fields zeroed on non-fluid planes (bit f)
-    const KP *kp;
+    double pre[ZM];
 
-    __device__ void init(const KP &k, double (*l)[NF][ZNR], int x0, int y0) {
-        kp = &k;
+    __device__ void init(const KP &k, double (*l)[ZNR], const double *field, int x0, int y0) {
         lds = l;
+        src = field;
         tid = threadIdx.x;
         a = tid % ZTX;
         b = tid / ZTX;
@@ -49,8 +44,6 @@ template <int NF> struct ZRing {
         plane = k.plane;
         own = x0 + a < k.nx && y0 + b < k.ny;
         node = own ? (unsigned)(y0 + b) * k.nx + (x0 + a) : 0u;
-        zmask = 0;
-        fmask = 0;
 #pragma unroll
         for (int m = 0; m < ZM; ++m) {
             const int r = tid + m * ZCB;
@@ -60,27 +53,18 @@ template <int NF> struct ZRing {
         }
     }
     __device__ void load(int p) {
-        const int zz = zwrap(p, nz);
-        const size_t base = (size_t)zz * plane;
-        const bool fl = zz >= kp->z0 && zz < kp->z1;
+        const size_t base = (size_t)zwrap(p, nz) * plane;
 #pragma unroll
-        for (int f = 0; f < NF; ++f)
-#pragma unroll
-            for (int m = 0; m < ZM; ++m)
-                if (has[m])
-                    pre[f][m] = ((zmask >> f) & 1) && !fl ? 0.0
-                                : ((fmask >> f) & 1)     ? (double)srcf[f][base + off[m]]
-                                                         : src[f][base + off[m]];
+        for (int m = 0; m < ZM; ++m)
+            if (has[m]) pre[m] = src[base + off[m]];
     }
     __device__ void commit(int p) {
 #pragma unroll
-        for (int f = 0; f < NF; ++f)
-#pragma unroll
-            for (int m = 0; m < ZM; ++m)
-                if (has[m]) lds[p & 3][f][tid + m * ZCB] = pre[f][m];
+        for (int m = 0; m < ZM; ++m)
+            if (has[m]) lds[p & 3][tid + m * ZCB] = pre[m];
     }
-    // field f at (x + dx, y + dy, plane p)
-    __device__ double at(int f, int p, int dx, int dy) const { return lds[p & 3][f][(b + 1 + dy) * ZWX + a + 1 + dx]; }
+    // the field at (x + dx, y + dy, plane p)
+    __device__ double at(int p, int dx, int dy) const { return lds[p & 3][(b + 1 + dy) * ZWX + a + 1 + dx]; }
     // planes [zs, ze) of the chunk, body(k) once per plane after the barrier
     template <class Body> __device__ void march(int zs, int ze, Body body) {
         load(zs - 1);
@@ -97,19 +81,19 @@ template <int NF> struct ZRing {
     }
 };
 
-__device__ inline void ztile(const KP &kp, int cz, int zlo, int zhi, int &x0, int &y0, int &zs, int &ze) {
+__device__ inline void ztile(const KP &kp, int cz, int &x0, int &y0, int &zs, int &ze) {
     const int ntx = (kp.nx + ZTX - 1) / ZTX;
     x0 = (int)(blockIdx.x % ntx) * ZTX;
     y0 = (int)(blockIdx.x / ntx) * ZTY;
-    zs = zlo + (int)blockIdx.y * cz;
-    ze = min(zs + cz, zhi);
+    zs = (int)blockIdx.y * cz;
+    ze = min(zs + cz, kp.nz);
 }
 
-// Grid of z-marching kernels over planes [zlo, zhi).
+// Grid of the z-marching kernels.
 constexpr int kZChunk = 16;
-dim3 zgrid(const KP &kp, int zlo, int zhi) {
+dim3 zgrid(const KP &kp) {
     const unsigned ntx = (kp.nx + ZTX - 1) / ZTX, nty = (kp.ny + ZTY - 1) / ZTY;
-    return dim3(ntx * nty, (unsigned)((zhi - zlo + kZChunk - 1) / kZChunk));
+    return dim3(ntx * nty, (unsigned)((kp.nz + kZChunk - 1) / kZChunk));
 }
 
 }  // namespace
