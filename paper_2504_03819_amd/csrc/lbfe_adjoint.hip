@@ -837,8 +837,8 @@ __global__ __launch_bounds__(RNT) void k_adj_rho(KP kp, const double *mub, const
     }
 }
 
-// rho_ave_bar = W'(rho_ave) rho_bar(x_s) of a solid node of a wall plane with
-// wall average rave and rho_bar g; wet receives dL/d(wet_value) = dW/d(wet)
+// rho_ave_bar = W'(rho_ave) rho_bar(x_s) of a solid node with wall average rave
+// and rho_bar g; wet receives dL/d(wet_value) = dW/d(wet)
 // rho_bar(x_s) (active branch of Eq. (38)).
 __device__ inline double wall_rho_bar(const KP &kp, double rave, double g, double &wet) {
     double dW = 1.0, dwet = 0.0;
@@ -993,23 +993,7 @@ __global__ __launch_bounds__(kBlock) void k_adj_wall_rho_solid_m(KP kp, const un
             den += wt;
         }
         if (den > 0.0) {
-            const double rave = num / den, g = rhobt[n];
-            double dW = 1.0, dwet = 0.0;
-            if (rave >= kp.lo && rave <= kp.hi) {
-                if (kp.wet_mode == LBFE_WET_PHI) {
-                    const double v = kp.wet_value * rave;
-                    const bool inside = v >= kp.lo && v <= kp.hi;
-                    dW = inside ? kp.wet_value : 0.0;
-                    dwet = inside ? rave : 0.0;
-                } else if (kp.wet_mode == LBFE_WET_DELTA) {
-                    const double v = rave - kp.wet_value;
-                    const bool inside = v >= kp.lo && v <= kp.hi;
-                    dW = inside ? 1.0 : 0.0;
-                    dwet = inside ? -1.0 : 0.0;
-                }
-            }
-            rb = dW * g;
-            wc = dwet * g;
+            rb = wall_rho_bar(kp, num / den, rhobt[n], wc);
         }
     }
     raveb[n] = rb;

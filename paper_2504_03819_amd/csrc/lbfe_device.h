@@ -567,9 +567,8 @@ __device__ inline double wall_average(const KP &kp, const double *g, int x, int 
     return num / den;
 }
 
-// Density of solid node (x, y) of wall plane zs, Eqs. (37)-(38).
-__device__ inline double wall_rho(const KP &kp, const double *rho, int x, int y, int zs) {
-    const double rave = wall_average(kp, rho, x, y, zs);
+// Density of a solid node whose fluid neighbours average to rave, Eq. (38).
+__device__ inline double window_rho(const KP &kp, double rave) {
     double out = rave;
     if (rave >= kp.lo && rave <= kp.hi) {  // contact-line window
         if (kp.wet_mode == LBFE_WET_PHI)
@@ -578,6 +577,11 @@ __device__ inline double wall_rho(const KP &kp, const double *rho, int x, int y,
             out = fmin(fmax(rave - kp.wet_value, kp.lo), kp.hi);
     }
     return out;
+}
+
+// Density of solid node (x, y) of wall plane zs, Eqs. (37)-(38).
+__device__ inline double wall_rho(const KP &kp, const double *rho, int x, int y, int zs) {
+    return window_rho(kp, wall_average(kp, rho, x, y, zs));
 }
 
 }  // namespace lbfe

@@ -100,15 +100,7 @@ __global__ __launch_bounds__(kBlock) void k_wall_rho_m(KP kp, const unsigned *nb
     if (n >= kp.N) return;
     const unsigned w = nbr[n];
     if (!solid_at(w)) return;
-    const double rave = fluid_average(kp, w, rho, n);
-    double out = rave;
-    if (rave >= kp.lo && rave <= kp.hi) {  // contact-line window
-        if (kp.wet_mode == LBFE_WET_PHI)
-            out = fmin(fmax(kp.wet_value * rave, kp.lo), kp.hi);
-        else if (kp.wet_mode == LBFE_WET_DELTA)
-            out = fmin(fmax(rave - kp.wet_value, kp.lo), kp.hi);
-    }
-    rho[n] = out;
+    rho[n] = window_rho(kp, fluid_average(kp, w, rho, n));
 }
 
 // mu = mu0(rho) - kappa lap_h rho, lap_h g = 6 sum_i w_i (g(x+c_i) - g(x))
