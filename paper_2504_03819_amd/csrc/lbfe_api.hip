@@ -148,18 +148,6 @@ bool fused_possible(const lbfe_params &p) {
     return !p.solid_mask && fused_plane_ok(p.precision, (size_t)p.nx * p.ny);
 }
 
-// mu0(rho): on large periodic grids the chain forms it from the density that it
-// stages anyway, and the workspace does not hold the field, which no pass
-// stores or reads (16 B per node and the halo's reads).  The logarithms
-// lengthen the chain's busiest waves, which only the bandwidth-bound sizes
-// hide (us per step, stored against formed: FP64 160^3 634 / 635, 200^3 1525 /
-// 1470, 256^3 2472 / 2453; FP32 160^3 309 / 330, 200^3 825 / 832, 256^3 1429 /
-// 1408; FP16 200^3 563 / 568, 256^3 940 / 885).
-bool mu0_in_chain(const lbfe_params &p) {
-    const size_t N = (size_t)p.nx * p.ny * p.nz;
-    return !p.walls_z && !p.solid_mask && N >= (p.precision == LBFE_FP64 ? 6u << 20 : 12u << 20);
-}
-
 size_t al(size_t x) { return (x + 255) & ~size_t(255); }
 
 Layout layout(const lbfe_params &p) {
@@ -174,7 +162,7 @@ Layout layout(const lbfe_params &p) {
     L.rho = take(8 * N);
     L.j = take(3 * rb * N);
     L.mu = take(8 * N);
-    if (!mu0_in_chain(p)) L.mu0 = take(8 * N);
+    L.mu0 = take(8 * N);
     L.F = take(3 * rb * N);
     L.Q = take(3 * rb * N);
     if (p.solid_mask) {
@@ -489,7 +477,14 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
     k.step_block = step_block_chunk(k, q.precision);
     if (q.chain_chunk == LBFE_AUTO) q.chain_chunk = chunk;
     k.chain_cz = q.chain_chunk;
-    k.mu0_in_chain = mu0_in_chain(q);
+    // mu0(rho): on large periodic grids the chain forms it from the density
+    // that it stages anyway, and no pass stores or reads the field (16 B per
+    // node and the halo's reads).  The logarithms lengthen the chain's busiest
+    // waves, which only the bandwidth-bound sizes hide (us per step, stored
+    // against formed: FP64 160^3 634 / 635, 200^3 1525 / 1470, 256^3 2472 /
+    // 2453; FP32 160^3 309 / 330, 200^3 825 / 832, 256^3 1429 / 1408; FP16
+    // 200^3 563 / 568, 256^3 940 / 885).
+    k.mu0_in_chain = !k.walls && !k.masked && k.N >= (q.precision == LBFE_FP64 ? 6u << 20 : 12u << 20);
     // Step path: the fused collide-stream-moments kernel reads the
     // populations once per step; it has no solid mask, and addresses one
     // z-plane of the lattice with 32-bit offsets.  It collides a ring around
@@ -537,7 +532,7 @@ int lbfe_bind_workspace(lbfe_ctx *c, void *ws, size_t bytes) {
     c->b.rho = (double *)(w + L.rho);
     c->b.j = w + L.j;
     c->b.mu = (double *)(w + L.mu);
-    c->b.mu0 = c->kp.mu0_in_chain ? nullptr : (double *)(w + L.mu0);
+    c->b.mu0 = (double *)(w + L.mu0);
     c->b.F = w + L.F;
     c->b.Q = w + L.Q;
     if (c->p.solid_mask) {

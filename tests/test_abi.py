@@ -150,14 +150,3 @@ def test_null_and_no_device_paths():
     p = lbfe.default_params()
     ctx = ctypes.c_void_p()
     assert L.lbfe_create(ctypes.byref(p), None, ctypes.byref(ctx)) == lbfe.E_DEVICE
-
-
-def test_large_periodic_workspace_holds_no_bulk_potential():
-    """Populations twice, rho, mu, j, F, Q and the reductions' partials (half a
-    byte per node): the 8 bytes of mu0 only where a pass stores it."""
-    N = 256 ** 3
-    for walls, low in ((0, 520), (1, 528)):
-        p = lbfe.default_params(nx=256, ny=256, nz=256, walls_z=walls)
-        n = ctypes.c_size_t()
-        assert lbfe.lib().lbfe_workspace_bytes(ctypes.byref(p), ctypes.byref(n)) == lbfe.OK
-        assert low * N <= n.value < (low + 1) * N
