@@ -138,12 +138,14 @@ template <bool NT> struct Pops<LBFE_FP16_DEV_F0FP32, NT> {
 // xcd_remap the tile index is permuted so that every XCD owns one
 // contiguous range of tiles (neighbouring rows share that XCD's L2).
 // A kernel that reads what the one before it wrote last takes its tiles in
-// descending order, each XCD its own: the last-level cache (256 MB) still holds
-// the end of it, or the XCD's L2 all of a small grid.
+// descending order: the last-level cache (256 MB) still holds the end of it, or
+// the XCDs' L2s good parts of a small grid, each of its own tiles, so there the
+// order is reversed within each XCD (masks of 32^3 in FP32 73.0 us a step with the
+// whole order reversed, 70.1; but 128^3 in FP64 304.3 and 305.8).
 // ---------------------------------------------------------------------------
 __device__ inline unsigned tile_id(const KP &kp, bool descending = false) {
     const unsigned b = blockIdx.x, nb = gridDim.x;
-    if (!kp.xcd_remap && !descending) return b;
+    if (!kp.xcd_remap && !(descending && kp.keep2)) return descending ? nb - 1 - b : b;
     const unsigned q = nb >> 3, r = nb & 7u, k = b & 7u;
     const unsigned i = descending ? q + (k < r ? 1 : 0) - 1 - (b >> 3) : b >> 3;
     return kp.xcd_remap ? k * q + (k < r ? k : r) + i : i * 8 + k;
