@@ -900,7 +900,7 @@ static size_t block_slots(const KP &kp, int cz) {
 // Planes per block of the step that runs chain and collide-stream in one
 // launch (0: two).  It saves a launch and the 7 fields between the two, and
 // pays with latency that few resident blocks hide and with the slots of its
-// last tiles and chunks.  FP64 gains to 1.5e6 slots (us per step, two launches /
+// last tiles and chunks.  FP64 gains to 1.5 x 2^20 slots (us per step, two launches /
 // one: 32^3 19.6 / 16.7, 64^3 49.4 / 40.4, 101 x 67 x 53 77.6 / 70.1, 96^3 135 /
 // 122, 112^3 199 / 193, but 116^3 262 / 273 and 512 x 512 x 5 189 / 245 on 1.8e6
 // and 2.1e6 slots), between walls to 2^20 (still, moving: 80^3 89 / 84, 95 / 83;
@@ -908,7 +908,10 @@ static size_t block_slots(const KP &kp, int cz) {
 // 201; 192 x 192 x 24 132 / 138, 141 / 157; 400 x 400 x 5 89 / 113, 102 / 128).  FP32
 // gains to 2^19 nodes (32^3 16.6 / 14.0, 64^3 33.6 / 30.8, 80^3 53.2 / 46.9, walls
 // 58.6 / 49.8, moving 67.6 / 51.0, 96^3 80.5 / 84.2), FP16 populations to 5 x 2^16
-// (32^3 16.6 / 12.9, 64^3 31.4 / 27.6, 101 x 67 x 45 33.4 / 34.6, walls 40.9 / 37.3).
+// (32^3 16.6 / 12.9, 64^3 31.4 / 27.6, 101 x 67 x 45 33.4 / 34.6, walls 40.9 / 37.3),
+// both to 2^17 where a single plane lies beside both walls (FP32 300 x 200 21.3 /
+// 18.6, 400 x 300 28.0 / 28.8, 700 x 700 77 / 83, moving 101 / 124; FP16 moving 450 x
+// 450 53 / 62).
 // Between walls FP64 blocks of 4 planes take the LDS of one block per CU: 2
 // planes (80^3 83 against 88).
 int step_block_chunk(const KP &kp, int prec) {
@@ -917,7 +920,9 @@ int step_block_chunk(const KP &kp, int prec) {
     if (given > 0 && given != 1 && given != 2 && given != 4) return 0;
     const int cz = given > 0 ? given : min(block_chunk(kp), kp.walls && prec == LBFE_FP64 ? 2 : 4);
     const bool small = prec == LBFE_FP64 ? block_slots(kp, cz) < (kp.walls ? 1u << 20 : 3u << 19)
-                                         : kp.nfluid < (prec == LBFE_FP32 ? 1u << 19 : 5u << 16);
+                       : kp.nfluid < (kp.walls && kp.z1 - kp.z0 == 1 ? 1u << 17
+                                      : prec == LBFE_FP32            ? 1u << 19
+                                                                     : 5u << 16);
     return small && block_chunks_fit(kp, cz) ? cz : 0;
 }
 

@@ -38,11 +38,14 @@ OM = [1.0, 1.0, 1.0, 0.5] + [1.0] * 7
 
 
 @pytest.mark.parametrize("wall_u", [(0.0, 0.0, 0.0, 0.0), (0.02, 0.0, -0.01, 0.01)])
-@pytest.mark.parametrize("shape,precision", [((90, 88, 90), "fp64"),     # one launch, non-temporal population loads
-                                             ((3, 701, 700), "fp32"),    # the same, both walls beside the one plane
-                                             ((5, 400, 400), "fp64"),    # two launches: mostly blocks beside a wall
-                                             ((4, 350, 701), "fp16dev_f0fp32")])  # chunks of the grid's two planes
-def test_walled_routes_equal_the_march(shape, precision, wall_u):
+@pytest.mark.parametrize("shape,precision,adjoint", [
+    ((90, 88, 90), "fp64", 0),              # one launch, non-temporal population loads
+    ((26, 150, 145), "fp32", 1),            # the same (a reverse context counts its lattices twice)
+    ((3, 701, 700), "fp32", 0),             # two launches: one plane beside both walls
+    ((3, 300, 201), "fp32", 0),             # one
+    ((5, 400, 400), "fp64", 0),             # two: mostly blocks beside a wall
+    ((4, 350, 701), "fp16dev_f0fp32", 0)])  # chunks of the grid's two planes
+def test_walled_routes_equal_the_march(shape, precision, adjoint, wall_u):
     nz, ny, nx = shape
     T = eos.temperature(0.8)
     say(f"walled route: {shape} {precision} {wall_u}")
@@ -50,7 +53,7 @@ def test_walled_routes_equal_the_march(shape, precision, wall_u):
     out = []
     for chunk in (0, 64):
         sim = make_sim(nx=nx, ny=ny, nz=nz, T=T, walls_z=1, wet_mode=1, wet_value=1.2, omega=OM, precision=precision,
-                       wall_u=wall_u, chain_chunk=chunk)
+                       wall_u=wall_u, chain_chunk=chunk, adjoint=adjoint)
         sim.init_density(rho0)
         sim.step(3)
         out.append((sim.get_state(), sim.field(2)))
