@@ -431,12 +431,15 @@ __global__ __launch_bounds__(NTC) void k_chain_march(KP kp, const double *__rest
             if (p <= ze + 1 && has) {
                 double P2[RB], mid[RB];
                 smooth_rows<WR, RB>(sr[s0 == 0 ? 4 : s0 - 1], cr, P2, mid);
-                // (the mu0 of a solid plane is its mu, from k_wall_planes)
-                const double kap6 = solid(g2) ? 0.0 : kp.kappa * 6.0;
+                // (the mu0 of a solid plane is its mu, from k_wall_planes, whatever
+                // the planes beside it hold)
+                const double kap6 = kp.kappa * 6.0;
+                const bool sol = solid(g2);
 #pragma unroll
                 for (int i = 0; i < RB; ++i) {
                     const double s27 = A1 * P0[i] + A0 * P1[i] + A1 * P2[i];
-                    v[i] = (MU0 ? mu_bulk(kp, rc[i]) : m0[i]) - kap6 * (s27 - rc[i]);
+                    const double d = s27 - rc[i];
+                    v[i] = (MU0 ? mu_bulk(kp, rc[i]) : m0[i]) - kap6 * (WALLS && sol ? 0.0 : d);
                     P0[i] = P1[i];
                     P1[i] = P2[i];
                     rc[i] = mid[i];

@@ -119,3 +119,29 @@ def test_fused_step_with_the_march_between_walls(shape, precision, wall_u):
             for which in range(6):
                 assert torch.equal(s.field(which), ref.field(which)), (n, which)
             assert torch.equal(s.get_state(), ref.get_state())
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_bad_density_stays_on_its_side_of_the_walls(precision, value):
+    """A NaN or an infinity beside the top wall: the step reports it, every
+    route spreads it alike, and nothing crosses to the bottom wall through the
+    periodic wrap of the planes."""
+    shape = nz, ny, nx = (14, 18, 70)
+    T = eos.temperature(0.8)
+    rho0 = torch.tensor(droplet_rho(shape, T, walls=True, radius=4.0))
+    out = []
+    for chunk in (0, 64, 3):
+        sim = make_sim(nx=nx, ny=ny, nz=nz, T=T, walls_z=1, wet_mode=1, wet_value=1.2, omega=OM, precision=precision,
+                       chain_chunk=chunk, step_path=lbfe.PATH_TWO_PASS)
+        sim.init_density(rho0)
+        f = sim.populations()
+        f[5, nz - 2, 9, 33] = value
+        sim.set_populations(f)
+        with pytest.raises(lbfe.LBFEError) as e:
+            sim.step(1)
+        assert e.value.code == lbfe.E_DIVERGED
+        out.append(sim.populations())
+    for g in out[1:]:
+        assert torch.equal(torch.isfinite(g), torch.isfinite(out[0]))
+    assert bool(torch.isfinite(out[0][:, :7]).all()) and not bool(torch.isfinite(out[0]).all())
