@@ -204,6 +204,15 @@ int need_init(lbfe_ctx *c) {
     return LBFE_OK;
 }
 
+// The moments of f[cur] have to be formed before its fields: always in a
+// capture, whose replays find whatever state the lattice then holds.
+bool need_moments(const lbfe_ctx *c) {
+    if (!c->aux_ok) return true;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) != hipSuccess) (void)hipGetLastError();
+    return st != hipStreamCaptureStatusNone;
+}
+
 int read_flag(lbfe_ctx *c, int &flag) {
     hipError_t e = hipMemcpyAsync(&flag, c->b.flag, sizeof(int), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -677,7 +686,7 @@ int lbfe_field(lbfe_ctx *c, int which, double *out) {
     if (r) return r;
     if (!out) return fail(c, LBFE_E_INVAL, "null output");
     if (which < LBFE_FIELD_RHO || which > LBFE_FIELD_PM) return fail(c, LBFE_E_INVAL, "unknown field");
-    hipError_t e = launch_aux(c->stream, c->p.precision, c->kp, c->b, c->cur, !c->aux_ok);
+    hipError_t e = launch_aux(c->stream, c->p.precision, c->kp, c->b, c->cur, need_moments(c));
     if (e == hipSuccess) e = launch_export(c->stream, c->p.precision, c->kp, c->b, which, out);
     if (e != hipSuccess) return hip_fail(c, e, "field export");
     return LBFE_OK;
@@ -686,7 +695,7 @@ int lbfe_field(lbfe_ctx *c, int which, double *out) {
 int lbfe_fields(lbfe_ctx *c, double *rho, double *u, double *mu, double *F) {
     int r = need_init(c);
     if (r) return r;
-    hipError_t e = launch_aux(c->stream, c->p.precision, c->kp, c->b, c->cur, !c->aux_ok);
+    hipError_t e = launch_aux(c->stream, c->p.precision, c->kp, c->b, c->cur, need_moments(c));
     if (e == hipSuccess && rho) e = launch_export(c->stream, c->p.precision, c->kp, c->b, LBFE_FIELD_RHO, rho);
     if (e == hipSuccess && u) e = launch_export(c->stream, c->p.precision, c->kp, c->b, LBFE_FIELD_U, u);
     if (e == hipSuccess && mu) e = launch_export(c->stream, c->p.precision, c->kp, c->b, LBFE_FIELD_MU, mu);
@@ -749,7 +758,7 @@ int lbfe_reduce(lbfe_ctx *c, double out[8]) {
     int r = need_init(c);
     if (r) return r;
     if (!out) return fail(c, LBFE_E_INVAL, "null output");
-    hipError_t e = launch_aux(c->stream, c->p.precision, c->kp, c->b, c->cur, !c->aux_ok);
+    hipError_t e = launch_aux(c->stream, c->p.precision, c->kp, c->b, c->cur, need_moments(c));
     if (e == hipSuccess) e = launch_reduce(c->stream, c->p.precision, c->kp, c->b);
     if (e == hipSuccess) e = hipMemcpyAsync(out, c->b.red, 8 * sizeof(double), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
@@ -771,7 +780,7 @@ int lbfe_reduce_into(lbfe_ctx *c, double *out_dev) {
     double *part = nullptr;
     hipError_t e = scratch_partials(c->device, &part);
     if (e != hipSuccess) return hip_fail(c, e, "reduce_into: scratch address");
-    e = launch_aux(c->stream, c->p.precision, c->kp, c->b, c->cur, !c->aux_ok);
+    e = launch_aux(c->stream, c->p.precision, c->kp, c->b, c->cur, need_moments(c));
     if (e == hipSuccess) e = launch_reduce_into(c->stream, c->p.precision, c->kp, c->b, part, out_dev);
     if (e != hipSuccess) return hip_fail(c, e, "reduce_into");
     return LBFE_OK;
