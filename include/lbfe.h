@@ -226,11 +226,13 @@ int lbfe_step(lbfe_ctx *ctx, int64_t nsteps);
  * kernel_ms[k] receives the summed milliseconds of class k over the nsteps
  * steps: 0 moments pass (with the wall density after it; on the fused path
  * only after the state was set from outside), 1 stencil chain (mu, force,
- * Q; zero where it runs inside the collide kernel), 2 collide-stream (fused
- * path: with the next step's moments), 3 wall density after the step (fused
- * path, walls only; zero on large grids, whose chain forms it).  On the state path: 0 the moments passes (with the
- * populations at the end and the wall density), 1 the chains, 2 the collide
- * passes (the first from the populations), 3 zero.  Synchronises after every
+ * Q; no launch where it runs inside the collide kernel), 2 collide-stream
+ * (fused path: with the next step's moments), 3 wall density after the step
+ * (fused path, walls only; no launch on large grids, whose chain forms it); an
+ * interval without a launch still holds the time between its two events.  On
+ * the state path: 0 the moments passes (with the populations at the end and
+ * the wall density), 1 the chains, 2 the collide passes (the first from the
+ * populations), 3 zero.  Synchronises after every
  * step (host array). */
 int lbfe_step_timed(lbfe_ctx *ctx, int64_t nsteps, double kernel_ms[4]);
 

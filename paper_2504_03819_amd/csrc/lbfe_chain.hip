@@ -1,6 +1,7 @@
-// The stencil chain of one step on gfx950, one kernel:
+// The stencil chain of one step on gfx950:
 //   rho  -> mu = mu0 - kappa lap_h rho                      (Eq. (32))
-//           (mu0 = mu0(rho) per node comes from the moments kernel)
+//           (mu0 = mu0(rho) per node comes from the pass that formed rho, on
+//           large periodic grids it is formed here)
 //        -> solid-node mu by the wall average              (Eq. (36))
 //   mu   -> G = grad_h mu, F = (1/3 - rho) G,               (Eq. (12))
 //           u = (j + F/2)/rho, phi = (p_m - rho/3) u
@@ -522,7 +523,7 @@ __global__ __launch_bounds__(WNT) void k_wall_planes(KP kp, double *rho, double 
 // k_wall_move): two launches a step instead of five (us per step with the wall
 // kernels apart / inside, moving walls: FP64 32^3 26.2 / 17.3, 101 x 67 x 53 77.0
 // / 68.1; FP32 64^3 37.5 / 30.4; still walls: FP64 32^3 20.5 / 17.6, 64^3 48.8 /
-// 46.1, 80^3 81.6 / 82.5).
+// 46.1, but 80^3 81.3 / 83.3 before 96^3 139 / 136).
 // ---------------------------------------------------------------------------
 constexpr int kFields = -1;  // P: mu, F and Q to memory, no collision
 template <int P, class real, bool WALLS, int TX, int TY, int CZ, int NT, bool NTL>

@@ -3,7 +3,7 @@
 //
 // One time step t -> t+1 on the post-streaming state f(t):
 //   k_moments   rho (double), j = sum f c, mu0(rho)          Eqs. (11), (32)
-//   k_wall_rho  density of the solid nodes (walls only)         Eqs. (37)-(38)
+//   k_wall_rho  density of the solid planes (small walled grids) Eqs. (37)-(38)
 //   k_chain_*   mu, mu at walls, F, u, phi and Q from rho, j, mu0 with
 //               LDS-staged stencils (lbfe_chain.hip)
 //                                              Eqs. (12), (27), (32), (36)
@@ -12,7 +12,8 @@
 // On small grids k_chain_block also collides, streams and forms the walls'
 // density and velocity term (lbfe_chain.hip).  On large FP64 and FP32 grids
 // k_fused (lbfe_fused.hip) collides, streams and forms rho, j, mu0 of f(t+1),
-// and k_moments runs only when the populations were set from outside.
+// and k_moments runs only when the populations were set from outside; between
+// walls the chain then forms the solid planes (k_wall_planes).
 // Populations are row-blocked (each x-row holds its 27 populations as 27
 // contiguous runs); one thread per node, x fastest, so every population load
 // and store of a wave64 is one contiguous 64-element run.

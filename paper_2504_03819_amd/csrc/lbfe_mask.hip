@@ -309,8 +309,7 @@ __global__ __launch_bounds__(ZCB) void k_fphi_z(KP kp, const unsigned *nbr, cons
 
 // ---- the FP64 stencils -------------------------------------------------------
 // In FP64 the three stencils are factored (lbfe_factored.h; the narrow forms
-// keep the point-by-point sums above, whose roundings their stored values
-// depend on): mu in one march, then F, phi and Q in another that keeps phi in
+// still have the point-by-point sums above): mu in one march, then F, phi and Q in another that keeps phi in
 // LDS.  At 192x192x96 the two take 29 and 66 us (20 and 120 B per node without
 // the halos), where the three point-by-point passes took 39, 66 and 79 us.
 
