@@ -474,7 +474,7 @@ int lbfe_create(const lbfe_params *p, void *hip_stream, lbfe_ctx **out) {
     const size_t real = real_bytes(q.precision);
     size_t node = 24 + 9 * real;  // rho, mu, mu0; j, F, Q
     if (k.masked) node += 4 + (q.precision == LBFE_FP64 ? 0 : 3 * real);  // neighbour word, phi
-    const size_t row = k.nx * (q.precision == LBFE_FP64 ? 8 : (q.precision == LBFE_FP32 ? 4 : 2));
+    const size_t row = (size_t)k.nx * (q.precision == LBFE_FP64 ? 8 : (q.precision == LBFE_FP32 ? 4 : 2));
     k.keep1 = lattice + node * k.N * sets < ((size_t)(row % 128 == 0 ? 320 : 344) << 20);
     k.keep2 = lattice < ((size_t)112 << 20);
     // Planes per workgroup of the stencil chain, chosen per grid unless given.

@@ -285,11 +285,12 @@ bool fused_plane_ok(int prec, size_t plane) {
 // slower.
 bool fused_fills(int prec, unsigned nx, unsigned ny) {
     const bool wide = prec == LBFE_FP64;
-    const unsigned tx = wide ? Tile<LBFE_FP64>::TX : Tile<LBFE_FP32>::TX, ty = wide ? Tile<LBFE_FP64>::TY : Tile<LBFE_FP32>::TY;
+    const unsigned tx = wide ? Tile<LBFE_FP64>::TX : Tile<LBFE_FP32>::TX;
+    const unsigned ty = wide ? Tile<LBFE_FP64>::TY : Tile<LBFE_FP32>::TY;
     const size_t plane = (size_t)nx * ny, slots = (size_t)((nx + tx - 1) / tx * tx) * ((ny + ty - 1) / ty * ty);
     if (plane * 100 >= slots * (wide ? 70 : 85)) return true;
     const size_t row = nx * real_bytes(prec);
-    return row % 128 != 0 && 3 * 27 * ny * row > ((size_t)4 << 20);
+    return row % 128 != 0 && row * ny * 81 > ((size_t)4 << 20);  // 3 planes of 27 populations
 }
 
 hipError_t launch_fused(hipStream_t s, int prec, const KP &kp, const Bufs &b, int cur) {
